@@ -15,6 +15,7 @@ namespace {
 struct G5State {
     pgh_ctx *ctx = nullptr;
     bool table = false;
+    int num_cu = 256;
     int n = 0;  // g5_set_n, applied when forces are computed (it may precede g5_set_xmj)
     // device staging, FP32 structure of arrays
     float *dj = nullptr;  // 4 x jcap: x, y, z, m
@@ -86,6 +87,10 @@ void g5_open(void)
     }
     g5.ctx = c;
     g5.table = false;
+    int ncu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0) == hipSuccess &&
+        ncu > 0)
+        g5.num_cu = ncu;
 }
 
 void g5_close(void)
@@ -165,9 +170,18 @@ void g5_calculate_force_on_x(double (*xi)[3], double (*ai)[3], double *pi, int n
     if (g5.table)
         st = pgh_calc_table(g5.ctx, ni, d, d + cap, d + 2 * cap, d + 3 * cap, d + 4 * cap,
                             d + 5 * cap, nullptr);
-    else
+    else {
+        // Forces handed out in double show every change of the FP32 summation
+        // order, and a host program pays for conversions and transfers far
+        // more than for the kernel (N = 16384: 95 of 290 us), so these calls
+        // keep one order: the LDS-tile kernels with one, or from 2^17
+        // i-particles up four, per lane (64-record tiles for few i-particles)
+        const int v = ni <= 4 * g5.num_cu ? 1 : ni >= (1 << 17) ? 3 : 0;
+        if (!check(pgh_set_variant(g5.ctx, PGH_FAMILY_NEWTON_ALLPAIRS, v), "g5_calculate_force_on_x"))
+            return;
         st = pgh_calc_newton(g5.ctx, ni, d, d + cap, d + 2 * cap, nullptr, d + 3 * cap,
                              d + 4 * cap, d + 5 * cap, pi ? d + 6 * cap : nullptr);
+    }
     if (!check(st, "g5_calculate_force_on_x")) return;
     const int outs = (!g5.table && pi) ? 4 : 3;
     for (int a = 0; a < outs; ++a)

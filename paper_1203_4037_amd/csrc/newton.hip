@@ -26,6 +26,9 @@
 // transcendental unit issues beside the VALU, so this trades one VALU op
 // per pair for a second transcendental.
 //
+// The "rows" kernel turns the mapping round: a workgroup holds TI i-particles
+// as wave-uniform values, its lanes take j-particles (k_newton_rows below).
+//
 // Accuracy.  Sums over a tile are formed in fresh registers and added to
 // the running totals once per tile, so FP32 rounding grows with
 // JT + nj/JT rather than nj.
@@ -55,36 +58,38 @@ hipError_t launch_pack_j(int n, const float *x, const float *y, const float *z, 
 }
 
 // Adds the S partial sums [S][4][n] of a j-split launch in split order
-// (ax..az and phi each optional).
+// (ax..az and phi each optional): blockIdx.y is the component, and eight
+// shares' loads are in flight at once, so S shares cost S / 8 memory
+// latencies (one thread per particle with its four loads a share waited for in
+// turn took 16.6 us for 27 shares of 20011 particles).
 __global__ void __launch_bounds__(256) k_combine_split(int n, int S, const float *__restrict__ part,
                                                        float *ax, float *ay, float *az, float *phi)
 {
+    const int c = blockIdx.y;
+    float *const out = c == 0 ? ax : c == 1 ? ay : c == 2 ? az : phi;
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float sx = 0.f, sy = 0.f, sz = 0.f, sp = 0.f;
-    for (int s = 0; s < S; ++s) {
-        const float *p = part + (size_t)s * 4 * n;
-        if (ax) {
-            sx += p[i];
-            sy += p[n + i];
-            sz += p[2 * n + i];
-        }
-        if (phi) sp += p[3 * n + i];
+    if (i >= n || !out) return;
+    const float *p = part + (size_t)c * n + i;
+    const size_t step = (size_t)4 * n;
+    float sum = 0.f;
+    int s = 0;
+    for (; s + 8 <= S; s += 8) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = p[(size_t)(s + k) * step];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum += v[k];
     }
-    if (ax) {
-        ax[i] = sx;
-        ay[i] = sy;
-        az[i] = sz;
-    }
-    if (phi) phi[i] = sp;
+    for (; s < S; ++s) sum += p[(size_t)s * step];
+    out[i] = sum;
 }
 
 hipError_t launch_combine_split(int n, int S, const float *part, float *ax, float *ay, float *az,
                                 float *phi, hipStream_t s)
 {
     if (n <= 0 || S <= 1) return hipSuccess;
-    hipLaunchKernelGGL(k_combine_split, dim3((n + 255) / 256), dim3(256), 0, s, n, S, part, ax, ay,
-                       az, phi);
+    hipLaunchKernelGGL(k_combine_split, dim3((n + 255) / 256, phi ? 4 : 3), dim3(256), 0, s, n, S,
+                       part, ax, ay, az, phi);
     return hipGetLastError();
 }
 
@@ -239,6 +244,142 @@ __global__ void __launch_bounds__(256) k_newton_allpairs(NewtonArgs a)
     }
 }
 
+// Sums over the lanes of a wave, two or four values at a time: v_permlane32_swap
+// exchanges the upper half of a with the lower half of b, so one add leaves
+// a's sum over lane pairs (l, l + 32) in the lower half and b's in the upper;
+// v_permlane16_swap does the same with rows of 16.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ float fold_halves(float a, float b)
+{
+    const u32x2 r =
+        __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
+__device__ __forceinline__ float fold_rows(float a, float b)
+{
+    const u32x2 r =
+        __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v)
+{
+    return __uint_as_float(
+        (unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+
+// The sum over each row of 16 lanes, in all of them (row_ror 8, 4, 2, 1).
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += dpp_f32<0x128>(v);
+    v += dpp_f32<0x124>(v);
+    v += dpp_f32<0x122>(v);
+    v += dpp_f32<0x121>(v);
+    return v;
+}
+
+// The "rows" kernel: TI i-particles per workgroup, the same for all its lanes
+// (held in SGPRs), and the j-particles dealt over its NT lanes: each lane
+// loads its own j-record straight from global memory (coalesced, two records
+// ahead) and uses it for TI pairs.  No LDS traffic, no barrier and no partial
+// sums in memory: the lanes' sums meet once, at the end.
+//
+// Bound by FP32 issue like k_newton_allpairs (the SGPR operand of the three
+// subtractions costs nothing measurable beside VGPR copies).  The point of
+// the mapping is that ni / TI workgroups fill the chip where ni / 256
+// cannot: the other kernel then takes its waves from the j-split, whose
+// partial sums cost a second launch and memory traffic, and whose shares of
+// whole 256-record tiles leave the last round of workgroups partly idle.
+// Measured, whole call (pack, force, combine) before and after:
+// N = 1024 14.9 -> 5 us of kernels, 256 x 4096 25.4 -> 5.5 us, 4096 22.2 -> 8
+// us of force, 20011 174 -> 128 us, 65536 1.29 -> 1.27 ms, 131072 5.34 ->
+// 5.07 ms.  The record two steps ahead matters: with the load of the next
+// record waited for at once, N = 65536 took 1.63 ms.
+template <int TI, int NT, bool REFINE, bool GUARD, bool PHI>
+__global__ void __launch_bounds__(NT) k_newton_rows(NewtonArgs a)
+{
+    constexpr int V = 4 * TI;   // sums per workgroup
+    constexpr int W = NT / 64;
+    __shared__ float red[W][V];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i0 = blockIdx.x * TI;
+    const float mscale = REFINE ? -0.5f : 1.0f;
+
+    float px[TI], py[TI], pz[TI], pe[TI], s[TI][4];
+#pragma unroll
+    for (int k = 0; k < TI; ++k) {
+        const int i = min(i0 + k, a.ni - 1);
+        px[k] = a.xi[i];
+        py[k] = a.yi[i];
+        pz[k] = a.zi[i];
+        pe[k] = a.eps2i ? a.eps2i[i] : a.eps2_all;
+        s[k][0] = s[k][1] = s[k][2] = s[k][3] = 0.f;
+    }
+    auto pairs = [&](float4 p) {
+        p.w *= mscale;
+#pragma unroll
+        for (int k = 0; k < TI; ++k)
+            newton_pair<REFINE, GUARD, PHI, false>(p, px[k], py[k], pz[k], pe[k], s[k][0], s[k][1],
+                                                   s[k][2], s[k][3]);
+    };
+
+    // this workgroup's share of the j-particles (blockIdx.y splits them; no
+    // share is empty)
+    const int jbase = blockIdx.y * a.jchunk;
+    const int nj = min(a.jchunk, a.nj - jbase);
+    const float4 *__restrict__ jm = a.jmem + jbase;
+    const int full = nj / NT;  // steps in which every lane has a record
+    // unconditional loads (past the end the last record, not used), so that
+    // no branch makes the compiler wait for one before the next is issued
+    auto load = [&](int t) { return jm[min(t * NT + tid, nj - 1)]; };
+    float4 p0 = load(0), p1 = load(1);
+    int t = 0;
+    for (; t + 2 <= full; t += 2) {
+        pairs(p0);
+        p0 = load(t + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        pairs(p1);
+        p1 = load(t + 3);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (t < full) {
+        pairs(p0);
+        p0 = p1;
+        ++t;
+    }
+    if (t * NT < nj) {
+        // a zero-mass record far away adds exactly zero, also unsoftened
+        if (t * NT + tid >= nj) p0 = make_float4(1.0e10f, 1.0e10f, 1.0e10f, 0.f);
+        pairs(p0);
+    }
+
+#pragma unroll
+    for (int k = 0; k < TI; ++k) {
+        // rows 0 .. 3 of the wave now hold the sums x, z, y, phi
+        const float v =
+            row_sum(fold_rows(fold_halves(s[k][0], s[k][1]), fold_halves(s[k][2], s[k][3])));
+        const int row = lane >> 4, c = ((row & 1) << 1) | (row >> 1);
+        if ((lane & 15) == 0) red[wave][4 * k + c] = v;
+    }
+    __syncthreads();
+    if (tid < V) {
+        float r = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) r += red[w][tid];
+        const int c = tid & 3, i = i0 + (tid >> 2);
+        if (REFINE && c < 3) r *= 0.25f;
+        if (i < a.ni) {
+            if (gridDim.y > 1)
+                a.part[((size_t)blockIdx.y * 4 + c) * a.ni + i] = r;
+            else if (c < 3 || PHI)
+                (c == 0 ? a.ax : c == 1 ? a.ay : c == 2 ? a.az : a.phi)[i] = r;
+        }
+    }
+}
+
 using NewtonKernel = void (*)(NewtonArgs);
 
 template <int KI, int JT, int U, bool RCP>
@@ -259,6 +400,73 @@ struct NewtonSet {
     }
 };
 
+template <int TI, int NT>
+NewtonKernel rows_kernel_t(bool refine, bool guard, bool phi)
+{
+    const int sel = (refine ? 4 : 0) | (guard ? 2 : 0) | (phi ? 1 : 0);
+    switch (sel) {
+        case 0: return k_newton_rows<TI, NT, false, false, false>;
+        case 1: return k_newton_rows<TI, NT, false, false, true>;
+        case 2: return k_newton_rows<TI, NT, false, true, false>;
+        case 3: return k_newton_rows<TI, NT, false, true, true>;
+        case 4: return k_newton_rows<TI, NT, true, false, false>;
+        case 5: return k_newton_rows<TI, NT, true, false, true>;
+        case 6: return k_newton_rows<TI, NT, true, true, false>;
+        default: return k_newton_rows<TI, NT, true, true, true>;
+    }
+}
+
+// The shape of a rows launch: i-particles and threads per workgroup, and the
+// j-shares it asks for.
+struct RowsShape {
+    int ti, nt, shares;
+};
+
+RowsShape rows_shape(int ni, int nj)
+{
+    RowsShape r;
+    // More i-particles per workgroup save j-record loads and end-of-loop
+    // sums, fewer give the workgroups that fill 256 CUs eight deep.  us of
+    // force at TI = 2, 4, 8: N = 4096 7.9, 8.0, 8.5; 6000 16.2, 15.2, 15.5;
+    // 8192 28.1, 24.7, 24.8; 11000 -, 42.8, 45.1; 16384 -, 89.0, 85.1; 65536
+    // -, 1355, 1266.  Few i-particles over a long list are bound by reading it
+    // from the L2 (1000 x 60000: TI = 2, 4 24.3, 23.6; 300 x 262144, shares
+    // alike: 38.6, 36.0), else by latency (256 x 4096: TI = 1, 2, 4 3.0, 3.2, 4.0).
+    // Lists of more than the 4 MiB of an L2 take the most, and shares below.
+    const bool beyond_l2 = nj >= 1 << 18 && ni >= 2000;
+    if (ni >= 12000 || beyond_l2)
+        r.ti = 8;
+    else if (ni >= 4500 || (ni >= 500 && nj >= 32768) || (ni >= 200 && nj >= 65536))
+        r.ti = 4;
+    else
+        r.ti = ni >= 200 ? 2 : 1;
+    const long groups = ((long)ni + r.ti - 1) / r.ti;
+    // sixteen waves per workgroup where there are few workgroups and at least
+    // four records per lane (300 x 16384, four and sixteen waves: 6.4, 5.2 us)
+    r.nt = r.ti <= 4 && groups < 1024 && nj >= 4096 ? 1024 : 256;
+    // and shares of at least 8192 records where even these leave the chip idle
+    // (64 x 60000, one and eight shares: 9.6, 6.7 us, the second launch included)
+    const long waves = groups * (r.nt / 64);
+    r.shares = 1;
+    if (waves < (beyond_l2 ? 4096 : 2048))
+        r.shares = (int)std::max(1L, std::min(((beyond_l2 ? 8192 : 4096) + waves - 1) / waves,
+                                              (long)nj / 8192));
+    return r;
+}
+
+NewtonKernel rows_kernel(const RowsShape &r, bool refine, bool guard, bool phi)
+{
+    if (r.nt == 1024)
+        return (r.ti == 1   ? &rows_kernel_t<1, 1024>
+                : r.ti == 2 ? &rows_kernel_t<2, 1024>
+                            : &rows_kernel_t<4, 1024>)(refine, guard, phi);
+    return (r.ti == 1   ? &rows_kernel_t<1, 256>
+            : r.ti == 2 ? &rows_kernel_t<2, 256>
+            : r.ti == 4 ? &rows_kernel_t<4, 256>
+                        : &rows_kernel_t<8, 256>)(refine, guard, phi);
+}
+
+// ki = 0: the rows kernel, whose shape follows from the sizes (rows_shape).
 struct NewtonVariant {
     const char *name;
     int ki, jt;
@@ -274,7 +482,9 @@ const NewtonVariant kNewtonVariants[] = {
     {"ki=1 jt=256 u=8 rcp", 1, 256, &NewtonSet<1, 256, 8, true>::get},
     {"ki=2 jt=256 u=4 rcp", 2, 256, &NewtonSet<2, 256, 4, true>::get},
     {"ki=4 jt=256 u=2 rcp", 4, 256, &NewtonSet<4, 256, 2, true>::get},
+    {"rows", 0, 64, nullptr},
 };
+constexpr int kRowsVariant = 8;
 constexpr int kNumNewtonVariants = sizeof(kNewtonVariants) / sizeof(kNewtonVariants[0]);
 
 }  // namespace
@@ -288,21 +498,31 @@ const char *newton_allpairs_variant_name(int v)
 
 int newton_allpairs_default(int ni, int nj, int num_cu)
 {
-    (void)nj;
-    // Measured with the j-split that holds 8 waves per SIMD: from 2^17
-    // i-particles up, four per lane (fewer j-tile reads per pair) are the
-    // fastest (N = 262144: 20.3 ms against 21.5 for one per lane); below, one
-    // per lane keeps the shares long enough; an i-set of at most 16 waves per
-    // 256 CUs takes the 64-record tiles, so that the j-split (one tile per
-    // share at least) gives it a wave per CU or more.  pgh_autotune confirms
-    // or replaces the choice for a given workload.
-    if (ni <= 4 * num_cu) return 1;
-    return ni >= (1 << 17) ? 3 : 0;
+    // Lists too short to give each lane of a workgroup a record: one
+    // i-particle per lane (100000 x 100: the rows kernel 20 us, this 17 us).
+    if (nj < 256 && ni >= 16384) return 0;
+    // From 196608 i-particles up, four per lane over LDS tiles, when the
+    // workgroups of its j-split spread evenly over the CUs (N = 262144: 19.1
+    // against 19.9 ms with rows, 230000 15.1 against 15.4, 10^6 292 against
+    // 308), which loses more than that otherwise (8 or 9 workgroups a CU at N =
+    // 300000: 28.3 against 26.1 ms; 400000: 50.5 against 47.1).  Below, rows
+    // (131072: 5.02 against 5.08 ms, 65536: 1.27 against 1.29 with one per
+    // lane, and more the smaller the set).  pgh_autotune confirms or replaces
+    // the choice for a given workload.
+    if (ni < 3 << 16) return kRowsVariant;
+    const long groups = ((ni + 1023L) / 1024) * newton_allpairs_split(ni, nj, 3, (size_t)64 << 20);
+    const long per_cu = (groups + num_cu - 1) / num_cu;
+    return 20 * groups >= 19 * per_cu * num_cu ? 3 : kRowsVariant;
 }
+
+int newton_allpairs_rows() { return kRowsVariant; }
 
 int newton_allpairs_split(int ni, int nj, int variant, size_t part_cap)
 {
     const NewtonVariant &v = kNewtonVariants[variant];
+    if (v.ki == 0)
+        return (int)std::max(1L, std::min((long)rows_shape(ni, nj).shares,
+                                          (long)(part_cap / (4 * (size_t)std::max(ni, 1)))));
     return split_count(ni, nj, v.ki, v.jt, kSplitTargetWaves, part_cap);
 }
 
@@ -315,6 +535,14 @@ hipError_t launch_newton_allpairs(const NewtonArgs &a0, int variant, bool refine
     S = std::max(1, S);
     a.jchunk = (int)(((long)a.nj + (long)S * v.jt - 1) / ((long)S * v.jt) * v.jt);
     S = std::max(1, (a.nj + a.jchunk - 1) / a.jchunk);
+    if (v.ki == 0) {
+        const RowsShape r = rows_shape(a.ni, a.nj);
+        hipLaunchKernelGGL(rows_kernel(r, refine, guard, a.phi != nullptr),
+                           dim3((a.ni + r.ti - 1) / r.ti, S), dim3(r.nt), 0, s, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess || S == 1) return e;
+        return launch_combine_split(a.ni, S, a.part, a0.ax, a0.ay, a0.az, a0.phi, s);
+    }
     const int per_block = 256 * v.ki;
     const dim3 grid((a.ni + per_block - 1) / per_block, S);
     hipLaunchKernelGGL(v.get(refine, guard, a.phi != nullptr), grid, dim3(256), 0, s, a);

@@ -695,8 +695,8 @@ int pgh_calc_newton_noalloc(pgh_ctx *c, int ni, const float *xi, const float *yi
     if (v < 0) {
         v = newton_allpairs_default(ni, c->nj, c->num_cu);
         // four i-particles per lane take their waves from the j-split, which
-        // the array caps: the default here keeps one per lane
-        if (v == 3) v = 0;
+        // the array caps: the rows kernel needs none
+        if (v == 3) v = newton_allpairs_rows();
     }
     // the split is limited to the shares whose partial sums fit the array
     // (S * 4 * ni floats); a launch that cannot be split needs no scratch

@@ -216,3 +216,31 @@ def test_pair_accuracy_of_the_rsqrt(pgh, ctx, refine):
     ulp = 2.0 ** -23
     assert ea.max() < 8 * ulp and rms(ea) < 1.5 * ulp, (ea.max() / ulp, rms(ea) / ulp)
     assert ep.max() < 4 * ulp and rms(ep) < ulp, (ep.max() / ulp, rms(ep) / ulp)
+
+
+@pytest.mark.parametrize("refine,zero_eps,with_phi", [(0, False, True), (1, False, False),
+                                                      (0, True, True), (1, True, True)])
+@pytest.mark.parametrize("ni,nj", [(1, 1), (5, 255), (199, 257), (200, 511), (203, 4099), (7, 4096),
+                                   (3, 17001), (500, 32769), (4501, 513), (12001, 300),
+                                   (2001, 1 << 18)])
+def test_rows_kernel_shapes(pgh, ctx, ni, nj, refine, zero_eps, with_phi):
+    """The rows kernel at the edges of its shapes: one to eight i-particles
+    per workgroup with a ragged last one, four and sixteen waves, lists shorter
+    than the lanes, one record more or less than whole steps, and shares."""
+    xj, yj, zj = synth.plummer(nj, 500 + nj)
+    xi, yi, zi = synth.plummer(ni, 600 + ni)
+    xi[0], yi[0], zi[0] = xj[0], yj[0], zj[0]  # a coincident pair
+    rng = np.random.default_rng(ni + nj)
+    mj = rng.uniform(0.1, 1.0, nj).astype(np.float32)
+    e2 = None if zero_eps else rng.uniform(1e-4, 1e-2, ni).astype(np.float32)
+    ctx.set_rsqrt_refine(refine)
+    names = [pgh.pgh_variant_name(0, v) for v in range(pgh.pgh_variant_count(0))]
+    ctx.set_variant(pgh.PGH_FAMILY_NEWTON_ALLPAIRS, names.index("rows"))
+    a, phi = _gpu_newton(ctx, xi, yi, zi, xj, yj, zj, mj, eps=0.0, eps2i=e2, with_phi=with_phi)
+    idx = np.unique(np.concatenate([np.arange(min(ni, 16)), np.arange(max(0, ni - 16), ni)]))
+    ref = oracle.newton(xi[idx], yi[idx], zi[idx], np.zeros(idx.size, np.float32) if zero_eps
+                        else e2[idx], xj, yj, zj, mj)
+    if nj > 1 or not zero_eps:
+        _check(a[:, idx], phi[idx] if with_phi else None, ref, f"rows {ni} x {nj}")
+    else:  # the coincident pair alone: nothing
+        assert np.all(a == 0) and np.all(phi == 0)
