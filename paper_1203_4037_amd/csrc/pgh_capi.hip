@@ -167,6 +167,20 @@ float table_scale(double smax, float rcut)
     return c;
 }
 
+// The least FP32 |d|^2 whose s = fma(|d|^2, c, 2) reaches s_max: pairs from
+// there on clamp to the last node (the FMA is monotone in |d|^2).
+float table_r2max(float c, double smax)
+{
+    const float top = (float)smax;
+    float r2 = (float)((smax - 2.0) / (double)c);
+    while (std::fmaf(r2, c, 2.0f) < top) r2 = std::nextafterf(r2, INFINITY);
+    for (;;) {
+        const float below = std::nextafterf(r2, 0.f);
+        if (!(below > 0.f) || std::fmaf(below, c, 2.0f) < top) return r2;
+        r2 = below;
+    }
+}
+
 int check_table_shape(pgh_ctx *c, int E, int F, float rcut)
 {
     if (E < 0 || E > 6) return fail(c, PGH_ERANGE, "E must be in [0, 6]");
@@ -857,9 +871,9 @@ int pgh_calc_table(pgh_ctx *c, int ni, const float *xi, const float *yi, const f
     DeviceGuard g(c->device);
     if (c->nj == 0) return zero_outputs(c, ni, ax, ay, az, phi);
     const double smax = smax_of(c->tab_E, c->tab_F);
-    TableArgs a{ni, xi, yi, zi, c->nj, c->jmem, c->tab, c->tab_E, c->tab_F,
-                table_scale(smax, c->tab_rcut), (float)smax, ax, ay, az, 0, nullptr,
-                phi ? c->ptab : nullptr, phi};
+    const float scale = table_scale(smax, c->tab_rcut);
+    TableArgs a{ni, xi, yi, zi, c->nj, c->jmem, c->tab, c->tab_E, c->tab_F, scale, (float)smax,
+                table_r2max(scale, smax), ax, ay, az, 0, nullptr, phi ? c->ptab : nullptr, phi};
     int v = c->variant[PGH_FAMILY_TABLE_ALLPAIRS];
     if (v < 0) v = table_allpairs_default(ni, c->nj, c->num_cu);
     const int S = table_allpairs_split(a, v, kMaxSplitFloats);
@@ -868,7 +882,7 @@ int pgh_calc_table(pgh_ctx *c, int ni, const float *xi, const float *yi, const f
         if (st) return st;
         a.part = c->part;
     }
-    PGH_HIP(c, launch_table_allpairs(a, v, S, c->stream));
+    PGH_HIP(c, launch_table_allpairs(a, v, S, c->num_cu, c->stream));
     return PGH_OK;
 }
 

@@ -44,6 +44,7 @@ struct TableArgs {
     int E, F;
     float c;     // (s_max - 2) / rcut^2
     float smax;  // 2^{2^E} (2 - 2^-F)
+    float r2max; // the least |d|^2 whose s reaches s_max
     float *ax, *ay, *az;
     int jchunk;
     float *part;
@@ -164,7 +165,8 @@ int table_allpairs_variants();
 const char *table_allpairs_variant_name(int v);
 int table_allpairs_default(int ni, int nj, int num_cu);
 int table_allpairs_split(const TableArgs &a, int variant, size_t part_cap);
-hipError_t launch_table_allpairs(const TableArgs &a, int variant, int S, hipStream_t s);
+hipError_t launch_table_allpairs(const TableArgs &a, int variant, int S, int num_cu,
+                                 hipStream_t s);
 
 int batch_resident_waves(int num_cu);  // waves of the persistent grid
 int newton_batch_variants();

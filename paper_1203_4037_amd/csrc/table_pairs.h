@@ -77,6 +77,16 @@ __device__ __forceinline__ void table_to_lds(float2 *stab, const float2 *__restr
     }
 }
 
+// Whether a position and mass are ordinary: small enough that no difference
+// of two such positions overflows when squared, and the mass finite.  A pair of
+// ordinary particles beyond the cutoff, whose node's entries are zero, adds
+// exactly zero; false also for NaN.
+__device__ __forceinline__ bool ordinary(float x, float y, float z, float m)
+{
+    return __builtin_fabsf(x) + __builtin_fabsf(y) + __builtin_fabsf(z) < 1.0e15f &&
+           __builtin_fabsf(m) <= 3.4028234e38f;
+}
+
 // The table force with the potential from a second table on the same bins
 // (P0_k = p(r_k) and chords P1_k): the LDS copy holds (G0, G1, P0, P1) per
 // node (in the HT form (H, G1, PH, P1) with PH_k = P0_k - P1_k s_k), read
