@@ -32,6 +32,7 @@
 #include <utility>
 
 #include "batch_queue.h"
+#include "table_filter.h"
 #include "table_pairs.h"
 
 namespace pgh {
@@ -39,6 +40,9 @@ namespace {
 
 // plans of at most this many tasks per wave run in the static order
 constexpr int kStaticRounds = 4;
+// k_batch_table_near evaluates a block of 64 records whole when some lane has
+// more candidates than this among its 2 x 32 pairs
+constexpr int kDirectHits = 24;
 
 // The lanes of one task: lane (phase, row) holds slots q + k stride
 // (k < KI) of its chunk (i-particles i0 + slot, the chunk's partial-sum
@@ -304,6 +308,260 @@ k_batch_table(BatchArgs a)
     }
 }
 
+// The same force with the pairs beyond the cutoff left out (table_filter.h).
+// A wave takes its task's list SB x 64 records at a time, the next ones in
+// flight meanwhile (a record a lane a step ahead left it waiting for memory
+// three quarters of the time):
+//   * records farther than the cutoff from the box around the chunk's
+//     i-particles are dropped, the others packed into the wave's LDS tile;
+//   * 64 kept records at a time, the matrix cores form |d|^2 - cutoff^2 with
+//     two columns of 32 i-particles (lane l holds l mod 32 and 32 + l mod 32);
+//     the signs give each lane a word of candidates per column, half of the
+//     rows in lanes < 32, half in the others;
+//   * each lane evaluates its own candidates one after another, in FP32 as
+//     k_batch_table does, reading each record by its own index.  Where the
+//     pairs inside the cutoff are not few (some lane has more than
+//     kDirectHits of 64) the 64 records are evaluated whole.
+// A paired task is its two chunks in turn.
+//
+// Per 64 x 64 pairs about 45 vector instructions for the operands, 64 for the
+// signs (one to two issue slots each) and four products, and 26 a round of
+// candidates, against 64 x 17 before; what is left is the launch, the first
+// loads' latency and the rounds.  Measured, per call in graphs of ten, with
+// k_batch_table (KI = 2, TW = 2, the default until then) and now: 4096 lists of
+// 4^3 cells 30.8 -> 18.1 us, 512 lists of 8^3 cells 95.6 -> 21.7, with the
+// potential 94.9 -> 22.7, with four times the cutoff (a tenth of the pairs
+// inside) 97.5 -> 62.
+//
+// MOM: also the i-side moments of the adjoint (table_tail_mom).
+template <int TB, bool PHI, int WPB, int SB, bool MOM>
+__global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(MOM || WPB > 4 ? 4 : 5, 8)))
+k_batch_table_near(BatchArgs a)
+{
+    static_assert(!MOM || !PHI, "moments come without a potential");
+    using Entry = std::conditional_t<PHI, float4, float2>;
+    __shared__ Entry stab[1 << TB];
+    __shared__ float4 jt[WPB][64 * SB];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const bool stat = a.static_order != 0;
+    const TaskStream ts = task_stream(a, WPB);
+    const unsigned G = gridDim.x * WPB;
+    const unsigned gw = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + wave);
+    const Task *const tbase = stat ? a.tasks : ts.tasks;
+    const unsigned n_t = stat ? (unsigned)a.n_tasks : ts.n_tasks;
+    unsigned round = 0;
+    unsigned t = stat ? static_task(a, 0, gw, G) : first_task(a, WPB, wave);
+    float4 *tile = jt[wave];
+
+    // an element of a uniform array at a lane's 32-bit offset; the offset is
+    // opaque, so that no address of 64 bits per lane and array is kept
+    // through the loops
+    auto at = [](const float *p, unsigned k) {
+        unsigned o = 4u * k;
+        asm volatile("" : "+v"(o));
+        return *(const float *)((const char *)p + o);
+    };
+    auto put = [](float *p, unsigned k, float v) {
+        unsigned o = 4u * k;
+        asm volatile("" : "+v"(o));
+        *(float *)((char *)p + o) = v;
+    };
+    // a chunk's i-particles (slot = lane; past the end the first) and the
+    // list's next SB records of this lane (past the end the last)
+    float ix, iy, iz;
+    float4 pre[SB];
+    auto load = [&](int j_off, int n_j, int base) {
+#pragma unroll
+        for (int s = 0; s < SB; ++s) {
+            if (base + 64 * s >= n_j) break;
+            const int j = min(base + 64 * s + lane, n_j - 1);
+            pre[s] = make_float4(at(a.xj + j_off, j), at(a.yj + j_off, j), at(a.zj + j_off, j),
+                                 at(a.mj + j_off, j));
+        }
+    };
+    auto begin = [&](int i_off, int n_i, int j_off, int n_j) {
+        const int i = lane < n_i ? lane : 0;
+        ix = at(a.xi + i_off, i);
+        iy = at(a.yi + i_off, i);
+        iz = at(a.zi + i_off, i);
+        load(j_off, n_j, 0);
+    };
+
+    Task tk{};
+    if (t < n_t) {
+        tk = tbase[t];
+        begin(tk.i_off, tk.n_i, tk.j_off, tk.n_j);
+    }
+    const int K = 1 << (a.E + a.F);
+    if (PHI)
+        tables_to_lds<false>((float4 *)stab, a.table, a.ptable, K, 0u);
+    else
+        table_to_lds<false>((float2 *)stab, a.table, K, 0u);
+    // (in SGPRs: the candidates are few and registers are not)
+    const unsigned kshift = 23u - (unsigned)a.F;
+    const TableConsts kc{a.c, __float_as_uint(a.smax), kshift - (PHI ? 4 : 3),
+                         (unsigned)(K - 1) << (PHI ? 4 : 3), ~((1u << kshift) - 1u)};
+    const char *tab = (const char *)stab;
+    __syncthreads();  // the only workgroup barrier: waves are independent after it
+    // whether pairs beyond the cutoff add exactly zero (and the cutoff is
+    // far above the smallest numbers, which the products may flush)
+    const Entry last = stab[K - 1];
+    bool last_zero = last.x == 0.f && last.y == 0.f && a.r2max > 1.0e-30f;
+    if constexpr (PHI) last_zero = last_zero && last.z == 0.f && last.w == 0.f;
+
+    while (t < n_t) {
+        const unsigned tn = stat ? 0u : pop_task(ts, lane);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), as in k_batch_table
+        const unsigned t_next =
+            stat ? static_task(a, ++round, gw, G) : __builtin_amdgcn_readfirstlane(tn);
+        int fld = 0;
+        if (t_next < n_t && lane < 12) fld = ((const int *)(tbase + t_next))[lane];
+
+        const int parts = tk.n_i2 > 0 ? 2 : 1;
+        for (int sub = 0; sub < parts; ++sub) {
+            const int i_off = sub ? tk.i_off2 : tk.i_off, n_i = sub ? tk.n_i2 : tk.n_i;
+            const int j_off = sub ? tk.j_off2 : tk.j_off, n_j = sub ? tk.n_j2 : tk.n_j;
+            if (sub) begin(i_off, n_i, j_off, n_j);
+
+            // the box around the chunk (lanes past its end hold its first
+            // i-particle), or all space when nothing may be left out
+            const bool whole = !last_zero || __any(!ordinary(ix, iy, iz, 0.f));
+            const float xl = uniform(whole ? -INFINITY : wave_min(ix)),
+                        xh = uniform(whole ? INFINITY : wave_max(ix)),
+                        yl = uniform(whole ? -INFINITY : wave_min(iy)),
+                        yh = uniform(whole ? INFINITY : wave_max(iy)),
+                        zl = uniform(whole ? -INFINITY : wave_min(iz)),
+                        zh = uniform(whole ? INFINITY : wave_max(iz));
+            const float cx = uniform(whole ? 0.f : 0.5f * (xl + xh)),
+                        cy = uniform(whole ? 0.f : 0.5f * (yl + yh)),
+                        cz = uniform(whole ? 0.f : 0.5f * (zl + zh));
+            const FilterOps cols =
+                filter_cols_of(ix, iy, iz, lane < n_i, last_zero, cx, cy, cz, a.r2max);
+            float px[2], py[2], pz[2];  // of both columns
+            both_halves(ix, px), both_halves(iy, py), both_halves(iz, pz);
+            float tx[2] = {0.f, 0.f}, ty[2] = {0.f, 0.f}, tz[2] = {0.f, 0.f}, tp[2] = {0.f, 0.f};
+            float tm[MOM ? 7 : 1][2];
+#pragma unroll
+            for (int c = 0; c < (MOM ? 7 : 1); ++c) tm[c][0] = tm[c][1] = 0.f;
+
+            for (int base = 0; base < n_j; base += 64 * SB) {
+                wave_sync();  // the previous tile's reads are done
+                int kept = 0;
+#pragma unroll
+                for (int s = 0; s < SB; ++s) {
+                    if (base + 64 * s >= n_j) break;
+                    // the distance to the box, formed as a pair's |d|^2 is:
+                    // each step is monotone, so no pair with the box's
+                    // i-particles has a smaller one
+                    const float4 v = pre[s];
+                    const float ex = __builtin_fmaxf(__builtin_fmaxf(xl - v.x, v.x - xh), 0.f);
+                    const float ey = __builtin_fmaxf(__builtin_fmaxf(yl - v.y, v.y - yh), 0.f);
+                    const float ez = __builtin_fmaxf(__builtin_fmaxf(zl - v.z, v.z - zh), 0.f);
+                    const float r2 =
+                        __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));
+                    const bool keep = base + 64 * s + lane < n_j &&
+                                      (r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
+                    const unsigned long long who = __ballot(keep);
+                    if (keep) {
+                        const int k = kept + lanes_below(who);
+                        tile[(k & ~63) | filter_slot(k & 63)] = v;
+                    }
+                    kept += __popcll(who);
+                }
+                wave_sync();
+                if (base + 64 * SB < n_j) load(j_off, n_j, base + 64 * SB);
+
+                for (int k0 = 0; k0 < kept; k0 += 64) {
+                    const float4 *rows64 = tile + k0;
+                    const bool valid = k0 + lane < kept;
+                    const FilterOps rows = filter_rows_of(rows64[filter_slot(lane)], valid, cx, cy, cz);
+                    const unsigned m0 = filter_mask(rows, cols.t[0]);
+                    unsigned m1 = 0;
+                    if (n_i > 32) m1 = filter_mask(rows, cols.t[1]);
+                    const float4 *mine = rows64 + (lane & 32);  // this half's rows
+                    if (__any(__popc(m0) + __popc(m1) > kDirectHits)) {
+                        // rows past the last kept one are made far away, massless
+                        if (!valid)
+                            tile[k0 + filter_slot(lane)] = make_float4(kFar, kFar, kFar, 0.f);
+                        wave_sync();
+                        const TableConsts kd = table_consts(a.c, a.smax, a.E, a.F, PHI ? 4 : 3);
+#pragma unroll 1
+                        for (int p = 0; p < 32; ++p) {
+                            if constexpr (MOM)
+                                table_pairs_mom<2>(mine[p], px, py, pz, tab, kd, tx, ty, tz, tm);
+                            else
+                                table_pairs_v<2, false, PHI>(mine[p], px, py, pz, tab, kd, tx, ty,
+                                                             tz, tp);
+                        }
+                        continue;
+                    }
+                    auto near = [&](unsigned m, auto q_c) {
+                        constexpr int q = decltype(q_c)::value;
+                        while (m) {
+                            const int p = __builtin_clz(m);
+                            m ^= 0x80000000u >> p;
+                            const float4 r = mine[p];
+                            TableGather<1, PHI> g;
+                            table_head<1, false, PHI>(r, px + q, py + q, pz + q, tab, kc, g);
+                            if constexpr (MOM) {
+                                float sm[7][1];
+#pragma unroll
+                                for (int c = 0; c < 7; ++c) sm[c][0] = tm[c][q];
+                                table_tail_mom<1>(r.w, g, tx + q, ty + q, tz + q, sm);
+#pragma unroll
+                                for (int c = 0; c < 7; ++c) tm[c][q] = sm[c][0];
+                            } else {
+                                table_tail<1, PHI>(r.w, g, tx + q, ty + q, tz + q, tp + q);
+                            }
+                        }
+                    };
+                    near(m0, std::integral_constant<int, 0>{});
+                    near(m1, std::integral_constant<int, 1>{});
+                }
+            }
+
+            // the two halves' rows; lane l then keeps slot l
+            auto slots = [&](const float *v) {
+                const float s0 = v[0] + __shfl_xor(v[0], 32), s1 = v[1] + __shfl_xor(v[1], 32);
+                return lane < 32 ? s0 : s1;
+            };
+            const float ox = slots(tx), oy = slots(ty), oz = slots(tz);
+            const float op = PHI ? slots(tp) : 0.f;
+            float om[MOM ? 7 : 1];
+#pragma unroll
+            for (int c = 0; c < (MOM ? 7 : 1); ++c) om[c] = MOM ? slots(tm[c]) : 0.f;
+            if (lane < n_i) {
+                if (tk.n_parts <= 1) {
+                    put(a.ax + i_off, lane, ox);
+                    put(a.ay + i_off, lane, oy);
+                    put(a.az + i_off, lane, oz);
+                    if (PHI) put(a.phi + i_off, lane, op);
+                    if constexpr (MOM) {
+#pragma unroll
+                        for (int c = 0; c < 7; ++c)
+                            put(a.mom + (size_t)c * a.ni_total + i_off, lane, om[c]);
+                    }
+                } else {
+                    // partial sums of one part of a split j-list (k_combine)
+                    const size_t q = (size_t)(tk.slot + tk.part) * 64 + (sub ? tk.n_i : 0) + lane;
+                    a.partial[q] = make_float4(ox, oy, oz, op);
+                    if constexpr (MOM) {
+                        a.mpartial[2 * q] = make_float4(om[0], om[1], om[2], om[3]);
+                        a.mpartial[2 * q + 1] = make_float4(om[4], om[5], om[6], 0.f);
+                    }
+                }
+            }
+        }
+        t = t_next;
+        if (t < n_t) {
+            tk = task_of_fields(fld);
+            begin(tk.i_off, tk.n_i, tk.j_off, tk.n_j);
+        }
+    }
+}
+
 using TableKernel = void (*)(BatchArgs);
 
 // A kernel of a variant for a table of 2^tb nodes, and its waves per
@@ -335,6 +593,20 @@ TableKernelPick pick(int tb, bool phi)
                 : k_batch_table<KI, TW, 14, HT, false, kWideWaves, PF>, kWideWaves};
 }
 
+// The variant that finds the pairs inside the cutoff first: two columns of
+// i-particles per lane, two rows of records per tile, four waves.
+TableKernelPick pick_near(int tb, bool phi)
+{
+    if (tb <= 10)
+        return {phi ? k_batch_table_near<10, true, 4, 2, false>
+                    : k_batch_table_near<10, false, 4, 4, false>, 4};
+    if (tb <= 12)
+        return {phi ? k_batch_table_near<12, true, kMidWaves, 2, false>
+                    : k_batch_table_near<12, false, kMidWaves, 2, false>, kMidWaves};
+    return {phi ? k_batch_table_near<13, true, kMidWaves, 2, false>
+                : k_batch_table_near<14, false, kMidWaves, 2, false>, kMidWaves};
+}
+
 struct TableBatchVariant {
     const char *name;
     int wpb;  // waves per workgroup (tables of at most 2^10 nodes)
@@ -353,7 +625,7 @@ struct TableBatchVariant {
 const TableBatchVariant kTableBatchVariants[] = {
     {"ki=1 tw=1 wg=4", 4, pick<1, 1, false, 4>},
     {"ki=2 tw=1 wg=4", 4, pick<2, 1, false, 4>},
-    {"ki=2 tw=2 wg=4", 4, pick<2, 2, false, 4>},
+    {"ki=2 tw=2 wg=4", 4, pick_near},
     {"ki=1 tw=1 wg=16", 16, pick<1, 1, false, 16>},
     {"ki=2 tw=2 wg=16", 16, pick<2, 2, false, 16>},
     {"ki=1 tw=1 wg=4 pf", 4, pick<1, 1, false, 4, true>},
@@ -388,6 +660,8 @@ const char *table_batch_variant_name(int v)
 
 int table_batch_default() { return 2; }
 
+bool table_batch_near(int v) { return v == 2; }
+
 // The pair-slot figures of set_wave_prio: a quarter of the plan's
 // interactions per wave of the launch, and its mean task.
 static void set_prio_args(BatchArgs &a)
@@ -400,18 +674,11 @@ static void set_prio_args(BatchArgs &a)
 hipError_t launch_table_batch_moments(const BatchArgs &a0, int num_cu, hipStream_t s)
 {
     if (a0.n_tasks <= 0) return hipSuccess;
-    // two-wave workgroups: their LDS holds a CU to six waves per SIMD, so
-    // the seven moment sums per i-particle fit in registers without spills
-    // (16.3 us against 18.1 us with four-wave workgroups on 8^3 cell lists
-    // of 65536 particles), and the next record read from LDS before the
-    // current pair's table gathers are waited for (16.0 against 16.3 us); a
-    // table of 2^12 nodes or more leaves room for two workgroups per CU or
-    // one, which then run 16 waves each
     const int tb = a0.E + a0.F;
-    const int wpb = tb <= 10 ? 2 : 16;
-    const TableKernel k = tb <= 10   ? k_batch_table<1, 2, 10, false, false, 2, true, true>
-                          : tb <= 12 ? k_batch_table<1, 2, 12, false, false, 16, false, true>
-                                     : k_batch_table<1, 2, 13, false, false, 16, false, true>;
+    const int wpb = tb <= 10 ? 4 : kMidWaves;
+    const TableKernel k = tb <= 10   ? k_batch_table_near<10, false, 4, 4, true>
+                          : tb <= 12 ? k_batch_table_near<12, false, kMidWaves, 2, true>
+                                     : k_batch_table_near<13, false, kMidWaves, 2, true>;
     BatchArgs a = a0;
     a.phi = nullptr;
     a.ptable = nullptr;

@@ -15,6 +15,19 @@
 
 using namespace pgh;
 
+// A task list cut for the table kernel that leaves out the pairs beyond the
+// cutoff (kNearRule), of plans whose own list is cut finer than it wants.
+struct NearList {
+    int n_tasks;  // 0: the kernel takes the plan's own list
+    int nq, q_begin[kQueues + 1];
+    int n_chunks, n_slots;
+    char *block;  // device: the counters, partial sums, tasks and chunks below
+    unsigned *queue;
+    float4 *partial;
+    Task *tasks;
+    SplitChunk *chunks;
+};
+
 struct pgh_plan {
     pgh_ctx *owner;
     // the plan of a tree's lists, owned by the tree (pgh_tree_plan hands it
@@ -54,6 +67,7 @@ struct pgh_plan {
     bool i_cover, j_cover;
     // every i-row is in exactly one i-major task of the table adjoint
     bool i_once;
+    NearList near;
     // partial moments of split chunks (pgh_batch_table_moments), grown on
     // its first call on the plan: two float4 per partial sum
     float4 *mpartial;
@@ -190,6 +204,12 @@ int check_table_shape(pgh_ctx *c, int E, int F, float rcut)
     return PGH_OK;
 }
 
+void free_near(pgh_plan *p)
+{
+    (void)hipFree(p->near.block);
+    p->near = NearList{};
+}
+
 void free_plan_memory(pgh_plan *p)
 {
     (void)hipFree(p->tasks);
@@ -207,6 +227,7 @@ void free_plan_memory(pgh_plan *p)
     (void)hipFree(p->vals);
     (void)hipFree(p->order);
     (void)hipFree(p->sort_temp);
+    free_near(p);
 }
 
 // Grows a scratch buffer of float4 records (synchronises before freeing).
@@ -313,6 +334,7 @@ void reset_plan(pgh_plan *p)
     p->n_jtasks = p->n_itasks = 0;
     p->n_tasks = 0;
     p->n_chunks = 0;
+    free_near(p);
 }
 
 // The context's pinned upload buffer, at least `bytes` long.  Every upload
@@ -373,6 +395,53 @@ int planner_waves(const pgh_ctx *c)
     return c->plan_waves > 0 ? c->plan_waves : batch_resident_waves(c->num_cu);
 }
 
+// The task list of k_batch_table_near for a plan made on the host: the same
+// items cut by kNearRule.  Synchronous.
+int near_fill(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items, int ni_total,
+              int nj_total)
+{
+    HostPlan &hp = c->hp;
+    std::string err;
+    int st = plan_tasks(items, n_items, ni_total, nj_total, near_waves(p->waves), hp, err,
+                        c->plan_pack != 0, kNearRule);
+    if (st) return fail(c, st, err);
+    const size_t n_t = (size_t)hp.n_tasks, n_c = hp.split.size();
+    if (n_t == 0) return PGH_OK;
+    // one allocation and one copy: [partial sums | counters | tasks | chunks],
+    // all but the first uploaded
+    const size_t queue_bytes = (size_t)kQueues * kQueueStride * sizeof(unsigned);
+    const size_t part_bytes = (size_t)hp.n_slots * 64 * sizeof(float4);
+    const size_t up_bytes = queue_bytes + n_t * sizeof(Task) + n_c * sizeof(SplitChunk);
+    NearList &l = p->near;
+    if (hipMalloc((void **)&l.block, part_bytes + up_bytes) != hipSuccess) {
+        l.block = nullptr;
+        return fail(c, PGH_ENOMEM, "hipMalloc(table task list) failed");
+    }
+    st = ensure_pinned(c, up_bytes);
+    if (st) return st;
+    char *pin = (char *)c->pin, *up = l.block + part_bytes;
+    std::memset(pin, 0, queue_bytes);
+    write_tasks(hp, (Task *)(pin + queue_bytes));
+    if (n_c)
+        std::memcpy(pin + queue_bytes + n_t * sizeof(Task), hp.split.data(),
+                    n_c * sizeof(SplitChunk));
+    if (hipMemcpyAsync(up, pin, up_bytes, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+        hipStreamSynchronize(c->stream) != hipSuccess) {
+        (void)hipStreamSynchronize(c->stream);  // no copy may still read the pinned buffer
+        return fail(c, PGH_EHIP, "uploading the table task list failed");
+    }
+    l.partial = (float4 *)l.block;
+    l.queue = (unsigned *)up;
+    l.tasks = (Task *)(up + queue_bytes);
+    l.chunks = (SplitChunk *)(up + queue_bytes + n_t * sizeof(Task));
+    l.nq = hp.nq;
+    std::copy(hp.q_begin, hp.q_begin + kQueues + 1, l.q_begin);
+    l.n_chunks = (int)n_c;
+    l.n_slots = hp.n_slots;
+    l.n_tasks = (int)n_t;
+    return PGH_OK;
+}
+
 // Plans the items into p on the host, reusing its device arrays when they
 // are large enough.  The tasks are written straight into the context's
 // pinned buffer and copied from there; waits for the stream.  On failure p
@@ -410,6 +479,9 @@ int plan_fill(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items, int n
     }
     set_plan_counts(p, n_items, ni_total, nj_total, (int)n_t, hp.nq, hp.q_begin, hp.interactions,
                     (int)n_c, hp.n_slots, hp.ordered);
+    // chunks of less than 64 suit the other kernels only (a tree's lists are
+    // for the Newton force)
+    if (c->hp.chunk < 64 && !p->tree_owned) return near_fill(c, p, n_items, items, ni_total, nj_total);
     return PGH_OK;
 }
 
@@ -1065,6 +1137,21 @@ BatchArgs batch_args(pgh_ctx *c, const pgh_plan *p)
     return a;
 }
 
+// Puts the plan's task list for k_batch_table_near, if it has one, into a.
+void use_near_list(BatchArgs &a, const pgh_plan *p)
+{
+    const NearList &l = p->near;
+    if (l.n_tasks == 0) return;
+    a.n_tasks = l.n_tasks;
+    a.tasks = l.tasks;
+    a.nq = l.nq;
+    std::copy(l.q_begin, l.q_begin + kQueues + 1, a.q_begin);
+    a.queue = l.queue;
+    a.partial = l.partial;
+    a.n_chunks = l.n_chunks;
+    a.chunks = l.chunks;
+}
+
 }  // namespace
 
 int pgh_batch_newton(pgh_ctx *c, const pgh_plan *p, const float *xi, const float *yi,
@@ -1117,8 +1204,11 @@ int pgh_batch_table(pgh_ctx *c, const pgh_plan *p, const float *xi, const float 
     a.F = c->tab_F;
     a.c = table_scale(smax, c->tab_rcut);
     a.smax = (float)smax;
-    const int v = c->variant[PGH_FAMILY_TABLE_BATCH];
-    PGH_HIP(c, launch_table_batch(a, v < 0 ? table_batch_default() : v, c->num_cu, c->stream));
+    a.r2max = table_r2max(a.c, smax);
+    int v = c->variant[PGH_FAMILY_TABLE_BATCH];
+    if (v < 0) v = table_batch_default();
+    if (table_batch_near(v)) use_near_list(a, p);
+    PGH_HIP(c, launch_table_batch(a, v, c->num_cu, c->stream));
     return PGH_OK;
 }
 
@@ -1138,7 +1228,7 @@ int pgh_batch_table_moments(pgh_ctx *c, pgh_plan *p, const float *xi, const floa
     if (p->nj_total > 0 && (!xj || !yj || !zj || !mj))
         return fail(c, PGH_EINVAL, "NULL j-particle array");
     DeviceGuard g(c->device);
-    const size_t n_mp = (size_t)p->n_slots * 64 * 2;
+    const size_t n_mp = (size_t)(p->near.n_tasks ? p->near.n_slots : p->n_slots) * 64 * 2;
     if (n_mp > p->mpartial_cap) {
         // a smaller array may still be read by launches in flight
         PGH_HIP(c, hipStreamSynchronize(c->stream));
@@ -1155,6 +1245,8 @@ int pgh_batch_table_moments(pgh_ctx *c, pgh_plan *p, const float *xi, const floa
     a.F = c->tab_F;
     a.c = table_scale(smax, c->tab_rcut);
     a.smax = (float)smax;
+    a.r2max = table_r2max(a.c, smax);
+    use_near_list(a, p);
     a.mom = mom;
     a.mpartial = p->mpartial;
     a.ni_total = p->ni_total;

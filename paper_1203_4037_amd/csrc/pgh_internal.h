@@ -76,6 +76,7 @@ struct BatchArgs {
     const float2 *table;
     int E, F;
     float c, smax;
+    float r2max;  // the least |d|^2 whose s reaches s_max
     const float2 *ptable;  // potential table (with phi), or NULL
     // Newton only: NULL, or the j-records packed (x, y, z, m) in place of
     // xj .. mj
@@ -174,6 +175,7 @@ const char *newton_batch_variant_name(int v);
 int table_batch_variants();
 const char *table_batch_variant_name(int v);
 int table_batch_default();  // the variant used when none is chosen
+bool table_batch_near(int v);  // whether variant v leaves out the pairs beyond the cutoff
 // k_combine over the split chunks of a batched launch (after it, same stream)
 hipError_t launch_combine(const BatchArgs &a, bool phi, hipStream_t s);
 // Device expansion of a compact plan (plan_expand.hip): the tasks of the

@@ -218,15 +218,15 @@ int deal_layout(size_t n, int *q_begin)
 // with short ones.  (Equal tasks of half a wave's work leave the last round
 // of the queue mostly idle whenever the task count is just above a multiple
 // of the wave count.)
-long long part_length(long long wave_iters, int waves)
+long long part_length(long long wave_iters, int waves, int div = 8)
 {
-    return std::max(512LL, (wave_iters / waves / 8 + 63) / 64 * 64);
+    return std::max(512LL, (wave_iters / waves / div + 63) / 64 * 64);
 }
 
 }  // namespace
 
 int plan_tasks(const pgh_item *items, int n_items, int ni_total, int nj_total, int waves,
-               HostPlan &out, std::string &err, bool pack)
+               HostPlan &out, std::string &err, bool pack, const PlanRule &rule)
 {
     Scratch &S = scratch();
     std::vector<int> &order = S.order;
@@ -247,9 +247,10 @@ int plan_tasks(const pgh_item *items, int n_items, int ni_total, int nj_total, i
     for (;;) {
         long long n = 0;
         for (int t : order) n += (items[t].n_i + csize - 1) / csize;
-        if (n >= waves || csize == 16) break;
+        if (n >= waves || csize <= rule.min_chunk) break;
         csize /= 2;
     }
+    out.chunk = csize;
     std::vector<PlanChunk> &chunks = out.chunks;
     chunks.clear();
     long long total = 0;  // wave-iterations
@@ -290,7 +291,7 @@ int plan_tasks(const pgh_item *items, int n_items, int ni_total, int nj_total, i
             if (pack && n < 64 && it.n_j > 0) open = (int)chunks.size() - 1;
         }
     }
-    const long long part_iters = part_length(total, waves);
+    const long long part_iters = part_length(total, waves, rule.part_div);
     // add_work records a wave's work (chunk a, and chunk b sharing the wave,
     // or b < 0), its cut and its tasks with their costs
     std::vector<PlanWork> &work = out.work;
@@ -324,6 +325,8 @@ int plan_tasks(const pgh_item *items, int n_items, int ni_total, int nj_total, i
     {
         if (pack) {
             S.pairs = packed;
+        } else if (!rule.pair) {
+            S.pairs.clear();
         } else {
             std::vector<int> &cand = S.cand;
             cand.clear();

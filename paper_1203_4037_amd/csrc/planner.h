@@ -32,6 +32,7 @@ struct PlanRef {
 // n_tasks task records (so the caller can put them straight into memory of
 // its choice, such as a pinned upload buffer).
 struct HostPlan {
+    int chunk = 64;                 // i-particles per chunk at most (64, 32 or 16)
     int n_tasks = 0;
     int nq = 0;                     // sublists in use
     int q_begin[kQueues + 1] = {0}; // sublist q is tasks [q_begin[q], q_begin[q + 1])
@@ -45,12 +46,27 @@ struct HostPlan {
     std::vector<PlanRef> dealt;     // the tasks in their final order
 };
 
+// How a plan's work is cut into tasks.  The defaults suit kernels whose time is
+// their pairs: chunks down to 16 i-particles (four lanes each) until every
+// resident wave has one, partly filled chunks paired, and parts of an eighth
+// of a wave's share.  The table kernel that leaves out the pairs beyond the
+// cutoff (k_batch_table_near) spends most of its time per list entry and
+// column of 32 i-particles, whatever the pairs: it wants whole chunks, no
+// part shorter than a wave's share, and a quarter of the waves.
+struct PlanRule {
+    int min_chunk = 16;  // 16, 32 or 64
+    int part_div = 8;    // parts of 1 / part_div of a wave's share of the work
+    bool pair = true;    // pair partly filled chunks (without packing)
+};
+constexpr PlanRule kNearRule{32, 1, false};
+inline int near_waves(int waves) { return waves / 4 > 1 ? waves / 4 : 1; }
+
 // Validates the items (non-negative fields, inside the arrays, disjoint
 // i-ranges) and cuts them into wave tasks for a device that holds `waves`
 // resident waves of the batched kernel.  Returns PGH_OK, or a status with a
 // message in err.
 int plan_tasks(const pgh_item *items, int n_items, int ni_total, int nj_total, int waves,
-               HostPlan &out, std::string &err, bool pack = false);
+               HostPlan &out, std::string &err, bool pack = false, const PlanRule &rule = {});
 
 // Writes the plan's hp.n_tasks tasks to dst, sublist after sublist, each
 // sublist longest first.

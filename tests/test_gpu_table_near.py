@@ -1,0 +1,181 @@
+"""The batched table force that leaves out the pairs beyond the cutoff
+(k_batch_table_near, the built-in default) and its all-pairs counterpart
+(k_table_rows): no pair inside the cutoff is missed, whatever the
+coordinates' offset and the list's shape, and inputs for which a pair beyond
+the cutoff does not add zero take the whole path."""
+import numpy as np
+import pytest
+
+import oracle
+from _helpers import norm_vec_err, rms, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+E, F = 4, 6
+K = 1 << (E + F)
+SMAX = np.float32(2.0 ** (1 << E) * (2 - 2.0 ** -F))
+
+
+@pytest.fixture(scope="module")
+def pgh():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1203_4037_amd as p
+    return p
+
+
+@pytest.fixture()
+def ctx(pgh):
+    c = pgh.Context(0)
+    yield c
+    c.close()
+
+
+def _scale(rcut):
+    """The float32 c of s = c |d|^2 + 2: the smallest at which rcut reaches s_max."""
+    r2 = np.float32(rcut) * np.float32(rcut)
+    c = np.float32((float(SMAX) - 2) / float(np.float32(rcut)) ** 2)
+    while np.float32(float(r2) * float(c) + 2.0) < SMAX:
+        c = np.nextafter(c, np.float32(np.inf))
+    return float(c)
+
+
+def _counts(items, pi, pj, rcut):
+    """For each i-row the list entries whose float32 s is below s_max."""
+    c = _scale(rcut)
+    out = np.zeros(pi.shape[1])
+    for i0, ni, j0, nj in items:
+        d = pj[:, None, j0:j0 + nj] - pi[:, i0:i0 + ni, None]
+        q = (d[0] * d[0]).astype(np.float64)
+        for k in (1, 2):  # fused multiply-adds: exact products, one rounding
+            q = (d[k].astype(np.float64) ** 2 + q).astype(np.float32).astype(np.float64)
+        out[i0:i0 + ni] = ((q * c + 2).astype(np.float32) < SMAX).sum(1)
+    return out
+
+
+def _lists(rng, centre, spread, clustered):
+    """Groups of 1 to 200 and lists of 0 to 1300 entries around the groups,
+    with gaps between the groups' rows."""
+    sizes_i = [1, 2, 31, 32, 33, 63, 64, 65, 96, 200]
+    sizes_j = [0, 1, 31, 63, 64, 65, 127, 255, 256, 257, 512, 1300]
+    items, xi, xj, i0, j0 = [], [], [], 0, 0
+    for a in sizes_i:
+        for b in sizes_j:
+            g = centre + spread * rng.random(3)
+            w = 0.02 if clustered else 0.1
+            xi.append(g[:, None] + w * (rng.random((3, a + 2)) - 0.5))
+            xj.append(g[:, None] + 2 * w * (rng.random((3, b)) - 0.5))
+            items.append((i0, a, j0, b))
+            i0 += a + 2
+            j0 += b
+    return (np.array(items, np.int32), np.concatenate(xi, 1).astype(np.float32),
+            np.concatenate(xj, 1).astype(np.float32))
+
+
+def _count_table(pgh, ctx, rcut):
+    """Force table of the S2 shape and a potential table that counts pairs:
+    1 on every node but the last."""
+    ctx.build_table(E, F, rcut, eps=rcut / 15)
+    t = np.zeros(2 * K, np.float32)
+    t[0:-2:2] = 1.0
+    ctx._sync_stream()
+    pgh.pgh_set_pot_table(ctx.h, to_dev(t)[0])
+
+
+@pytest.mark.parametrize("waves", [0, 64, 4096])
+@pytest.mark.parametrize("offset,rcut,clustered", [(0.0, 0.02, False), (0.0, 0.02, True),
+                                                   (37.0, 0.02, False), (-4000.0, 0.05, False),
+                                                   (0.5, 1e-4, True), (0.0, 0.08, False)])
+def test_every_pair_inside_the_cutoff_is_found(pgh, ctx, offset, rcut, clustered, waves):
+    """The neighbour counts, exact integers, of lists at the edges of the
+    kernel's blocks, on plans cut for few and for many waves."""
+    items, pi, pj = _lists(np.random.default_rng(3), np.full(3, offset), 0.3, clustered)
+    _count_table(pgh, ctx, rcut)
+    ctx.set_plan_waves(waves)
+    plan = ctx.plan(items, pi.shape[1], pj.shape[1])
+    one = np.ones(pj.shape[1], np.float32)
+    phi = to_host(*plan.table(*to_dev(*pi), *to_dev(*pj), to_dev(one)[0], with_phi=True))[3]
+    want = _counts(items, pi, pj, rcut)
+    rows = np.concatenate([np.arange(i, i + n) for i, n, _, _ in items])
+    assert want.max() >= 1
+    assert np.array_equal(phi[rows], want[rows])
+
+
+@pytest.mark.parametrize("n", [700, 5000])
+@pytest.mark.parametrize("offset,rcut", [(0.0, 0.03), (12.0, 0.03), (0.0, 0.4)])
+def test_all_pairs_counts(pgh, ctx, n, offset, rcut):
+    rng = np.random.default_rng(n)
+    p = (offset + 0.5 * rng.random((3, n))).astype(np.float32)
+    _count_table(pgh, ctx, rcut)
+    d = to_dev(*p)
+    ctx.set_j(*d, to_dev(np.ones(n, np.float32))[0])
+    phi = to_host(*ctx.table_force(*d, with_phi=True))[3]
+    assert np.array_equal(phi, _counts([(0, n, 0, n)], p, p, rcut))
+
+
+@pytest.mark.parametrize("what", ["last node", "nan i", "nan j", "inf j", "huge i", "inf mass",
+                                  "nan mass", "none"])
+@pytest.mark.parametrize("batched", [True, False])
+def test_whole_path_where_zero_is_not_certain(pgh, ctx, what, batched):
+    """Against the general kernels (variant 0): the same rows are NaN or
+    infinite, the others agree to the rounding of sums of up to 1000 terms
+    of at most m max|g d| each."""
+    rng = np.random.default_rng(5)
+    items = np.array([(0, 70, 0, 300), (70, 30, 300, 1000), (100, 64, 1300, 65)], np.int32)
+    pi = rng.random((3, 164)).astype(np.float32)
+    pj = rng.random((3, 1365)).astype(np.float32)
+    m = np.full(1365, 1.0, np.float32)
+    rcut = 0.2
+    table = ctx.build_table(E, F, rcut, eps=rcut / 15)
+    if what == "last node":
+        table[-2] = 0.5
+        ctx.set_table(E, F, rcut, to_dev(table)[0])
+    elif what == "nan i":
+        pi[1, [3, 120]] = np.nan
+    elif what == "nan j":
+        pj[2, [5, 700]] = np.nan
+    elif what == "inf j":
+        pj[0, 310] = np.inf
+    elif what == "huge i":
+        pi[0, 99] = 1e30
+    elif what == "inf mass":
+        m[[10, 1299]] = np.inf
+    elif what == "nan mass":
+        m[1364] = np.nan
+    di, dj = to_dev(*pi), to_dev(*pj, m)
+    fam = pgh.PGH_FAMILY_TABLE_BATCH if batched else pgh.PGH_FAMILY_TABLE_ALLPAIRS
+    plan = ctx.plan(items, 164, 1365)
+    got = []
+    for v in (0, -1):
+        ctx.set_variant(fam, v)
+        if batched:
+            got.append(np.stack(to_host(*plan.table(*di, *dj))))
+        else:
+            ctx.set_j(*dj)
+            got.append(np.stack(to_host(*ctx.table_force(*di))))
+    a, b = got
+    assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
+    if what in ("nan i", "nan j", "inf j", "inf mass", "nan mass"):
+        assert np.isnan(a).any()
+    s = np.array([2.0 ** (1 + (k >> F)) * (1 + (k & 63) / 64) for k in range(K)])
+    r = rcut * np.sqrt((s - 2) / (float(SMAX) - 2))
+    term = max(np.abs(table[0::2] * r).max(), 0.5 * np.sqrt(3))
+    fine = np.isfinite(a)
+    if what != "huge i" and fine.any():
+        assert np.abs(a[fine] - b[fine]).max() <= 1000 * 1000 * 2.0 ** -24 * term
+
+
+def test_default_against_the_oracle_with_many_pairs_inside(pgh, ctx):
+    """Lists most of whose pairs are inside the cutoff: the blocks are
+    evaluated whole."""
+    items, pi, pj = _lists(np.random.default_rng(9), np.zeros(3), 0.3, True)
+    rcut = 0.05
+    table = ctx.build_table(E, F, rcut, eps=rcut / 15)
+    m = np.random.default_rng(2).uniform(0.5, 1.5, pj.shape[1]).astype(np.float32)
+    plan = ctx.plan(items, pi.shape[1], pj.shape[1])
+    a = np.stack(to_host(*plan.table(*to_dev(*pi), *to_dev(*pj, m))))
+    ref = oracle.lut_items(items, *pi, *pj, m, E, F, float(np.float32(rcut)), table)
+    has = np.nan_to_num(ref[3]) > 0
+    e = norm_vec_err(a[:, has], np.stack(ref[:3])[:, has], ref[3][has])
+    assert rms(e) <= 1e-5 and e.max() <= 1e-3, (rms(e), e.max())
