@@ -22,6 +22,7 @@
 #include "table_pairs.h"
 #include "pgh_internal.h"
 #include "rows.h"
+#include "table_filter.h"
 
 namespace pgh {
 namespace {
@@ -37,6 +38,7 @@ __global__ void __launch_bounds__(NT) k_table_allpairs(TableArgs a)
     float2 *stab = (float2 *)dyn4;  // (G0, G1) per node
     float4 *stab4 = dyn4;           // (G0, G1, P0, P1) per node, with PHI
     __shared__ float4 tile[2][JT];
+    if (a.dense && *a.dense == 0) return;  // k_table_near computes this call
 
     const int tid = threadIdx.x;
     const int ibase = blockIdx.x * (NT * KI) + tid;
@@ -161,6 +163,29 @@ __global__ void __launch_bounds__(NT) k_table_allpairs(TableArgs a)
 // the cutoff, and by the launch for small sets: N = 4096 in a box of 21 cutoffs
 // 28.8 -> 12.7 us a call with 2^10 nodes, in 5 cutoffs 29.3 -> 13.4, in 1.7
 // cutoffs 28.9 -> 14.2.
+// A step whose tests all found pairs of most of their i-particles inside is
+// followed by this many evaluated whole without a test.
+constexpr int kWholeSteps = 7;
+
+// One j-record of the lane against Q uniform i-particles; s[k]: their sums.
+template <int Q, bool PHI>
+__device__ __forceinline__ void whole_pairs(const float4 p, const float *px, const float *py,
+                                            const float *pz, const char *tab, const TableConsts &kc,
+                                            float (*s)[PHI ? 4 : 3])
+{
+    TableGather<Q, PHI> q;
+    table_head<Q, false, PHI>(p, px, py, pz, tab, kc, q);
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+        const float mg = p.w * __builtin_fmaf(q.t[k].y, q.ds[k], q.t[k].x);
+        s[k][0] = __builtin_fmaf(mg, q.dx[k], s[k][0]);
+        s[k][1] = __builtin_fmaf(mg, q.dy[k], s[k][1]);
+        s[k][2] = __builtin_fmaf(mg, q.dz[k], s[k][2]);
+        if constexpr (PHI)
+            s[k][3] = __builtin_fmaf(p.w, __builtin_fmaf(q.t[k].w, q.ds[k], q.t[k].z), s[k][3]);
+    }
+}
+
 template <int TI, int NT, bool PHI>
 __global__ void __launch_bounds__(NT) k_table_rows(TableArgs a)
 {
@@ -213,8 +238,17 @@ __global__ void __launch_bounds__(NT) k_table_rows(TableArgs a)
             for (int c = 0; c < C; ++c) s[k][c] = 0.f;
         }
         whole = __builtin_amdgcn_readfirstlane(whole);
+        int blind = 0;  // steps still to be evaluated whole without a test
         auto pairs = [&](const float4 p) {
+            if (blind > 0) {
+                --blind;
+#pragma unroll
+                for (int k0 = 0; k0 < TI; k0 += Q)
+                    whole_pairs<Q, PHI>(p, px + k0, py + k0, pz + k0, tab, kc, s + k0);
+                return;
+            }
             const bool all = whole || __any(!ordinary(p.x, p.y, p.z, p.w));
+            int most = 0;  // tests that found pairs of most of their i-particles
 #pragma unroll
             for (int k0 = 0; k0 < TI; k0 += Q) {
                 float dx[Q], dy[Q], dz[Q], r2[Q];
@@ -262,6 +296,7 @@ __global__ void __launch_bounds__(NT) k_table_rows(TableArgs a)
 #pragma unroll
                 for (int k = 0; k < Q; ++k) hits += __any(__float_as_uint(r2[k]) < r2max) ? 1 : 0;
                 if (all || Q == 1 || 2 * hits > Q) {
+                    ++most;
                     tail(integral_constant<int, 0>{}, integral_constant<int, Q>{});
                     continue;
                 }
@@ -277,6 +312,7 @@ __global__ void __launch_bounds__(NT) k_table_rows(TableArgs a)
                         tail(integral_constant<int, 3>{}, integral_constant<int, 1>{});
                 }
             }
+            if (most == TI / Q) blind = kWholeSteps;
         };
 
         int t = 0;
@@ -324,6 +360,218 @@ __global__ void __launch_bounds__(NT) k_table_rows(TableArgs a)
     }
 }
 
+// Whether most pairs are to be evaluated: more than a quarter of 8 spread
+// i-particles' pairs with 4096 spread j-particles inside the cutoff, or a last
+// node that is not zero.  It chooses the kernel, never what is computed.
+template <bool PHI>
+__global__ void __launch_bounds__(1024) k_table_density(TableArgs a, int *dense)
+{
+    __shared__ int count;
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    int n = 0;
+    float4 p[4], q[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        p[k] = a.jmem[(long long)(4 * threadIdx.x + k) * a.nj / 4096];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int i = (int)((2 * k + 1) * (long long)a.ni / 16);
+        q[k] = make_float4(a.xi[i], a.yi[i], a.zi[i], 0.f);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        for (int l = 0; l < 4; ++l) {
+            const float dx = p[l].x - q[k].x, dy = p[l].y - q[k].y, dz = p[l].z - q[k].z;
+            n += dx * dx + dy * dy + dz * dz < a.r2max ? 1 : 0;
+        }
+    for (int m = 32; m; m >>= 1) n += __shfl_xor(n, m);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&count, n);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int K = 1 << (a.E + a.F);
+        const float2 e = a.table[K - 1];
+        bool zero = e.x == 0.f && e.y == 0.f;
+        if (PHI) zero = zero && a.ptable[K - 1].x == 0.f && a.ptable[K - 1].y == 0.f;
+        *dense = count > 8 * 4096 / 4 || !zero ? 1 : 0;
+    }
+}
+
+// The all-pairs table force with the pairs beyond the cutoff found on the
+// matrix cores (table_filter.h) and left out, for sets that are not small: the
+// workgroup's W waves hold the same chunk of NC columns of 32 i-particles (lane
+// l holds l mod 32 of each) and take a share of the j-particles each, 64
+// records at a time, two steps ahead; records farther than the cutoff from the
+// box around the chunk are dropped (which helps sets in cell or curve order),
+// the others go to the wave's LDS tile and, as bf16 terms, into the products,
+// 2 NC of them.  Each lane then evaluates its own candidates in FP32.  A step
+// most of whose pairs are inside is evaluated whole, and the next kWholeSteps
+// after it without a test.  The waves' sums meet in LDS at the end.
+//
+// Per 64 records and column 32 sign instructions, two products and the
+// candidates, and some 70 for the 64 records, against 64 x 17 / 2 per column
+// before: bound by the issue of these.  N = 65536 (T16, phi off) in a
+// box of 21 cutoffs 1121 -> 280 us, of 5 cutoffs 1138 -> 478, with most pairs
+// inside 1216 -> 1390 (auto_kernel leaves that to k_table_allpairs); N = 16384
+// 81 -> 28 us.
+template <int NC, int W, bool PHI>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_table_near(TableArgs a)
+{
+    constexpr int NI = 32 * NC;  // i-particles per chunk
+    constexpr int C = PHI ? 4 : 3;
+    extern __shared__ float4 dyn4[];
+    if (a.dense && *a.dense != 0) return;  // k_table_allpairs computes this call
+    const int K = 1 << (a.E + a.F);
+    // after the table, NI float4 per wave: its tile of 64 records, then its sums
+    float4 *const sums = dyn4 + (PHI ? K : K / 2);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float4 *const tile = sums + wave * NI;
+
+    // the wave's share of the j-particles, a multiple of 64 records
+    const int per = ((a.nj + 64 * W - 1) / (64 * W)) * 64;
+    const int jbase = min(wave * per, a.nj);
+    const int nj = min(per, a.nj - jbase);
+    const float4 *__restrict__ jm = a.jmem + jbase;
+    auto load = [&](int base) { return jm[max(0, min(base + lane, nj - 1))]; };
+
+    if (PHI)
+        tables_to_lds<false>(dyn4, a.table, a.ptable, K, 0u);
+    else
+        table_to_lds<false>((float2 *)dyn4, a.table, K, 0u);
+    const char *tab = (const char *)dyn4;
+    const unsigned kshift = 23u - (unsigned)a.F;
+    const TableConsts kc{a.c, __float_as_uint(a.smax), kshift - (PHI ? 4 : 3),
+                         (unsigned)(K - 1) << (PHI ? 4 : 3), ~((1u << kshift) - 1u)};
+    __syncthreads();
+    bool last_zero = a.r2max > 1.0e-30f;
+    if (PHI) {
+        const float4 e = dyn4[K - 1];
+        last_zero = last_zero && e.x == 0.f && e.y == 0.f && e.z == 0.f && e.w == 0.f;
+    } else {
+        const float2 e = ((const float2 *)dyn4)[K - 1];
+        last_zero = last_zero && e.x == 0.f && e.y == 0.f;
+    }
+
+    const int groups = (a.ni + NI - 1) / NI;
+    for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+        const int i0 = g * NI, n_i = min(NI, a.ni - i0);
+        float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f), p1 = p0;
+        if (nj > 0) p0 = load(0), p1 = load(64);
+        // the chunk, 64 i-particles at a time (past its end its first)
+        float ix[NC / 2], iy[NC / 2], iz[NC / 2];
+        bool odd = false;
+        float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+        for (int q = 0; q < NC / 2; ++q) {
+            const int k = 64 * q + lane, i = i0 + (k < n_i ? k : 0);
+            ix[q] = a.xi[i];
+            iy[q] = a.yi[i];
+            iz[q] = a.zi[i];
+            odd = odd || !ordinary(ix[q], iy[q], iz[q], 0.f);
+            lo[0] = __builtin_fminf(lo[0], ix[q]), hi[0] = __builtin_fmaxf(hi[0], ix[q]);
+            lo[1] = __builtin_fminf(lo[1], iy[q]), hi[1] = __builtin_fmaxf(hi[1], iy[q]);
+            lo[2] = __builtin_fminf(lo[2], iz[q]), hi[2] = __builtin_fmaxf(hi[2], iz[q]);
+        }
+        const bool whole = !last_zero || __any(odd);
+        float bl[3], bh[3], ce[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            bl[c] = uniform(whole ? -INFINITY : wave_min(lo[c]));
+            bh[c] = uniform(whole ? INFINITY : wave_max(hi[c]));
+            ce[c] = uniform(whole ? 0.f : 0.5f * (bl[c] + bh[c]));
+        }
+        u32x4 cols[NC];
+        float px[NC], py[NC], pz[NC];
+        float tx[NC], ty[NC], tz[NC], tp[NC];
+#pragma unroll
+        for (int q = 0; q < NC / 2; ++q) {
+            const FilterOps o = filter_cols_of(ix[q], iy[q], iz[q], 64 * q + lane < n_i, last_zero,
+                                               ce[0], ce[1], ce[2], a.r2max);
+            cols[2 * q] = o.t[0];
+            cols[2 * q + 1] = o.t[1];
+            both_halves(ix[q], px + 2 * q);
+            both_halves(iy[q], py + 2 * q);
+            both_halves(iz[q], pz + 2 * q);
+        }
+#pragma unroll
+        for (int q = 0; q < NC; ++q) tx[q] = ty[q] = tz[q] = tp[q] = 0.f;
+
+        int blind = 0;  // steps still to be evaluated whole without a test
+        for (int base = 0; base < nj; base += 64) {
+            const float4 v = p0;
+            p0 = p1;
+            p1 = load(base + 128);
+            const float ex = __builtin_fmaxf(__builtin_fmaxf(bl[0] - v.x, v.x - bh[0]), 0.f);
+            const float ey = __builtin_fmaxf(__builtin_fmaxf(bl[1] - v.y, v.y - bh[1]), 0.f);
+            const float ez = __builtin_fmaxf(__builtin_fmaxf(bl[2] - v.z, v.z - bh[2]), 0.f);
+            const float r2 = __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));
+            const bool valid = base + lane < nj;
+            // (each step is monotone: no pair with the chunk has a smaller |d|^2)
+            const bool keep = valid && (r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
+            if (!__any(keep)) continue;
+            wave_sync_tile();  // the previous step's reads are done
+            tile[filter_slot(lane)] = keep ? v : make_float4(1.0e10f, 1.0e10f, 1.0e10f, 0.f);
+            wave_sync_tile();
+            const float4 *mine = tile + (lane & 32);
+            bool direct = blind > 0;
+            unsigned m[NC];
+            if (!direct) {
+                const FilterOps rows = filter_rows_of(v, keep, ce[0], ce[1], ce[2]);
+                int hits = 0;
+#pragma unroll
+                for (int q = 0; q < NC; ++q) {
+                    m[q] = filter_mask(rows, cols[q]);
+                    hits += __popc(m[q]);
+                }
+                direct = __any(hits > 12 * NC);
+                if (direct) blind = kWholeSteps + 1;
+            }
+            if (direct) {
+                --blind;
+                const TableConsts kd = table_consts(a.c, a.smax, a.E, a.F, PHI ? 4 : 3);
+#pragma unroll 2
+                for (int p = 0; p < 32; ++p)
+                    table_pairs_v<NC, false, PHI>(mine[p], px, py, pz, tab, kd, tx, ty, tz, tp);
+                continue;
+            }
+            auto near = [&](unsigned w, auto q_c) {
+                constexpr int q = decltype(q_c)::value;
+                while (w) {
+                    const int p = __builtin_clz(w);
+                    w ^= 0x80000000u >> p;
+                    table_pairs_v<1, false, PHI>(mine[p], px + q, py + q, pz + q, tab, kc, tx + q,
+                                                 ty + q, tz + q, tp + q);
+                }
+            };
+            near(m[0], std::integral_constant<int, 0>{});
+            near(m[1], std::integral_constant<int, 1>{});
+            if constexpr (NC > 2) {
+                near(m[2], std::integral_constant<int, 2>{});
+                near(m[3], std::integral_constant<int, 3>{});
+            }
+        }
+
+        // both halves' rows, then the waves' shares in order
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+            const float sx = tx[q] + __shfl_xor(tx[q], 32), sy = ty[q] + __shfl_xor(ty[q], 32);
+            const float sz = tz[q] + __shfl_xor(tz[q], 32);
+            const float sp = PHI ? tp[q] + __shfl_xor(tp[q], 32) : 0.f;
+            if (lane < 32) tile[32 * q + lane] = make_float4(sx, sy, sz, sp);
+        }
+        __syncthreads();
+        for (int k = tid; k < C * n_i; k += 64 * W) {
+            const int c = k / n_i, i = k - c * n_i;
+            float r = 0.f;
+            for (int w = 0; w < W; ++w) r += ((const float *)(sums + w * NI + i))[c];
+            (c == 0 ? a.ax : c == 1 ? a.ay : c == 2 ? a.az : a.phi)[i0 + i] = r;
+        }
+        if (g + (int)gridDim.x < groups) __syncthreads();
+    }
+}
+
 using TableKernel = void (*)(TableArgs);
 
 // Tables of more than 32 KiB in LDS (2^13 nodes and more, or 2^12 with the
@@ -365,9 +613,10 @@ const TableVariant kTableVariants[] = {
     PGH_TABLE_VARIANT("ki=1 jt=256 u=4 htab", 1, 256, 4, true),
     PGH_TABLE_VARIANT("ki=2 jt=256 u=4 htab", 2, 256, 4, true),
     {"rows", 0, 64, nullptr, nullptr, nullptr, nullptr},
+    {"near", 0, 64, nullptr, nullptr, nullptr, nullptr},
 };
 #undef PGH_TABLE_VARIANT
-constexpr int kRowsVariant = 5;
+constexpr int kRowsVariant = 5, kNearVariant = 6;
 constexpr int kNumTableVariants = sizeof(kTableVariants) / sizeof(kTableVariants[0]);
 
 bool is_phi(const TableArgs &a) { return a.phi && a.ptable; }
@@ -375,6 +624,44 @@ bool is_phi(const TableArgs &a) { return a.phi && a.ptable; }
 size_t table_lds_bytes(const TableArgs &a)
 {
     return (is_phi(a) ? sizeof(float4) : sizeof(float2)) << (a.E + a.F);
+}
+
+// The built-in choice, made per launch (kAutoVariant, not a selectable
+// variant).  Times: T16, k_table_allpairs against the kernel taken, first in a
+// box of 21 cutoffs, then with every pair inside:
+//   * the rows kernel up to 10^8 pairs, where k_table_allpairs' workgroup per 256
+//     i-particles leaves CUs idle (N = 5500: 42 -> 15 us, 42 -> 18; 8192: 29.6 ->
+//     24.9, 30.0 -> 29.0; 5000 x 20000 54 -> 34, 55 -> 44), and for few
+//     i-particles;
+//   * k_table_near above, for at least 8192 x 4096 (N = 16384 81 -> 28, 83 -> 89);
+//     from 4 x 10^8 pairs on, where every pair inside would cost it more than
+//     the 9 us of k_table_density and a launch that returns at once,
+//     k_table_density picks k_table_near or k_table_allpairs on the device
+//     (N = 32768 277 -> 86, 302 -> 308; 65536 1097 -> 292, 1196 -> 1203);
+//   * k_table_allpairs otherwise (3000 x 60000: 67 us, both others 63 and 78).
+constexpr int kAutoVariant = kNumTableVariants;
+
+enum class AutoKernel { rows, near, allpairs };
+
+AutoKernel auto_kernel(int ni, int nj)
+{
+    if (nj < 256 && ni >= 16384) return AutoKernel::allpairs;
+    if ((double)ni * nj <= 1.0e8 || ni < 1024) return AutoKernel::rows;
+    return ni >= 8192 && nj >= 4096 ? AutoKernel::near : AutoKernel::allpairs;
+}
+
+bool auto_decides(int ni, int nj) { return (double)ni * nj >= 4.0e8; }
+
+// k_table_allpairs' variant: two i-particles per lane once these fill the CUs
+int allpairs_variant(int ni, int num_cu)
+{
+    return ((long)ni + 127) / 128 >= 4L * num_cu ? 1 : 0;
+}
+
+int rows_split(const TableArgs &a, size_t part_cap)
+{
+    return (int)std::max(1L, std::min((long)rows_shape(a.ni, a.nj).shares,
+                                      (long)(part_cap / (4 * (size_t)std::max(a.ni, 1)))));
 }
 
 }  // namespace
@@ -386,22 +673,19 @@ const char *table_allpairs_variant_name(int v)
     return (v >= 0 && v < kNumTableVariants) ? kTableVariants[v].name : nullptr;
 }
 
-int table_allpairs_default(int ni, int nj, int num_cu)
-{
-    // The rows kernel for small sets, whose time is launches and idle CUs with
-    // a workgroup per 256 i-particles (N = 1000: 12.5 against 58 us, most of it
-    // the host's; 4096 13 to 14 against 29 whatever the pairs inside).
-    if ((double)ni * nj <= 3.0e7) return kRowsVariant;
-    const long waves_ki2 = (long)(ni + 127) / 128;
-    return waves_ki2 >= 4L * num_cu ? 1 : 0;
-}
+int table_allpairs_default() { return kAutoVariant; }
 
-int table_allpairs_split(const TableArgs &a, int variant, size_t part_cap)
+int table_allpairs_split(const TableArgs &a, int variant, int num_cu, size_t part_cap)
 {
+    if (variant == kAutoVariant) {
+        const AutoKernel k = auto_kernel(a.ni, a.nj);
+        if (k == AutoKernel::rows) return rows_split(a, part_cap);
+        if (k == AutoKernel::near && !auto_decides(a.ni, a.nj)) return 1;
+        variant = allpairs_variant(a.ni, num_cu);
+    }
+    if (variant == kNearVariant) return 1;
+    if (variant == kRowsVariant) return rows_split(a, part_cap);
     const TableVariant &v = kTableVariants[variant];
-    if (v.ki == 0)
-        return (int)std::max(1L, std::min((long)rows_shape(a.ni, a.nj).shares,
-                                          (long)(part_cap / (4 * (size_t)std::max(a.ni, 1)))));
     if (table_lds_bytes(a) > kWideTableBytes)
         return split_count(a.ni, a.nj, v.ki, kWideNT, kWideTargetWaves, part_cap);
     return split_count(a.ni, a.nj, v.ki, v.jt, kSplitTargetWaves, part_cap);
@@ -442,20 +726,65 @@ hipError_t launch_table_rows(TableArgs a, int S, int num_cu, hipStream_t s)
     return launch_combine_split(a.ni, S, a.part, a.ax, a.ay, a.az, phi ? a.phi : nullptr, s);
 }
 
+template <int W>
+TableKernel near_kernel(int nc, bool phi)
+{
+    if (nc == 4) return phi ? k_table_near<4, W, true> : k_table_near<4, W, false>;
+    return phi ? k_table_near<2, W, true> : k_table_near<2, W, false>;
+}
+
+hipError_t launch_table_near(const TableArgs &a, int num_cu, hipStream_t s)
+{
+    const bool phi = is_phi(a);
+    // four columns share a record's terms; two give small sets more waves
+    const size_t table = table_lds_bytes(a);
+    const int nc = a.ni >= 32768 ? 4 : 2;
+    // eight waves and two workgroups to a CU, or sixteen where a large table
+    // (or few chunks) leaves room for one
+    const int groups = (a.ni + 32 * nc - 1) / (32 * nc);
+    const int w = table > 32768 || groups <= num_cu ? 16 : 8;
+    const size_t lds = table + (size_t)w * 32 * nc * sizeof(float4);
+    const TableKernel kern = w == 16 ? near_kernel<16>(nc, phi) : near_kernel<8>(nc, phi);
+    hipError_t e = allow_dynamic_lds((const void *)kern, lds);
+    if (e != hipSuccess) return e;
+    // a large table is copied once per CU
+    const int blocks = table > 16384 ? std::min(groups, num_cu * (w == 16 ? 1 : 2)) : groups;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * w), lds, s, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_table_allpairs(const TableArgs &a0, int variant, int S, int num_cu,
                                  hipStream_t s)
 {
     if (a0.ni <= 0) return hipSuccess;
-    const TableVariant &v = kTableVariants[variant];
     TableArgs a = a0;
     const bool phi = is_phi(a);
+    S = std::max(1, S);
+    int *const dense = a.dense;
+    a.dense = nullptr;
+    if (variant == kAutoVariant) {
+        const AutoKernel k = auto_kernel(a.ni, a.nj);
+        variant = k == AutoKernel::rows   ? kRowsVariant
+                  : k == AutoKernel::near ? kNearVariant
+                                          : allpairs_variant(a.ni, num_cu);
+        if (k == AutoKernel::near && auto_decides(a.ni, a.nj)) {
+            a.dense = dense;
+            hipLaunchKernelGGL(phi ? k_table_density<true> : k_table_density<false>, dim3(1),
+                               dim3(1024), 0, s, a, dense);
+            hipError_t e = hipGetLastError();
+            if (e == hipSuccess) e = launch_table_near(a, num_cu, s);
+            if (e != hipSuccess) return e;
+            variant = allpairs_variant(a.ni, num_cu);
+        }
+    }
+    if (variant == kNearVariant) return launch_table_near(a, num_cu, s);
+    if (variant == kRowsVariant) return launch_table_rows(a, S, num_cu, s);
+    const TableVariant &v = kTableVariants[variant];
     const size_t lds = table_lds_bytes(a);
     const bool wide = lds > kWideTableBytes;
     const int nt = wide ? kWideNT : 256, jt = wide ? kWideNT : v.jt;
-    S = std::max(1, S);
-    if (v.ki == 0) return launch_table_rows(a, S, num_cu, s);
     a.jchunk = (int)(((long)a.nj + (long)S * jt - 1) / ((long)S * jt) * jt);
     S = std::max(1, (a.nj + a.jchunk - 1) / a.jchunk);
     const int per_block = nt * v.ki;
@@ -466,7 +795,8 @@ hipError_t launch_table_allpairs(const TableArgs &a0, int variant, int S, int nu
     hipLaunchKernelGGL(kern, grid, dim3(nt), lds, s, a);
     e = hipGetLastError();
     if (e != hipSuccess || S == 1) return e;
-    return launch_combine_split(a.ni, S, a.part, a0.ax, a0.ay, a0.az, phi ? a0.phi : nullptr, s);
+    return launch_combine_split(a.ni, S, a.part, a0.ax, a0.ay, a0.az, phi ? a0.phi : nullptr, s,
+                                a.dense);
 }
 
 namespace {

@@ -64,8 +64,10 @@ hipError_t launch_pack_j(int n, const float *x, const float *y, const float *z, 
 // latencies (one thread per particle with its four loads a share waited for in
 // turn took 16.6 us for 27 shares of 20011 particles).
 __global__ void __launch_bounds__(256) k_combine_split(int n, int S, const float *__restrict__ part,
-                                                       float *ax, float *ay, float *az, float *phi)
+                                                       float *ax, float *ay, float *az, float *phi,
+                                                       const int *dense)
 {
+    if (dense && *dense == 0) return;
     const int c = blockIdx.y;
     float *const out = c == 0 ? ax : c == 1 ? ay : c == 2 ? az : phi;
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -86,11 +88,11 @@ __global__ void __launch_bounds__(256) k_combine_split(int n, int S, const float
 }
 
 hipError_t launch_combine_split(int n, int S, const float *part, float *ax, float *ay, float *az,
-                                float *phi, hipStream_t s)
+                                float *phi, hipStream_t s, const int *dense)
 {
     if (n <= 0 || S <= 1) return hipSuccess;
     hipLaunchKernelGGL(k_combine_split, dim3((n + 255) / 256, phi ? 4 : 3), dim3(256), 0, s, n, S,
-                       part, ax, ay, az, phi);
+                       part, ax, ay, az, phi, dense);
     return hipGetLastError();
 }
 

@@ -100,6 +100,7 @@ struct pgh_ctx {
     float tab_rcut = 0.f;
     float2 *tab = nullptr;  // device, 2^kMaxTableBits entries
     float *gcopy = nullptr;  // device, kGradCopies x 2^(kMaxAdjTableBits+1): table-adjoint scratch
+    int *word = nullptr;     // device, one word: k_table_density's answer
     float2 *ptab = nullptr;  // device, potential table on the force table's bins
     int pot_set = 0;         // ptab matches the current force table
     int variant[4] = {-1, -1, -1, -1};
@@ -596,7 +597,10 @@ int pgh_open(pgh_ctx **out, int device, void *hip_stream)
     e = hipMalloc((void **)&c->tab, sizeof(float2) << kMaxTableBits);
     const size_t gcopy_bytes = (sizeof(float2) << kMaxAdjTableBits) * kGradCopies;
     if (e == hipSuccess) e = hipMalloc((void **)&c->gcopy, gcopy_bytes);
-    if (e == hipSuccess) e = hipMalloc((void **)&c->ptab, sizeof(float2) << kMaxPotTableBits);
+    // the potential table, and behind it the word of k_table_density
+    if (e == hipSuccess)
+        e = hipMalloc((void **)&c->ptab, (sizeof(float2) << kMaxPotTableBits) + sizeof(int));
+    if (e == hipSuccess) c->word = (int *)(c->ptab + (1 << kMaxPotTableBits));
     if (e != hipSuccess) {
         g_open_error = std::string("hipMalloc(table): ") + hipGetErrorString(e);
         (void)hipFree(c->tab);
@@ -945,10 +949,11 @@ int pgh_calc_table(pgh_ctx *c, int ni, const float *xi, const float *yi, const f
     const double smax = smax_of(c->tab_E, c->tab_F);
     const float scale = table_scale(smax, c->tab_rcut);
     TableArgs a{ni, xi, yi, zi, c->nj, c->jmem, c->tab, c->tab_E, c->tab_F, scale, (float)smax,
-                table_r2max(scale, smax), ax, ay, az, 0, nullptr, phi ? c->ptab : nullptr, phi};
+                table_r2max(scale, smax), ax, ay, az, 0, nullptr, phi ? c->ptab : nullptr, phi,
+                c->word};
     int v = c->variant[PGH_FAMILY_TABLE_ALLPAIRS];
-    if (v < 0) v = table_allpairs_default(ni, c->nj, c->num_cu);
-    const int S = table_allpairs_split(a, v, kMaxSplitFloats);
+    if (v < 0) v = table_allpairs_default();
+    const int S = table_allpairs_split(a, v, c->num_cu, kMaxSplitFloats);
     if (S > 1) {
         int st = ensure_part(c, (size_t)S * 4 * ni);
         if (st) return st;

@@ -50,6 +50,9 @@ struct TableArgs {
     float *part;
     const float2 *ptable;  // (P0, P1) per node of the potential table, or NULL
     float *phi;            // potential output (with ptable), or NULL
+    // a word of device memory where k_table_density says which kernel computes
+    // the call (non-zero: k_table_allpairs); a kernel given NULL always does
+    int *dense;
 };
 
 // Arguments of the persistent batched kernels.
@@ -164,8 +167,8 @@ hipError_t launch_newton_allpairs(const NewtonArgs &a, int variant, bool refine,
 
 int table_allpairs_variants();
 const char *table_allpairs_variant_name(int v);
-int table_allpairs_default(int ni, int nj, int num_cu);
-int table_allpairs_split(const TableArgs &a, int variant, size_t part_cap);
+int table_allpairs_default();
+int table_allpairs_split(const TableArgs &a, int variant, int num_cu, size_t part_cap);
 hipError_t launch_table_allpairs(const TableArgs &a, int variant, int S, int num_cu,
                                  hipStream_t s);
 

@@ -46,12 +46,6 @@ __device__ __forceinline__ float row_sum(float v)
     return v;
 }
 
-// A wave-uniform value moved to an SGPR.
-__device__ __forceinline__ float uniform(float x)
-{
-    return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
-}
-
 // The shape of a rows launch: i-particles and threads per workgroup, and the
 // j-shares it asks for.
 struct RowsShape {

@@ -38,7 +38,8 @@ __device__ __forceinline__ void set_tile_prio(int rem, int ntiles)
 }
 
 int split_count(int ni, int nj, int ki, int jt, int target_waves, size_t part_cap);
+// (with a word `dense`: only where it is not zero)
 hipError_t launch_combine_split(int n, int S, const float *part, float *ax, float *ay, float *az,
-                                float *phi, hipStream_t s);
+                                float *phi, hipStream_t s, const int *dense = nullptr);
 
 }  // namespace pgh

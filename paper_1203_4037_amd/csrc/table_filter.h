@@ -108,12 +108,6 @@ __device__ __forceinline__ FilterOps filter_cols(float x, float y, float z, floa
     return filter_ops(k0, k1);
 }
 
-// A wave-uniform value moved to an SGPR.
-__device__ __forceinline__ float uniform(float x)
-{
-    return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
-}
-
 // A lane's value of particle l mod 32 and of particle 32 + l mod 32.
 __device__ __forceinline__ void both_halves(float v, float *o)
 {
@@ -160,6 +154,15 @@ __device__ __forceinline__ int lanes_below(unsigned long long who)
 {
     return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(who >> 32),
                                           __builtin_amdgcn_mbcnt_lo((unsigned)who, 0u));
+}
+
+// LDS operations of one wave complete in order; this keeps the compiler
+// from moving reads of a wave's tile above the writes of its other lanes.
+__device__ __forceinline__ void wave_sync_tile()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // The candidates of 64 rows for the column lane mod 32 of one operand: bit

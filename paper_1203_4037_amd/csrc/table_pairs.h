@@ -77,6 +77,12 @@ __device__ __forceinline__ void table_to_lds(float2 *stab, const float2 *__restr
     }
 }
 
+// A wave-uniform value moved to an SGPR.
+__device__ __forceinline__ float uniform(float x)
+{
+    return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
+}
+
 // Whether a position and mass are ordinary: small enough that no difference
 // of two such positions overflows when squared, and the mass finite.  A pair of
 // ordinary particles beyond the cutoff, whose node's entries are zero, adds

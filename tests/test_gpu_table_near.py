@@ -179,3 +179,31 @@ def test_default_against_the_oracle_with_many_pairs_inside(pgh, ctx):
     has = np.nan_to_num(ref[3]) > 0
     e = norm_vec_err(a[:, has], np.stack(ref[:3])[:, has], ref[3][has])
     assert rms(e) <= 1e-5 and e.max() <= 1e-3, (rms(e), e.max())
+
+
+# sizes at the edges of the columns, the chunks and the waves' shares; both
+# sides of the built-in choice, which for the last two is made on the device
+@pytest.mark.parametrize("ni,nj,variant", [(1, 1, "near"), (31, 64, "near"), (33, 65, "near"),
+                                           (64, 513, "near"), (129, 4097, "near"),
+                                           (2001, 1025, "near"), (40000, 700, "near"),
+                                           (1000, 90000, None), (2000, 60000, None),
+                                           (8191, 13000, None), (8193, 13000, None),
+                                           (40000, 4095, None), (20001, 20001, None)])
+@pytest.mark.parametrize("rcut", [0.03, 0.4])
+def test_all_pairs_counts_of_the_near_kernel(pgh, ctx, ni, nj, variant, rcut):
+    """Counts of up to 300 spread rows; a whole second call into fresh outputs
+    agrees, so the choice made on the device leaves no row unwritten."""
+    rng = np.random.default_rng(ni + nj)
+    pi = (0.5 * rng.random((3, ni))).astype(np.float32)
+    pj = (0.5 * rng.random((3, nj))).astype(np.float32)
+    _count_table(pgh, ctx, rcut)
+    fam = pgh.PGH_FAMILY_TABLE_ALLPAIRS
+    names = [pgh.pgh_variant_name(fam, v) for v in range(pgh.pgh_variant_count(fam))]
+    ctx.set_variant(fam, -1 if variant is None else names.index(variant))
+    di = to_dev(*pi)
+    ctx.set_j(*to_dev(*pj, np.ones(nj, np.float32)))
+    out = [np.stack(to_host(*ctx.table_force(*di, with_phi=True))) for _ in range(2)]
+    rows = np.unique(np.linspace(0, ni - 1, 300).astype(int))
+    items = [(int(i), 1, 0, nj) for i in rows]
+    assert np.array_equal(out[0][3][rows], _counts(items, pi, pj, rcut)[rows])
+    assert np.array_equal(*out) and np.isfinite(out[0]).all()
