@@ -455,7 +455,8 @@ int plan_fill(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items, int n
     {
         std::string err;
         const int st =
-            plan_tasks(items, n_items, ni_total, nj_total, p->waves, hp, err, c->plan_pack != 0);
+            plan_tasks(items, n_items, ni_total, nj_total, p->waves, hp, err, c->plan_pack != 0,
+                       p->tree_owned ? kTreeRule : PlanRule{});
         if (st) return fail(c, st, err);
     }
     DeviceGuard g(c->device);
@@ -499,7 +500,8 @@ int plan_fill_device(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items
     if (c->plan_pack) return plan_fill(c, p, n_items, items, ni_total, nj_total);
     {
         std::string err;
-        const int st = plan_descs(items, n_items, ni_total, nj_total, p->waves, dp, err);
+        const int st = plan_descs(items, n_items, ni_total, nj_total, p->waves, dp, err,
+                                  p->tree_owned ? kTreeRule : PlanRule{});
         if (st == kPlanOnHost) return plan_fill(c, p, n_items, items, ni_total, nj_total);
         if (st) return fail(c, st, err);
     }
@@ -1662,9 +1664,9 @@ int pgh_tree_walk(pgh_ctx *c, pgh_tree *t, float theta, int record_src)
             t->plan->tree_owned = true;
             c->plans.push_back(t->plan);
         }
-        st = c->plan_device ? plan_fill_device(c, t->plan, s.n_groups, s.host_items.data(), s.n,
+        st = c->plan_device ? plan_fill_device(c, t->plan, s.n_groups, s.host_items, s.n,
                                                (int)s.n_entries)
-                            : plan_fill(c, t->plan, s.n_groups, s.host_items.data(), s.n,
+                            : plan_fill(c, t->plan, s.n_groups, s.host_items, s.n,
                                         (int)s.n_entries);
         if (st) {
             drop_plan();

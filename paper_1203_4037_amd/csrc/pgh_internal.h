@@ -258,7 +258,7 @@ struct TreeState {
     int node_cap = 0;
     int *begin = nullptr, *count = nullptr, *level = nullptr, *first_child = nullptr,
         *n_child = nullptr, *parent = nullptr;
-    int *nc = nullptr;        // per level: children per node, chunk sums, child bounds
+    int *nc = nullptr;        // per rank: levels of its nodes; node counts per level
     long long nc_cap = 0;
     NodeMoments *mom = nullptr;
     float4 *com = nullptr;    // FP32 centre of mass per node (w unused)
@@ -280,7 +280,6 @@ struct TreeState {
     size_t tmp_bytes = 0;
     unsigned *word = nullptr;  // 16 words: min/max frame, leaf count, walk overflow, frontier
     int *count_out = nullptr;
-    float *rc2 = nullptr;      // (l_L / theta)^2 per level for the walk
     int *lvl = nullptr;        // first node of each level (device), kTreeMaxLevel + 3 entries
     // results of the last build / walk
     int n = 0, n_nodes = 0, n_leaves = 0, depth = 0, n_groups = 0, max_level_nodes = 0;
@@ -292,7 +291,11 @@ struct TreeState {
     float theta = 0.f;
     int record_src = 0;
     long long n_entries = 0, interactions = 0;
-    std::vector<pgh_item> host_items;
+    // pinned host memory: what the host reads of a build and a walk, and the
+    // items of the last walk, n_groups of them
+    void *page = nullptr;
+    pgh_item *host_items = nullptr;
+    int host_items_cap = 0;
 };
 
 // Each returns PGH_OK or a status with a message in `err`.  Every step runs on

@@ -218,9 +218,9 @@ int deal_layout(size_t n, int *q_begin)
 // with short ones.  (Equal tasks of half a wave's work leave the last round
 // of the queue mostly idle whenever the task count is just above a multiple
 // of the wave count.)
-long long part_length(long long wave_iters, int waves, int div = 8)
+long long part_length(long long wave_iters, long long n64, int waves, const PlanRule &rule)
 {
-    return std::max(512LL, (wave_iters / waves / div + 63) / 64 * 64);
+    return std::max(n64 < waves ? (long long)rule.part_min : 512LL, (wave_iters / waves / rule.part_div + 63) / 64 * 64);
 }
 
 }  // namespace
@@ -244,9 +244,11 @@ int plan_tasks(const pgh_item *items, int n_items, int ni_total, int nj_total, i
     // added inside the wave).
     waves = std::max(1, waves);
     int csize = 64;
+    long long n64 = 0;  // chunks of 64
     for (;;) {
         long long n = 0;
         for (int t : order) n += (items[t].n_i + csize - 1) / csize;
+        if (csize == 64) n64 = n;
         if (n >= waves || csize <= rule.min_chunk) break;
         csize /= 2;
     }
@@ -291,7 +293,7 @@ int plan_tasks(const pgh_item *items, int n_items, int ni_total, int nj_total, i
             if (pack && n < 64 && it.n_j > 0) open = (int)chunks.size() - 1;
         }
     }
-    const long long part_iters = part_length(total, waves, rule.part_div);
+    const long long part_iters = part_length(total, n64, waves, rule);
     // add_work records a wave's work (chunk a, and chunk b sharing the wave,
     // or b < 0), its cut and its tasks with their costs
     std::vector<PlanWork> &work = out.work;
@@ -396,7 +398,7 @@ void write_tasks(const HostPlan &hp, Task *dst)
 }
 
 int plan_descs(const pgh_item *items, int n_items, int ni_total, int nj_total, int waves,
-               DescPlan &out, std::string &err)
+               DescPlan &out, std::string &err, const PlanRule &rule)
 {
     Scratch &S = scratch();
     std::vector<int> &order = S.order;
@@ -416,8 +418,8 @@ int plan_descs(const pgh_item *items, int n_items, int ni_total, int nj_total, i
         total += n_full * std::max(1LL, (long long)it.n_j);
         if (n_last) total += std::max(1LL, lane_steps(it.n_j, chunk_js(n_last)));
     }
-    if (n64 < waves) return kPlanOnHost;
-    const long long part_iters = part_length(total, waves);
+    if (n64 < waves && rule.min_chunk < 64) return kPlanOnHost;
+    const long long part_iters = part_length(total, n64, waves, rule);
     // every cost is at most part_iters + 64 (a part of at most part_iters
     // steps rounded up to whole tiles), so kmax - cost fits the sort keys
     const long long kmax = part_iters + 64;

@@ -57,8 +57,16 @@ struct PlanRule {
     int min_chunk = 16;  // 16, 32 or 64
     int part_div = 8;    // parts of 1 / part_div of a wave's share of the work
     bool pair = true;    // pair partly filled chunks (without packing)
+    int part_min = 512;  // entries of a part at least (512 once chunks of 64 fill the waves)
 };
 constexpr PlanRule kNearRule{32, 1, false};
+// A tree's lists are planned anew at every walk, and only a plan in chunks of 64
+// has the compact form that the device expands: with chunks of 16 the host took
+// longer than the tree's kernels (walk and plan of 531 groups, 131072 particles:
+// 641 us, 165 so).  Parts of 256 make up for the waves that whole chunks leave
+// empty (the force of 115 groups 42 us, with 512 and 128 entries 54 and 42, in
+// chunks of 16 54).
+constexpr PlanRule kTreeRule{64, 8, true, 256};
 inline int near_waves(int waves) { return waves / 4 > 1 ? waves / 4 : 1; }
 
 // Validates the items (non-negative fields, inside the arrays, disjoint
@@ -94,7 +102,7 @@ constexpr int kPlanOnHost = 1;
 // same plan.  Returns PGH_OK, kPlanOnHost, or an error status with a
 // message in err.
 int plan_descs(const pgh_item *items, int n_items, int ni_total, int nj_total, int waves,
-               DescPlan &out, std::string &err);
+               DescPlan &out, std::string &err, const PlanRule &rule = {});
 
 // Task lists of the table adjoint: j-major (a chunk of j-entries against the
 // item's i-range) and i-major (an i-chunk against a j-range).

@@ -161,36 +161,76 @@ __global__ void __launch_bounds__(256) k_gather(int n, const int *__restrict__ p
     xm[r] = v;
 }
 
-// Level table of the octree build: level L holds nodes [lvl[L], lvl[L + 1]);
-// the write kernel of level L sets lvl[L + 2].  All sizes stay on the device:
-// the host launches every level without waiting for the one before.
+// Level table of the octree build: level L holds nodes [lvl[L], lvl[L + 1]),
+// in rank order.  All sizes stay on the device: the host launches the whole
+// build without waiting.
 constexpr int kLvl = kTreeMaxLevel + 3;
+constexpr int kLevels = kTreeMaxLevel + 1;
+// What the host reads after a wait, written by kernels into pinned memory (a
+// copy to ordinary host memory costs a launch and a wait of its own each).
+struct TreeHostPage {
+    unsigned word[16];
+    int lvl[kLvl];
+    int n_groups;
+    long long entries;
+};
+__global__ void __launch_bounds__(64) k_report(const unsigned *w, const int *lvl,
+                                               const int *n_groups, TreeHostPage *page)
+{
+    const int i = threadIdx.x;
+    if (i < 16) page->word[i] = w[i];
+    if (lvl && i < kLvl) page->lvl[i] = lvl[i];
+    if (n_groups && i == 0) page->n_groups = *n_groups;
+}
+
 // word indices in TreeState::word
 constexpr int kWordLeaves = 6, kWordOverflow = 9, kWordMaxLevel = 10;
 
-__global__ void k_root(int n, int *begin, int *count, int *level, int *parent, int *lvl)
+// The octree of the sorted keys, all levels at once.  With d(r) the leading
+// octal digits that key r shares with key r - 1 (-1 for r = 0), the cells that
+// begin at rank r are those of the levels above d(r); such a cell is a node if
+// its parent holds more than n_leaf particles.  So each rank knows from a few
+// neighbouring keys the levels (consecutive ones) of the nodes that begin at
+// it, as a mask, and a node's place in its level is the number of nodes of the
+// level that begin at earlier ranks:
+//   k_node_mask   the masks, and per chunk of 256 ranks and level their counts;
+//   k_node_scan   the counts' offsets within each level;
+//   k_node_write  the level table and the nodes' first rank, level, parent and
+//                 first child (the children of a node are consecutive: they
+//                 begin at its ranks);
+//   k_node_ends   the nodes' particle counts and numbers of children.
+// Four launches, bound by their latency and two passes over the keys; the same
+// nodes in the same order level by level took three launches for each of the 22
+// levels, 482 us of a tree of 2^20 particles; these four take 45.
+constexpr int kNodeChunk = 256;  // ranks of a wave in k_node_mask and k_node_write
+
+// leading octal digits that two keys share (kTreeMaxLevel: the same key)
+__device__ inline int common_digits(unsigned long long a, unsigned long long b)
 {
-    begin[0] = 0;
-    count[0] = n;
-    level[0] = 0;
-    parent[0] = -1;
-    lvl[0] = 0;
-    lvl[1] = 1;
-    for (int L = 2; L < kLvl; ++L) lvl[L] = 1;
+    const unsigned long long x = a ^ b;
+    return x ? (__clzll((long long)x) - 1) / 3 : kTreeMaxLevel;
 }
 
-__device__ inline int digit_of(unsigned long long k, int L)
+// the cell of a key at level L
+__device__ inline unsigned long long cell_at(unsigned long long k, int L)
 {
-    return (int)((k >> (3 * (kTreeMaxLevel - L))) & 7ull);
+    return k >> (3 * (kTreeMaxLevel - L));
 }
 
-// First r in [lo, hi) whose digit at level L is >= d (keys sorted and sharing
-// the digits above L, so the digit is non-decreasing in r).
-__device__ inline int lower_digit(const unsigned long long *key, int lo, int hi, int d, int L)
+// First r in (lo, hi] beyond the cell at level L of rank lo (hi: none before).
+__device__ inline int cell_end(const unsigned long long *key, int lo, int hi, int L)
 {
+    const unsigned long long c = cell_at(key[lo], L);
+    int step = 8;  // most cells are small: doubling steps, then the search
+    while (step < hi - lo && cell_at(key[lo + step], L) == c) {
+        lo += step;
+        step = min(2 * step, 1 << 29);
+    }
+    hi = lo + min(step, hi - lo);
+    ++lo;
     while (lo < hi) {
         const int mid = lo + ((hi - lo) >> 1);
-        if (digit_of(key[mid], L) < d)
+        if (cell_at(key[mid], L) == c)
             lo = mid + 1;
         else
             hi = mid;
@@ -198,12 +238,52 @@ __device__ inline int lower_digit(const unsigned long long *key, int lo, int hi,
     return lo;
 }
 
-// The split of level L in three kernels, with the level's size read on the
-// device: k_split_count (block b takes the b-th of kSplitBlocks contiguous
-// chunks of the level's nodes), k_split_scan (one workgroup: the chunks'
-// offsets and the next level's size), k_split_write (the same chunks again:
-// each node's children go to the next level at its offset).
-constexpr int kSplitBlocks = 2048;
+__global__ void __launch_bounds__(256) k_node_mask(int n, int n_leaf,
+                                                   const unsigned long long *__restrict__ key,
+                                                   unsigned *__restrict__ mask, int chunks,
+                                                   int *__restrict__ sums)
+{
+    const int lane = threadIdx.x & 63;
+    const int chunk = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6);
+    if (chunk >= chunks) return;
+    int sum = 0;  // lane L: the chunk's nodes of level L, the lane after: its leaves
+#pragma unroll 1
+    for (int k = 0; k < kNodeChunk / 64; ++k) {
+        const long long rl = (long long)chunk * kNodeChunk + 64 * k + lane;
+        const int r = (int)min(rl, (long long)n - 1);
+        const unsigned long long me = key[r];
+        const int d = r == 0 ? -1 : common_digits(key[r - 1], me);
+        // levels <= e of the cells that begin here are split
+        const int e = n_leaf < n - r ? common_digits(me, key[r + n_leaf]) : -1;
+        bool node = d < kTreeMaxLevel;
+        if (node && d >= 0 && e < d) {
+            // is the parent's cell, of level d, longer than n_leaf?  Its first
+            // rank, if within n_leaf before r, and its length from there
+            const unsigned long long c = cell_at(me, d);
+            int lo = r > n_leaf ? r - n_leaf : 0, hi = r - 1;
+            while (lo < hi) {
+                const int mid = lo + ((hi - lo) >> 1);
+                if (cell_at(key[mid], d) == c)
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
+            node = n_leaf < n - lo && cell_at(key[lo + n_leaf], d) == c;
+        }
+        const int first = d + 1, last = max(first, min(e, kTreeMaxLevel - 1) + 1);
+        unsigned m = node ? (2u << last) - (1u << first) : 0u;
+        if (rl >= n) m = 0u;
+        if (rl < n) mask[r] = m;
+        for (int L = 0; L < kLevels; ++L) {
+            const int c = __popcll(__ballot((m >> L) & 1));
+            sum += lane == L ? c : 0;
+        }
+        // of the nodes that begin at a rank the deepest is a leaf
+        const int c = __popcll(__ballot(m != 0));
+        sum += lane == kLevels ? c : 0;
+    }
+    if (lane <= kLevels) sums[(size_t)lane * chunks + chunk] = sum;
+}
 
 // Inclusive prefix sum over the 64 lanes of a wave (all lanes active) by DPP
 // lane moves: the sums of up to four lanes inside each row of 16 (row shifts
@@ -237,145 +317,131 @@ __device__ inline int block_incl_scan(int v, int *sh, int *total)
     return v + add;
 }
 
-__device__ inline void split_chunk(int n, int *lo, int *hi)
-{
-    const int chunk = (n + kSplitBlocks - 1) / kSplitBlocks;
-    *lo = min(n, (int)blockIdx.x * chunk);
-    *hi = min(n, *lo + chunk);
-}
-
-// nc[i] = non-empty children of the i-th node of level L (0 for a leaf),
-// bnd[7 i + d - 1] = the first particle of its child digits >= d (d = 1..7;
-// for split nodes only), bsum[b] = the children of chunk b;
-// w[kWordLeaves] counts the leaves (one atomic per workgroup).  Eight lanes
-// take a node, lane d - 1 searching boundary d over the whole node (the
-// searches are independent, so a node costs one binary search of latency).
-__global__ void __launch_bounds__(256) k_split_count(int L, int n_leaf,
-                                                     const int *__restrict__ lvl,
-                                                     const int *__restrict__ begin,
-                                                     const int *__restrict__ count,
-                                                     const unsigned long long *__restrict__ key,
-                                                     int *__restrict__ nc, int *__restrict__ bnd,
-                                                     int *__restrict__ bsum, unsigned *w)
+// Workgroup L: the exclusive offsets of the chunks' counts of level L, in
+// place, and the level's size in total[L] (the last workgroup: of the leaves).
+__global__ void __launch_bounds__(256) k_node_scan(int chunks, int *sums, int *total)
 {
     __shared__ int sh[4];
-    if (w[kWordOverflow]) return;
-    const int off = lvl[L], n_level = lvl[L + 1] - off;
-    int lo, hi;
-    split_chunk(n_level, &lo, &hi);
-    const int g = (int)threadIdx.x >> 3, j = (int)threadIdx.x & 7;
-    int kids = 0, leaves = 0;
-    for (int i0 = lo; i0 < hi; i0 += 32) {  // uniform trip count for the workgroup
-        const int i = i0 + g;
-        int b = 0, c = 0;
-        if (i < hi) {
-            b = begin[off + i];
-            c = count[off + i];
-        }
-        const bool split = i < hi && c > n_leaf && L < kTreeMaxLevel;
-        int p = b + c;  // lane 7: the node's end
-        if (split && j < 7) p = lower_digit(key, b, b + c, j + 1, L + 1);
-        // child j of the node is [boundary j, boundary j + 1), boundary 0 = b
-        // (DPP lane moves: the lane before, then the sum over the group by
-        // the pairs inside each quad and the half-row mirror)
-        const int q = __builtin_amdgcn_update_dpp(0, p, 0x111, 0xF, 0xF, true);  // row_shr:1
-        const int start = j == 0 ? b : q;
-        int k = (split && p > start) ? 1 : 0;
-        k += __builtin_amdgcn_update_dpp(0, k, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-        k += __builtin_amdgcn_update_dpp(0, k, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
-        k += __builtin_amdgcn_update_dpp(0, k, 0x141, 0xF, 0xF, false);  // row_half_mirror
-        if (split && j < 7) bnd[7 * (size_t)i + j] = p;
-        if (i < hi && j == 0) {
-            nc[i] = k;
-            kids += k;
-            leaves += k == 0;
-        }
-    }
-    int tot = 0;
-    block_incl_scan(kids, sh, &tot);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-    block_incl_scan(leaves, sh, &tot);
-    if (threadIdx.x == 0 && tot) atomicAdd(&w[kWordLeaves], (unsigned)tot);
-}
-
-// The chunks' exclusive offsets in bsum, and the next level's size in
-// lvl[L + 2].  Children that would pass the node capacity set the overflow
-// word instead: every later kernel of the build returns at once, and the
-// host builds again with more room.
-__global__ void __launch_bounds__(256) k_split_scan(int L, int cap, int *lvl, int *bsum,
-                                                    unsigned *w)
-{
-    __shared__ int sh[4];
-    if (w[kWordOverflow]) return;
-    constexpr int per = kSplitBlocks / 256;
-    int v[per], sum = 0;
+    int *v = sums + (size_t)blockIdx.x * chunks;
+    int run = 0;
+    for (int c0 = 0; c0 < chunks; c0 += 1024) {
+        const int c = c0 + 4 * (int)threadIdx.x;
+        int x[4], sum = 0, tot = 0;
 #pragma unroll
-    for (int k = 0; k < per; ++k) {
-        v[k] = bsum[per * threadIdx.x + k];
-        sum += v[k];
-    }
-    int tot = 0;
-    int run = block_incl_scan(sum, sh, &tot) - sum;
-#pragma unroll
-    for (int k = 0; k < per; ++k) {
-        bsum[per * threadIdx.x + k] = run;
-        run += v[k];
-    }
-    if (threadIdx.x == 0) {
-        const int next_off = lvl[L + 1];
-        if ((long long)next_off + tot > cap) {
-            atomicOr(&w[kWordOverflow], 1u);
-            lvl[L + 2] = next_off;
-        } else {
-            lvl[L + 2] = next_off + tot;
-            atomicMax(&w[kWordMaxLevel], (unsigned)tot);
+        for (int k = 0; k < 4; ++k) {
+            x[k] = c + k < chunks ? v[c + k] : 0;
+            sum += x[k];
         }
-    }
-}
-
-// Writes the children of level L (from the bounds k_split_count kept) at
-// lvl[L + 1] + the node's offset.
-__global__ void __launch_bounds__(256) k_split_write(int L, const int *__restrict__ lvl,
-                                                     const int *__restrict__ nc,
-                                                     const int *__restrict__ bnd,
-                                                     const int *__restrict__ bsum, int *begin,
-                                                     int *count, int *level, int *first_child,
-                                                     int *n_child, int *parent,
-                                                     const unsigned *w)
-{
-    __shared__ int sh[4];
-    if (w[kWordOverflow]) return;
-    const int off = lvl[L], n_level = lvl[L + 1] - off, next_off = lvl[L + 1];
-    int lo, hi;
-    split_chunk(n_level, &lo, &hi);
-    int run = bsum[blockIdx.x];
-    for (int t0 = lo; t0 < hi; t0 += 256) {  // uniform trip count for the workgroup
-        const int i = t0 + (int)threadIdx.x;
-        const int k = i < hi ? nc[i] : 0;
-        int tot = 0;
-        const int incl = block_incl_scan(k, sh, &tot);
-        if (i < hi) {
-            const int node = off + i;
-            const int fc = next_off + run + incl - k;
-            if (k) {
-                const int b = begin[node], c = count[node];
-                int prev = b, j = fc;
-                for (int d = 1; d <= 8; ++d) {
-                    const int p = d == 8 ? b + c : bnd[7 * (size_t)i + d - 1];
-                    if (p > prev) {
-                        begin[j] = prev;
-                        count[j] = p - prev;
-                        level[j] = L + 1;
-                        parent[j] = node;
-                        ++j;
-                    }
-                    prev = p;
-                }
-            }
-            first_child[node] = k ? fc : -1;
-            n_child[node] = k;
+        int at = run + block_incl_scan(sum, sh, &tot) - sum;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (c + k < chunks) v[c + k] = at;
+            at += x[k];
         }
         run += tot;
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = run;
+}
+
+// More nodes than the arrays hold set the overflow word instead: every later
+// kernel of the build returns at once, and the host builds again with more room.
+__global__ void __launch_bounds__(256) k_node_write(int n, const unsigned *__restrict__ mask,
+                                                    int chunks, const int *__restrict__ sums,
+                                                    const int *__restrict__ total, int cap,
+                                                    int *__restrict__ begin,
+                                                    int *__restrict__ level,
+                                                    int *__restrict__ first_child,
+                                                    int *__restrict__ n_child,
+                                                    int *__restrict__ parent, int *lvl, unsigned *w)
+{
+    const int lane = threadIdx.x & 63;
+    const int chunk = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6);
+    int off[kLevels + 1];
+    long long all = 0;
+    int widest = 0;
+#pragma unroll
+    for (int L = 0; L < kLevels; ++L) {
+        const int c = total[L];
+        off[L] = (int)all;
+        all = min(all + c, (long long)INT_MAX);
+        if (L) widest = max(widest, c);
+    }
+    off[kLevels] = (int)all;
+    const bool over = all > cap;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+#pragma unroll
+        for (int L = 0; L <= kLevels; ++L) lvl[L] = off[L];
+        lvl[kLevels + 1] = off[kLevels];
+        if (over) w[kWordOverflow] = 1u;
+        w[kWordMaxLevel] = (unsigned)widest;
+        w[kWordLeaves] = (unsigned)total[kLevels];
+    }
+    if (over || chunk >= chunks) return;
+    // lane L: the nodes of level L before this step
+    int run = lane < kLevels ? sums[(size_t)lane * chunks + chunk] : 0;
+    const unsigned long long before = (1ull << lane) - 1;
+    unsigned ms[kNodeChunk / 64];
+#pragma unroll
+    for (int k = 0; k < kNodeChunk / 64; ++k) {
+        const long long rl = (long long)chunk * kNodeChunk + 64 * k + lane;
+        ms[k] = rl < n ? mask[rl] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kNodeChunk / 64; ++k) {
+        const long long rl = (long long)chunk * kNodeChunk + 64 * k + lane;
+        const unsigned m = ms[k];
+        int node = -1;  // this rank's node of level L - 1, where it has one
+        int last = -1;  // the last node of level L - 1 that begins at or before r
+#pragma unroll
+        for (int L = 0; L < kLevels; ++L) {
+            const unsigned long long b = __ballot((m >> L) & 1);
+            const int at0 = off[L] + __builtin_amdgcn_readlane(run, L);
+            if (b == 0) {
+                node = -1;
+                last = at0 - 1;
+                continue;
+            }
+            const int at = at0 + __popcll(b & before);
+            run += lane == L ? __popcll(b) : 0;
+            const bool has = (m >> L) & 1;
+            if (has) {
+                if (node >= 0) first_child[node] = at;
+                begin[at] = (int)rl;
+                level[at] = L;
+                parent[at] = last;
+                if (!((m >> L) & 2)) {  // no node begins here a level below: a leaf
+                    first_child[at] = -1;
+                    n_child[at] = 0;
+                }
+            }
+            node = has ? at : -1;
+            last = has ? at : at - 1;
+        }
+    }
+}
+
+// A node ends where its next sibling begins, the last one with its cell; the
+// last one also knows the number of its parent's children.
+__global__ void __launch_bounds__(256) k_node_ends(int n, const unsigned long long *__restrict__ key,
+                                                   const int *__restrict__ lvl,
+                                                   const unsigned *__restrict__ w,
+                                                   const int *__restrict__ begin,
+                                                   const int *__restrict__ level,
+                                                   const int *__restrict__ first_child,
+                                                   const int *__restrict__ parent,
+                                                   int *__restrict__ count,
+                                                   int *__restrict__ n_child)
+{
+    if (w[kWordOverflow]) return;
+    const int nodes = lvl[kLevels];
+    for (int j = blockIdx.x * 256 + threadIdx.x; j < nodes; j += gridDim.x * 256) {
+        const int b = begin[j], p = parent[j];
+        if (j + 1 < nodes && parent[j + 1] == p) {
+            count[j] = begin[j + 1] - b;
+        } else {
+            count[j] = cell_end(key, b, n, level[j]) - b;
+            if (p >= 0) n_child[p] = j + 1 - first_child[p];
+        }
     }
 }
 
@@ -648,7 +714,7 @@ struct WalkArgs {
     const int4 *node;  // walk records (k_pack_nodes)
     const float4 *com, *pp;
     int npp;
-    const float *rc2;  // (l_L / theta)^2 per level, device
+    float rc2[kTreeMaxLevel + 1];  // (l_L / theta)^2 per level
     const float4 *xm;  // particles (x, y, z, m) in key order
     long long *glen;        // pass 1 output: list length per group
     const long long *goff;  // pass 2 input: list offset per group
@@ -659,40 +725,39 @@ struct WalkArgs {
 };
 
 
-// LDS written by some lanes of a wave and then read by others.
-__device__ inline void wave_sync_lds()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
+constexpr int kWalkWaves = 4;  // waves of a workgroup, walking one group together
+constexpr int kMapSeg = 256;  // entries per wave of a segment of the write pass's map
 
-constexpr int kWalkWaves = 2;  // waves per workgroup, each walking its own groups
-constexpr int kMapSeg = 256;  // entries per segment of the write pass's map
-
-// Breadth-first walk of one group per wave.  The 64 lanes test 64 frontier
-// nodes at a time; wave prefix sums place each lane's contributions in the
-// list and its opened children in the next frontier (double-buffered in LDS).
-// Pass 1 (WRITE = false) only counts; pass 2 writes the entries at the
-// offsets of the scanned counts, in the same order: the contributions of 64
-// nodes form one contiguous block of the list, which the lanes write entry
-// by entry (coalesced), each finding its entry's node by a binary search over
-// the wave's inclusive counts.
+// Breadth-first walk, a workgroup of W = kWalkWaves waves per group.  Its 64 W lanes test as
+// many frontier nodes at a time; prefix sums over the workgroup place each
+// lane's contributions in the list and its opened children in the next
+// frontier (double-buffered in LDS).  Pass 1 (WRITE = false) only counts; pass
+// 2 writes the entries at the offsets of the scanned counts, in the same
+// order: the contributions of the nodes tested together form one contiguous
+// block of the list, which the lanes write entry by entry (coalesced), each
+// finding its entry's node through a map.
+//
+// Bound by the latency of its steps, some 20 levels deep with a few hundred
+// nodes each, so four waves share a group: 3739 groups of a tree of 2^20
+// particles 63 us to count and 106 to write, against 107 and 214 with a wave
+// per group; not slower with 53342 groups of at most 64 either.
 template <bool WRITE, int FCAP>
 __global__ void __launch_bounds__(64 * kWalkWaves) k_walk(WalkArgs a)
 {
-    __shared__ int fr[kWalkWaves][2][FCAP];
+    constexpr int W = kWalkWaves;
+    __shared__ int fr[2][FCAP];
+    __shared__ int2 tot[2][W];
     // write pass: each lane's first entry and source code, and the lane that
-    // owns each entry of a segment of kMapSeg entries
-    __shared__ int s_start[kWalkWaves][64], s_src[kWalkWaves][64];
-    __shared__ unsigned char s_map[kWalkWaves][kMapSeg];
+    // owns each entry of a segment of kMapSeg W entries
+    __shared__ int s_start[WRITE ? 64 * W : 1], s_src[WRITE ? 64 * W : 1];
+    __shared__ unsigned char s_map[WRITE ? kMapSeg * W : 1];
     __shared__ float rc2[kTreeMaxLevel + 1];
-    if (threadIdx.x <= kTreeMaxLevel) rc2[threadIdx.x] = a.rc2[threadIdx.x];
-    __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int n_waves = gridDim.x * kWalkWaves;
-    int maxf = 0;  // largest frontier this wave met (one atomic at the end)
-    for (int g = blockIdx.x * kWalkWaves + w; g < a.n_groups; g += n_waves) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid <= kTreeMaxLevel) rc2[tid] = a.rc2[tid];
+    if (!WRITE && blockIdx.x == 0 && tid == 0) a.glen[a.n_groups] = 0;  // for the scan's total
+    int maxf = 0;  // largest frontier of this workgroup (one atomic at the end)
+    int step = 0;
+    for (int g = blockIdx.x; g < a.n_groups; g += gridDim.x) {
         const int gn = a.groups[g];
         const float4 lo = a.glo[g], hi = a.ghi[g];
         const int4 grec = a.node[gn];
@@ -701,27 +766,24 @@ __global__ void __launch_bounds__(64 * kWalkWaves) k_walk(WalkArgs a)
         long long len = 0;
         int cur = 0, ncur = 1;
         bool over = false;
-        if (lane == 0) fr[w][0][0] = 0;
-        wave_sync_lds();
+        if (tid == 0) fr[0][0] = 0;
+        __syncthreads();
         while (ncur > 0) {
             int nnext = 0;
-            for (int c0 = 0; c0 < ncur; c0 += 64) {
-                const int idx = c0 + lane;
+            for (int c0 = 0; c0 < ncur; c0 += 64 * W, step ^= 1) {
+                const int idx = c0 + tid;
                 int emit = 0, push = 0, code = 0, fc = 0;
                 if (idx < ncur) {
-                    const int t = fr[w][cur][idx];
+                    const int t = fr[cur][idx];
                     const int4 r = a.node[t];
+                    const float4 cm = a.com[t];
                     const int b = r.x, c = r.y, nch = r.w & 0xffff, L = r.w >> 16;
                     fc = r.z;
                     const bool anc = L <= glev && b <= gb && gb < b + c;
-                    bool acc = false;
-                    if (!anc) {
-                        const float4 cm = a.com[t];
-                        const float ex = fmaxf(fmaxf(lo.x - cm.x, cm.x - hi.x), 0.f);
-                        const float ey = fmaxf(fmaxf(lo.y - cm.y, cm.y - hi.y), 0.f);
-                        const float ez = fmaxf(fmaxf(lo.z - cm.z, cm.z - hi.z), 0.f);
-                        acc = rc2[L] < ex * ex + ey * ey + ez * ez;
-                    }
+                    const float ex = fmaxf(fmaxf(lo.x - cm.x, cm.x - hi.x), 0.f);
+                    const float ey = fmaxf(fmaxf(lo.y - cm.y, cm.y - hi.y), 0.f);
+                    const float ez = fmaxf(fmaxf(lo.z - cm.z, cm.z - hi.z), 0.f);
+                    const bool acc = !anc && rc2[L] < ex * ex + ey * ey + ez * ez;
                     if (acc) {
                         emit = a.npp;
                         code = t * a.npp;  // first pseudo-particle
@@ -732,36 +794,47 @@ __global__ void __launch_bounds__(64 * kWalkWaves) k_walk(WalkArgs a)
                         push = nch;
                     }
                 }
-                const int e_inc = wave_incl_scan(emit);
-                const int p_inc = wave_incl_scan(push);
-                const int e_tot = __builtin_amdgcn_readlane(e_inc, 63);
-                const int p_tot = __builtin_amdgcn_readlane(p_inc, 63);
+                int e_inc = wave_incl_scan(emit);
+                int p_inc = wave_incl_scan(push);
+                // two buffers in turn: one barrier a step is enough
+                if (lane == 63) tot[step][w] = make_int2(e_inc, p_inc);
+                __syncthreads();
+                int e_tot = 0, p_tot = 0, e_before = 0, p_before = 0;
+#pragma unroll
+                for (int k = 0; k < W; ++k) {
+                    const int2 v = tot[step][k];
+                    if (k < w) e_before += v.x, p_before += v.y;
+                    e_tot += v.x;
+                    p_tot += v.y;
+                }
+                e_inc += e_before;
+                p_inc += p_before;
                 if (nnext + p_tot > FCAP) {
                     over = true;
                     break;
                 }
-                for (int k = 0; k < push; ++k) fr[w][cur ^ 1][nnext + p_inc - push + k] = fc + k;
+                for (int k = 0; k < push; ++k) fr[cur ^ 1][nnext + p_inc - push + k] = fc + k;
                 if (WRITE && e_tot > 0) {
                     const int r0 = e_inc - emit;  // this lane's first entry
-                    s_start[w][lane] = r0;
-                    s_src[w][lane] = code;
+                    s_start[tid] = r0;
+                    s_src[tid] = code;
                     const long long base = out + len;
                     // segment by segment: every lane marks its entries in the
-                    // map, then the entries are written 64 at a time, each lane
-                    // finding its entry's source through the map
-                    for (int seg = 0; seg < e_tot; seg += kMapSeg) {
-                        const int m0 = max(r0, seg), m1 = min(e_inc, seg + kMapSeg);
-                        for (int e = m0; e < m1; ++e) s_map[w][e - seg] = (unsigned char)lane;
-                        wave_sync_lds();
-                        const int seg_end = min(e_tot, seg + kMapSeg);
-                        for (int e = seg + lane; e < seg_end; e += 64) {
-                            const int l = s_map[w][e - seg];
-                            const int k = e - s_start[w][l];
-                            const int cd = s_src[w][l];
+                    // map, then the entries are written, each lane finding its
+                    // entry's source through the map
+                    for (int seg = 0; seg < e_tot; seg += kMapSeg * W) {
+                        const int m0 = max(r0, seg), m1 = min(e_inc, seg + kMapSeg * W);
+                        for (int e = m0; e < m1; ++e) s_map[e - seg] = (unsigned char)tid;
+                        __syncthreads();
+                        const int seg_end = min(e_tot, seg + kMapSeg * W);
+                        for (int e = seg + tid; e < seg_end; e += 64 * W) {
+                            const int l = s_map[e - seg];
+                            const int k = e - s_start[l];
+                            const int cd = s_src[l];
                             a.xmj[base + e] = cd >= 0 ? a.pp[cd + k] : a.xm[-1 - cd + k];
                             if (a.src) a.src[base + e] = cd >= 0 ? -(1 + cd + k) : -1 - cd + k;
                         }
-                        wave_sync_lds();
+                        __syncthreads();
                     }
                 }
                 len += e_tot;
@@ -769,30 +842,45 @@ __global__ void __launch_bounds__(64 * kWalkWaves) k_walk(WalkArgs a)
             }
             if (over) break;
             maxf = max(maxf, nnext);
-            wave_sync_lds();
+            __syncthreads();
             cur ^= 1;
             ncur = nnext;
         }
         if (over) {
-            if (lane == 0) atomicOr(a.overflow, 1u);
+            if (tid == 0) atomicOr(a.overflow, 1u);
             len = 0;
         }
-        if (!WRITE && lane == 0) a.glen[g] = len;
-        wave_sync_lds();
+        if (!WRITE && tid == 0) a.glen[g] = len;
+        __syncthreads();
     }
-    if (!WRITE && lane == 0 && maxf > 0) atomicMax(a.max_frontier, (unsigned)maxf);
+    if (!WRITE && tid == 0 && maxf > 0) atomicMax(a.max_frontier, (unsigned)maxf);
 }
 
-__global__ void k_tail_zero(long long *p) { *p = 0; }
+template <bool WRITE, int FCAP>
+void launch_walk(const WalkArgs &a, int num_cu, hipStream_t s)
+{
+    // resident workgroups: FCAP's two buffers of LDS each
+    const int per_cu = FCAP > kWalkFrontier / 2 ? 4 : 8;
+    hipLaunchKernelGGL((k_walk<WRITE, FCAP>), dim3(std::min(a.n_groups, per_cu * num_cu)),
+                       dim3(64 * kWalkWaves), 0, s, a);
+}
 
+// The walked groups' items, on the device and in pinned host memory, with the
+// status words and the number of entries.
 __global__ void __launch_bounds__(256) k_items_j(int n_groups, const long long *__restrict__ goff,
                                                  const long long *__restrict__ glen,
-                                                 pgh_item *items)
+                                                 const unsigned *__restrict__ w, pgh_item *items,
+                                                 pgh_item *host_items, TreeHostPage *page)
 {
     const int g = blockIdx.x * 256 + threadIdx.x;
+    if (g < 16) page->word[g] = w[g];
+    if (g == 0) page->entries = goff[n_groups];
     if (g >= n_groups) return;
-    items[g].j_off = (int)goff[g];
-    items[g].n_j = (int)glen[g];
+    pgh_item it = items[g];
+    it.j_off = (int)goff[g];
+    it.n_j = (int)glen[g];
+    items[g] = it;
+    host_items[g] = it;
 }
 
 int blocks_of(long long n, int per) { return (int)std::max(1LL, (n + per - 1) / per); }
@@ -858,9 +946,11 @@ void tree_release(TreeState &t)
 {
     void *ps[] = {t.key, t.key_in, t.perm, t.iota, t.xs, t.ys, t.zs, t.ms, t.mark, t.xin, t.inv, t.res,
                   t.begin, t.count, t.level, t.first_child, t.n_child, t.parent, t.nc, t.mom, t.com, t.pp, t.groups, t.glo, t.ghi, t.glen, t.goff,
-                  t.items, t.xmj, t.src, t.tmp, t.word, t.count_out, t.rc2, t.lvl,
+                  t.items, t.xmj, t.src, t.tmp, t.word, t.count_out, t.lvl,
                   t.xm, t.nrec};
     for (void *p : ps) (void)hipFree(p);
+    (void)hipHostFree(t.page);
+    (void)hipHostFree(t.host_items);
     t = TreeState();
 }
 
@@ -877,13 +967,10 @@ int tree_build(TreeState &t, int n, const float *x, const float *y, const float 
     t.n_entries = t.interactions = 0;
     std::fill(t.level_off, t.level_off + kTreeMaxLevel + 2, 0);
     std::fill(t.frame, t.frame + 5, 0.f);
-    t.host_items.clear();
-    if (!t.word) {
-        TREE_ALLOC(hipMalloc((void **)&t.word, 16 * sizeof(unsigned)) == hipSuccess);
-        TREE_ALLOC(hipMalloc((void **)&t.count_out, sizeof(int)) == hipSuccess);
-        TREE_ALLOC(hipMalloc((void **)&t.rc2, (kTreeMaxLevel + 1) * sizeof(float)) == hipSuccess);
-        TREE_ALLOC(hipMalloc((void **)&t.lvl, kLvl * sizeof(int)) == hipSuccess);
-    }
+    TREE_ALLOC(t.word || hipMalloc((void **)&t.word, 16 * sizeof(unsigned)) == hipSuccess);
+    TREE_ALLOC(t.count_out || hipMalloc((void **)&t.count_out, sizeof(int)) == hipSuccess);
+    TREE_ALLOC(t.lvl || hipMalloc((void **)&t.lvl, kLvl * sizeof(int)) == hipSuccess);
+    TREE_ALLOC(t.page || hipHostMalloc(&t.page, sizeof(TreeHostPage)) == hipSuccess);
     if (n == 0) {
         t.built = 1;
         return PGH_OK;
@@ -912,9 +999,12 @@ int tree_build(TreeState &t, int n, const float *x, const float *y, const float 
     hipLaunchKernelGGL(k_frame, dim3(std::min(blocks_of(n, 256), num_cu)), dim3(256), 0, s, n,
                        x, y, z, t.word);
     TREE_HIP(hipGetLastError());
-    unsigned wv[6];
-    TREE_HIP(hipMemcpyAsync(wv, t.word, sizeof wv, hipMemcpyDeviceToHost, s));
+    TreeHostPage *page = static_cast<TreeHostPage *>(t.page);
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, t.word, (const int *)nullptr,
+                       (const int *)nullptr, page);
+    TREE_HIP(hipGetLastError());
     TREE_HIP(hipStreamSynchronize(s));
+    const unsigned *wv = page->word;
     float lo[3], hi[3], ext = 0.f;
     for (int a = 0; a < 3; ++a) {
         lo[a] = float_of_ord(wv[a]);
@@ -952,13 +1042,15 @@ int tree_build(TreeState &t, int n, const float *x, const float *y, const float 
                    grow(&t.goff, &dummy, cap + 1) && grow(&t.items, &dummy, cap));
         t.group_cap = (int)cap;
     }
-    // per level: children per node, chunk sums, child bounds (7 per node)
-    const long long nc_need = 8LL * (n + 1) + kSplitBlocks + 1;
+    // the ranks' masks, the chunks' counts per level, the levels' sizes
+    const long long chunks = blocks_of(n, kNodeChunk);
+    const long long nc_need = n + (kLevels + 1) * (chunks + 1);
     if (t.nc_cap < nc_need) {
         long long dummy = 0;
-        const long long cap = 8LL * (std::max(n, 1024) + 1) + kSplitBlocks + 1;
-        TREE_ALLOC(grow(&t.nc, &dummy, cap));
-        t.nc_cap = cap;
+        const long long cap = std::max(n, 1024);
+        const long long words = cap + (kLevels + 1) * (blocks_of(cap, kNodeChunk) + 1LL);
+        TREE_ALLOC(grow(&t.nc, &dummy, words));
+        t.nc_cap = words;
     }
     long long want = std::max<long long>(2LL * n + 64, 4096);
     for (;;) {
@@ -978,32 +1070,30 @@ int tree_build(TreeState &t, int n, const float *x, const float *y, const float 
         }
         const int cap = t.node_cap;
         hipLaunchKernelGGL(k_init_words, dim3(1), dim3(64), 0, s, t.word);
-        hipLaunchKernelGGL(k_root, dim3(1), dim3(1), 0, s, n, t.begin, t.count, t.level, t.parent,
-                           t.lvl);
-        TREE_HIP(hipGetLastError());
         // level L has at most min(n, 8^L) nodes
         auto level_bound = [&](int L) {
             long long b = 1;
             for (int k = 0; k < L && b < n; ++k) b *= 8;
             return (int)std::min<long long>(b, n);
         };
-        int *cnt = t.nc, *bsum = t.nc + (n + 1), *bnd = bsum + kSplitBlocks + 1;
-        for (int L = 0; L <= kTreeMaxLevel; ++L) {
-            hipLaunchKernelGGL(k_split_count, dim3(kSplitBlocks), dim3(256), 0, s, L, n_leaf,
-                               t.lvl, t.begin, t.count, t.key, cnt, bnd, bsum, t.word);
-            hipLaunchKernelGGL(k_split_scan, dim3(1), dim3(256), 0, s, L, cap, t.lvl, bsum,
-                               t.word);
-            hipLaunchKernelGGL(k_split_write, dim3(kSplitBlocks), dim3(256), 0, s, L, t.lvl, cnt,
-                               bnd, bsum, t.begin, t.count, t.level, t.first_child, t.n_child,
-                               t.parent, t.word);
-            TREE_HIP(hipGetLastError());
-        }
+        const int gnodes = std::min(blocks_of(cap, 256), 16 * num_cu);
+        unsigned *mask = (unsigned *)t.nc;
+        int *sums = t.nc + n, *total = sums + (kLevels + 1) * chunks;
+        const dim3 by_chunk(blocks_of(chunks, 4));
+        hipLaunchKernelGGL(k_node_mask, by_chunk, dim3(256), 0, s, n, n_leaf, t.key, mask,
+                           (int)chunks, sums);
+        hipLaunchKernelGGL(k_node_scan, dim3(kLevels + 1), dim3(256), 0, s, (int)chunks, sums, total);
+        hipLaunchKernelGGL(k_node_write, by_chunk, dim3(256), 0, s, n, mask, (int)chunks, sums,
+                           total, cap, t.begin, t.level, t.first_child, t.n_child, t.parent, t.lvl,
+                           t.word);
+        hipLaunchKernelGGL(k_node_ends, dim3(gnodes), dim3(256), 0, s, n, t.key, t.lvl, t.word,
+                           t.begin, t.level, t.first_child, t.parent, t.count, t.n_child);
+        TREE_HIP(hipGetLastError());
         for (int L = kTreeMaxLevel; L >= 0; --L) {
             const int grid = std::min(blocks_of(level_bound(L), 32), 16 * num_cu);
             hipLaunchKernelGGL(k_moments, dim3(grid), dim3(256), 0, s, L, t.lvl, t.word, t.begin,
                                t.count, t.first_child, t.n_child, t.xm, t.mom);
         }
-        const int gnodes = std::min(blocks_of(cap, 256), 16 * num_cu);
         hipLaunchKernelGGL(k_pseudo, dim3(gnodes), dim3(256), 0, s, t.lvl, t.word, t.mom, t.quad,
                            t.pp, t.com);
         hipLaunchKernelGGL(k_pack_nodes, dim3(gnodes), dim3(256), 0, s, t.lvl, t.word, t.begin,
@@ -1020,12 +1110,12 @@ int tree_build(TreeState &t, int n, const float *x, const float *y, const float 
                            t.ghi, t.items);
         TREE_HIP(hipGetLastError());
         // the one wait of the build: sizes and flags
-        int lv[kLvl];
-        unsigned wv2[16];
-        TREE_HIP(hipMemcpyAsync(lv, t.lvl, sizeof lv, hipMemcpyDeviceToHost, s));
-        TREE_HIP(hipMemcpyAsync(wv2, t.word, sizeof wv2, hipMemcpyDeviceToHost, s));
-        TREE_HIP(hipMemcpyAsync(&t.n_groups, t.count_out, sizeof(int), hipMemcpyDeviceToHost, s));
+        hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, t.word, t.lvl, t.count_out, page);
+        TREE_HIP(hipGetLastError());
         TREE_HIP(hipStreamSynchronize(s));
+        const int *lv = page->lvl;
+        const unsigned *wv2 = page->word;
+        t.n_groups = page->n_groups;
         if (wv2[kWordOverflow]) {
             want = 2LL * cap;
             continue;
@@ -1053,20 +1143,17 @@ int tree_walk(TreeState &t, float theta, int record_src, int num_cu, hipStream_t
     t.theta = theta;
     t.record_src = record_src ? 1 : 0;
     t.n_entries = t.interactions = 0;
-    t.host_items.clear();
     if (t.n_groups == 0) {
         t.walked = 1;
         return PGH_OK;
     }
     // (l_L / theta)^2 per level, rounded once from double
-    float rc2[kTreeMaxLevel + 1];
+    WalkArgs a{};
     for (int L = 0; L <= kTreeMaxLevel; ++L) {
         const double l = std::ldexp((double)t.frame[3], -L);
-        rc2[L] = theta > 0.f ? (float)((l / theta) * (l / theta)) : INFINITY;
+        a.rc2[L] = theta > 0.f ? (float)((l / theta) * (l / theta)) : INFINITY;
     }
-    TREE_HIP(hipMemcpyAsync(t.rc2, rc2, sizeof rc2, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_init_words, dim3(1), dim3(64), 0, s, t.word);
-    WalkArgs a{};
     a.n_groups = t.n_groups;
     a.groups = t.groups;
     a.glo = t.glo;
@@ -1075,7 +1162,6 @@ int tree_walk(TreeState &t, float theta, int record_src, int num_cu, hipStream_t
     a.com = t.com;
     a.pp = t.pp;
     a.npp = t.quad ? 3 : 1;
-    a.rc2 = t.rc2;
     a.xm = t.xm;
     a.glen = t.glen;
     a.goff = t.goff;
@@ -1085,33 +1171,34 @@ int tree_walk(TreeState &t, float theta, int record_src, int num_cu, hipStream_t
     // come back to the host in one wait.  It runs with the small frontier
     // (LDS for 2 walking waves per SIMD); if a group's frontier outgrew it,
     // it runs again with the large one (1 per SIMD).
-    const int grid_small = std::min(blocks_of(t.n_groups, kWalkWaves), 4 * num_cu);
-    const int grid_large = std::min(blocks_of(t.n_groups, kWalkWaves), 2 * num_cu);
+    TreeHostPage *page = static_cast<TreeHostPage *>(t.page);
     bool large = false;
     unsigned over = 0, maxf = 0;
     long long total = 0;
-    t.host_items.resize(t.n_groups);
+    if (t.n_groups > t.host_items_cap) {
+        const int cap = t.n_groups + std::min(t.n_groups / 4, INT_MAX - t.n_groups);
+        (void)hipHostFree(t.host_items);
+        t.host_items = nullptr;
+        t.host_items_cap = 0;
+        TREE_ALLOC(hipHostMalloc((void **)&t.host_items, sizeof(pgh_item) * (size_t)cap) ==
+                   hipSuccess);
+        t.host_items_cap = cap;
+    }
     for (;;) {
         if (large)
-            hipLaunchKernelGGL((k_walk<false, kWalkFrontier>), dim3(grid_large),
-                               dim3(64 * kWalkWaves), 0, s, a);
+            launch_walk<false, kWalkFrontier>(a, num_cu, s);
         else
-            hipLaunchKernelGGL((k_walk<false, kWalkFrontier / 2>), dim3(grid_small),
-                               dim3(64 * kWalkWaves), 0, s, a);
-        TREE_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_tail_zero, dim3(1), dim3(1), 0, s, t.glen + t.n_groups);
+            launch_walk<false, kWalkFrontier / 2>(a, num_cu, s);
         TREE_HIP(hipGetLastError());
         size_t tb = t.tmp_bytes;
         TREE_HIP(hipcub::DeviceScan::ExclusiveSum(t.tmp, tb, t.glen, t.goff, t.n_groups + 1, s));
         hipLaunchKernelGGL(k_items_j, dim3(blocks_of(t.n_groups, 256)), dim3(256), 0, s,
-                           t.n_groups, t.goff, t.glen, t.items);
+                           t.n_groups, t.goff, t.glen, t.word, t.items, t.host_items, page);
         TREE_HIP(hipGetLastError());
-        TREE_HIP(hipMemcpyAsync(&over, t.word + 7, sizeof over, hipMemcpyDeviceToHost, s));
-        TREE_HIP(hipMemcpyAsync(&maxf, t.word + 8, sizeof maxf, hipMemcpyDeviceToHost, s));
-        TREE_HIP(hipMemcpyAsync(&total, t.goff + t.n_groups, sizeof total, hipMemcpyDeviceToHost, s));
-        TREE_HIP(hipMemcpyAsync(t.host_items.data(), t.items, sizeof(pgh_item) * t.n_groups,
-                                hipMemcpyDeviceToHost, s));
         TREE_HIP(hipStreamSynchronize(s));
+        over = page->word[7];
+        maxf = page->word[8];
+        total = page->entries;
         if (!over || large) break;
         large = true;
         hipLaunchKernelGGL(k_init_words, dim3(1), dim3(64), 0, s, t.word);
@@ -1141,14 +1228,13 @@ int tree_walk(TreeState &t, float theta, int record_src, int num_cu, hipStream_t
     a.xmj = t.xmj;
     a.src = record_src ? t.src : nullptr;
     if (large)
-        hipLaunchKernelGGL((k_walk<true, kWalkFrontier>), dim3(grid_large),
-                           dim3(64 * kWalkWaves), 0, s, a);
+        launch_walk<true, kWalkFrontier>(a, num_cu, s);
     else
-        hipLaunchKernelGGL((k_walk<true, kWalkFrontier / 2>), dim3(grid_small),
-                           dim3(64 * kWalkWaves), 0, s, a);
+        launch_walk<true, kWalkFrontier / 2>(a, num_cu, s);
     TREE_HIP(hipGetLastError());
     long long inter = 0;
-    for (const pgh_item &it : t.host_items) inter += (long long)it.n_i * it.n_j;
+    for (int g = 0; g < t.n_groups; ++g)
+        inter += (long long)t.host_items[g].n_i * t.host_items[g].n_j;
     t.n_entries = total;
     t.interactions = inter;
     t.walked = 1;

@@ -620,3 +620,48 @@ def test_handle_errors(pgh, ctx):
     t2 = other.tree().build(*d).walk(0.75)
     assert t2.stats()["walked"] == 1
     other.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 9, 255, 256, 257, 1024, 1279, 4099])
+@pytest.mark.parametrize("n_leaf", [1, 8, 64])
+def test_nodes_at_the_edges_of_the_chunks(pgh, ctx, n, n_leaf):
+    """The node arrays, built from all levels at once by chunks of 256 ranks,
+    with runs of coincident particles (chains of single children) across the
+    chunks' edges; integers, exact."""
+    x, y, z = (v.copy() for v in synth.plummer(n, 77))
+    for at, k in ((250, 12), (1000, 70), (1270, 9)):
+        for v in (x, y, z):
+            v[at:at + k] = v[min(at, n - 1)]
+    m = synth.equal_masses(n)
+    t, _ = _build(ctx, x, y, z, m, n_leaf, 64)
+    o = oracle.tree_build(x, y, z, m, n_leaf=n_leaf)
+    st = t.stats()
+    assert st["n_nodes"] == o.n_nodes and st["n_leaves"] == int((o.n_child == 0).sum())
+    assert st["depth"] == o.level.max()
+    assert st["max_level_nodes"] == np.bincount(o.level).max()
+    for f, ref in (("node_begin", o.begin), ("node_count", o.count), ("node_level", o.level),
+                   ("node_first_child", o.first_child), ("node_n_child", o.n_child),
+                   ("node_parent", o.parent)):
+        assert np.array_equal(t.get(f), ref), f
+    assert np.array_equal(t.get("groups"), o.find_groups(64))
+    t.walk(0.6)
+    st = t.stats()
+    items = t.get("items")
+    assert st["n_entries"] == items[:, 3].sum() and items[:, 1].sum() == n
+
+
+@pytest.mark.parametrize("n", [50, 3000, 40000])
+def test_small_trees_plans_are_the_same_on_host_and_device(pgh, ctx, n):
+    """The tree's own cut of its lists into tasks, expanded on the device and
+    made on the host: the same tasks, so the same force bit for bit."""
+    x, y, z = synth.plummer(n, 91)
+    m = synth.equal_masses(n)
+    ctx.set_eps_to_all(1.0 / 256)
+    t, _ = _build(ctx, x, y, z, m, 8, 256)
+    out = []
+    for on in (True, False):
+        ctx.set_plan_expansion(on)
+        t.walk(0.75)
+        out.append(np.stack(to_host(*t.newton())))
+    ctx.set_plan_expansion(True)
+    assert np.array_equal(*out)
