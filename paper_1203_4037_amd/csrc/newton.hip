@@ -65,9 +65,10 @@ hipError_t launch_pack_j(int n, const float *x, const float *y, const float *z, 
 // turn took 16.6 us for 27 shares of 20011 particles).
 __global__ void __launch_bounds__(256) k_combine_split(int n, int S, const float *__restrict__ part,
                                                        float *ax, float *ay, float *az, float *phi,
-                                                       const int *dense)
+                                                       const int *dense, const int *same)
 {
     if (dense && *dense == 0) return;
+    if (same && same_set(same)) return;
     const int c = blockIdx.y;
     float *const out = c == 0 ? ax : c == 1 ? ay : c == 2 ? az : phi;
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -88,11 +89,12 @@ __global__ void __launch_bounds__(256) k_combine_split(int n, int S, const float
 }
 
 hipError_t launch_combine_split(int n, int S, const float *part, float *ax, float *ay, float *az,
-                                float *phi, hipStream_t s, const int *dense)
+                                float *phi, hipStream_t s, const int *dense,
+                                const int *same)
 {
     if (n <= 0 || S <= 1) return hipSuccess;
     hipLaunchKernelGGL(k_combine_split, dim3((n + 255) / 256, phi ? 4 : 3), dim3(256), 0, s, n, S,
-                       part, ax, ay, az, phi, dense);
+                       part, ax, ay, az, phi, dense, same);
     return hipGetLastError();
 }
 
@@ -130,6 +132,7 @@ namespace {
 template <int KI, int JT, int U, bool RCP, bool REFINE, bool GUARD, bool PHI>
 __global__ void __launch_bounds__(256) k_newton_allpairs(NewtonArgs a)
 {
+    if (a.same && same_set(a.same)) return;
     static_assert(JT % 256 == 0 || JT == 64, "a tile is 64 records or whole workgroup rounds");
     constexpr int PER = JT >= 256 ? JT / 256 : 1;  // records each thread loads per tile
     __shared__ float4 tile[2][JT];
@@ -267,6 +270,7 @@ __global__ void __launch_bounds__(256) k_newton_allpairs(NewtonArgs a)
 template <int TI, int NT, bool REFINE, bool GUARD, bool PHI>
 __global__ void __launch_bounds__(NT) k_newton_rows(NewtonArgs a)
 {
+    if (a.same && same_set(a.same)) return;
     constexpr int V = 4 * TI;   // sums per workgroup
     constexpr int W = NT / 64;
     __shared__ float red[W][V];
@@ -411,8 +415,11 @@ const NewtonVariant kNewtonVariants[] = {
     {"ki=2 jt=256 u=4 rcp", 2, 256, &NewtonSet<2, 256, 4, true>::get},
     {"ki=4 jt=256 u=2 rcp", 4, 256, &NewtonSet<4, 256, 2, true>::get},
     {"rows", 0, 64, nullptr},
+    // each pair once (newton_mutual.hip) where the i-particles are the
+    // j-particles, else the rows kernel
+    {"mutual", 0, 64, nullptr},
 };
-constexpr int kRowsVariant = 8;
+constexpr int kRowsVariant = 8, kMutualVariant = 9;
 constexpr int kNumNewtonVariants = sizeof(kNewtonVariants) / sizeof(kNewtonVariants[0]);
 
 }  // namespace
@@ -444,6 +451,7 @@ int newton_allpairs_default(int ni, int nj, int num_cu)
 }
 
 int newton_allpairs_rows() { return kRowsVariant; }
+int newton_allpairs_mutual() { return kMutualVariant; }
 
 int newton_allpairs_split(int ni, int nj, int variant, size_t part_cap)
 {
@@ -469,14 +477,16 @@ hipError_t launch_newton_allpairs(const NewtonArgs &a0, int variant, bool refine
                            dim3((a.ni + r.ti - 1) / r.ti, S), dim3(r.nt), 0, s, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || S == 1) return e;
-        return launch_combine_split(a.ni, S, a.part, a0.ax, a0.ay, a0.az, a0.phi, s);
+        return launch_combine_split(a.ni, S, a.part, a0.ax, a0.ay, a0.az, a0.phi, s, nullptr,
+                                    a.same);
     }
     const int per_block = 256 * v.ki;
     const dim3 grid((a.ni + per_block - 1) / per_block, S);
     hipLaunchKernelGGL(v.get(refine, guard, a.phi != nullptr), grid, dim3(256), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || S == 1) return e;
-    return launch_combine_split(a.ni, S, a.part, a0.ax, a0.ay, a0.az, a0.phi, s);
+    return launch_combine_split(a.ni, S, a.part, a0.ax, a0.ay, a0.az, a0.phi, s, nullptr,
+                                    a.same);
 }
 
 }  // namespace pgh

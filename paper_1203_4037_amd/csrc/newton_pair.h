@@ -4,7 +4,16 @@
 
 #include <hip/hip_runtime.h>
 
+#include "pgh_internal.h"
+
 namespace pgh {
+
+// Whether the words that k_same_set wrote (newton_mutual.hip) say that a
+// launch's i-particles are its j-particles.
+__device__ __forceinline__ bool same_set(const int *same)
+{
+    return __all(same[threadIdx.x & (kSameWords - 1)]);
+}
 
 // 1/q from the transcendental unit (v_rcp_f32), which issues alongside the
 // VALU; with GUARD a zero q gives 0 instead of inf.

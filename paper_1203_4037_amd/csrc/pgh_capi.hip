@@ -101,6 +101,7 @@ struct pgh_ctx {
     float2 *tab = nullptr;  // device, 2^kMaxTableBits entries
     float *gcopy = nullptr;  // device, kGradCopies x 2^(kMaxAdjTableBits+1): table-adjoint scratch
     int *word = nullptr;     // device, one word: k_table_density's answer
+    int *same = nullptr;     // device, kSameWords words: k_same_set's answer
     float2 *ptab = nullptr;  // device, potential table on the force table's bins
     int pot_set = 0;         // ptab matches the current force table
     int variant[4] = {-1, -1, -1, -1};
@@ -250,6 +251,12 @@ int ensure_scratch(pgh_ctx *c, float4 **buf, size_t *cap, size_t n)
 
 // Upper bound of the partial-sum buffer of j-split launches (floats).
 constexpr size_t kMaxSplitFloats = (size_t)64 << 20;
+// and of the mutual kernel's sums (1 GiB), a strip of the set at a time
+constexpr size_t kMaxMutualFloats = (size_t)256 << 20;
+// From here on the mutual kernel pays (N = 32768: 326 us each pair twice, 327
+// mutual; 40000: 494, 456), and looking whether the sets are the same costs a
+// call in which they aren't 8 us of 494.
+constexpr int kMutualMin = 40000;
 
 // Scratch of the allocation-free entry point (pgh_calc_newton_noalloc): the
 // partial sums of its j-split, in a device array of fixed size that each GPU
@@ -289,6 +296,19 @@ int ensure_part(pgh_ctx *c, size_t n)
     c->part = nb;
     c->part_cap = n;
     return PGH_OK;
+}
+
+// The same where a launch can do without: false if the buffer is too small and
+// cannot grow (no memory, or the stream is being captured).
+bool part_ready(pgh_ctx *c, size_t n)
+{
+    if (n <= c->part_cap) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+        return false;
+    if (ensure_part(c, n) == PGH_OK) return true;
+    (void)hipGetLastError();  // not the launches' error
+    return false;
 }
 
 int zero_outputs(pgh_ctx *c, int n, float *a, float *b, float *d, float *e)
@@ -599,10 +619,15 @@ int pgh_open(pgh_ctx **out, int device, void *hip_stream)
     e = hipMalloc((void **)&c->tab, sizeof(float2) << kMaxTableBits);
     const size_t gcopy_bytes = (sizeof(float2) << kMaxAdjTableBits) * kGradCopies;
     if (e == hipSuccess) e = hipMalloc((void **)&c->gcopy, gcopy_bytes);
-    // the potential table, and behind it the word of k_table_density
+    // the potential table, and behind it the words of k_table_density and
+    // k_same_set
     if (e == hipSuccess)
-        e = hipMalloc((void **)&c->ptab, (sizeof(float2) << kMaxPotTableBits) + sizeof(int));
-    if (e == hipSuccess) c->word = (int *)(c->ptab + (1 << kMaxPotTableBits));
+        e = hipMalloc((void **)&c->ptab,
+                      (sizeof(float2) << kMaxPotTableBits) + (1 + kSameWords) * sizeof(int));
+    if (e == hipSuccess) {
+        c->word = (int *)(c->ptab + (1 << kMaxPotTableBits));
+        c->same = c->word + 1;
+    }
     if (e != hipSuccess) {
         g_open_error = std::string("hipMalloc(table): ") + hipGetErrorString(e);
         (void)hipFree(c->tab);
@@ -754,10 +779,21 @@ int pgh_calc_newton(pgh_ctx *c, int ni, const float *xi, const float *yi, const 
         return fail(c, PGH_EINVAL, "NULL i-particle or output array");
     DeviceGuard g(c->device);
     if (c->nj == 0) return zero_outputs(c, ni, ax, ay, az, phi);
-    NewtonArgs a{ni, xi, yi, zi, eps2_i, c->eps2_all, c->nj, c->jmem, ax, ay, az, phi, 0, nullptr};
+    NewtonArgs a{ni, xi, yi, zi, eps2_i, c->eps2_all, c->nj, c->jmem, ax, ay, az, phi, 0, nullptr,
+                 nullptr};
     const bool guard = (eps2_i == nullptr) && !(c->eps2_all > 0.f);
     int v = c->variant[PGH_FAMILY_NEWTON_ALLPAIRS];
+    const bool mutual = v == newton_allpairs_mutual() || (v < 0 && ni >= kMutualMin);
     if (v < 0) v = newton_allpairs_default(ni, c->nj, c->num_cu);
+    if (mutual && ni == c->nj && !eps2_i) {
+        const MutualShape m = mutual_shape(ni, kMaxMutualFloats);
+        if (m.strip > 0 && part_ready(c, m.floats)) {
+            PGH_HIP(c, launch_same_set(ni, xi, yi, zi, c->jmem, c->same, c->stream));
+            PGH_HIP(c, launch_newton_mutual(m, ni, c->jmem, c->eps2_all, c->refine != 0, guard, ax,
+                                            ay, az, phi, c->part, c->same, c->stream));
+            a.same = c->same;
+        }
+    }
     const int S = newton_allpairs_split(ni, c->nj, v, kMaxSplitFloats);
     if (S > 1) {
         int st = ensure_part(c, (size_t)S * 4 * ni);
@@ -781,7 +817,8 @@ int pgh_calc_newton_noalloc(pgh_ctx *c, int ni, const float *xi, const float *yi
         return fail(c, PGH_ESTATE, "the device's scratch array could not be located at pgh_open");
     DeviceGuard g(c->device);
     if (c->nj == 0) return zero_outputs(c, ni, ax, ay, az, phi);
-    NewtonArgs a{ni, xi, yi, zi, eps2_i, c->eps2_all, c->nj, c->jmem, ax, ay, az, phi, 0, nullptr};
+    NewtonArgs a{ni, xi, yi, zi, eps2_i, c->eps2_all, c->nj, c->jmem, ax, ay, az, phi, 0, nullptr,
+                 nullptr};
     const bool guard = (eps2_i == nullptr) && !(c->eps2_all > 0.f);
     int v = c->variant[PGH_FAMILY_NEWTON_ALLPAIRS];
     if (v < 0) {

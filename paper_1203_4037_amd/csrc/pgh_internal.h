@@ -20,6 +20,7 @@ namespace pgh {
 constexpr int kMaxTableBits = 14;
 constexpr int kMaxPotTableBits = 13;
 constexpr int kMaxAdjTableBits = 13;
+constexpr int kSameWords = 64;  // words of k_same_set, one a lane of a wave
 
 // Arguments of the all-pairs Newton kernels.  jmem holds (x, y, z, m)
 // records; eps2i may be null (then eps2_all applies to every i).
@@ -32,7 +33,24 @@ struct NewtonArgs {
     float *ax, *ay, *az, *phi;
     int jchunk;   // j-particles per workgroup share (set by the launcher)
     float *part;  // partial sums [S][4][ni] when the j-range is split
+    // not NULL: return at once where the sets are the same (k_same_set)
+    const int *same;
 };
+
+// The launch of the mutual kernel on a set of n (newton_mutual.hip).
+struct MutualShape {
+    int block, blocks;  // l-particles of a block, blocks of the set
+    int chunk;          // k-particles of a workgroup
+    int strip;          // blocks of a launch
+    size_t floats;      // scratch floats of a launch
+};
+// (strip = 0: not even one block's sums fit part_cap floats)
+MutualShape mutual_shape(int n, size_t part_cap);
+hipError_t launch_same_set(int n, const float *x, const float *y, const float *z,
+                           const float4 *jmem, int *same, hipStream_t s);
+hipError_t launch_newton_mutual(const MutualShape &m, int n, const float4 *jmem, float eps2,
+                                bool refine, bool guard, float *ax, float *ay, float *az,
+                                float *phi, float *part, const int *same, hipStream_t s);
 
 // Arguments of the all-pairs table-force kernels.
 struct TableArgs {
@@ -160,7 +178,8 @@ hipError_t allow_dynamic_lds(const void *kernel, size_t bytes);
 int newton_allpairs_variants();
 const char *newton_allpairs_variant_name(int v);
 int newton_allpairs_default(int ni, int nj, int num_cu);
-int newton_allpairs_rows();  // the variant that needs no j-split for large i-sets
+int newton_allpairs_rows();
+int newton_allpairs_mutual();  // the variant that needs no j-split for large i-sets
 int newton_allpairs_split(int ni, int nj, int variant, size_t part_cap);
 hipError_t launch_newton_allpairs(const NewtonArgs &a, int variant, bool refine, bool guard,
                                   int S, hipStream_t s);

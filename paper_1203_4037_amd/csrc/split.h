@@ -38,8 +38,10 @@ __device__ __forceinline__ void set_tile_prio(int rem, int ntiles)
 }
 
 int split_count(int ni, int nj, int ki, int jt, int target_waves, size_t part_cap);
-// (with a word `dense`: only where it is not zero)
+// (with a word `dense`: only where it is not zero; with the words of k_same_set:
+// only where the sets differ)
 hipError_t launch_combine_split(int n, int S, const float *part, float *ax, float *ay, float *az,
-                                float *phi, hipStream_t s, const int *dense = nullptr);
+                                float *phi, hipStream_t s, const int *dense = nullptr,
+                                const int *same = nullptr);
 
 }  // namespace pgh

@@ -244,3 +244,62 @@ def test_rows_kernel_shapes(pgh, ctx, ni, nj, refine, zero_eps, with_phi):
         _check(a[:, idx], phi[idx] if with_phi else None, ref, f"rows {ni} x {nj}")
     else:  # the coincident pair alone: nothing
         assert np.all(a == 0) and np.all(phi == 0)
+
+
+@pytest.mark.parametrize("n", [1, 2, 65, 191, 3072, 3073, 6147, 9409, 524288])
+@pytest.mark.parametrize("refine,zero_eps,with_phi", [(0, False, True), (1, False, True),
+                                                      (0, True, False), (1, True, True)])
+def test_mutual_kernel(pgh, ctx, n, refine, zero_eps, with_phi):
+    """Each pair once: sets of one block and less, at the edges of blocks and of
+    chunks, and of more blocks than a launch's scratch memory holds; masses of
+    a wide range, coincident particles.  With one coordinate changed the
+    i-particles are another set and take the rows kernel, bit for bit."""
+    if n == 524288 and (refine or zero_eps):
+        pytest.skip("the strips do not depend on these")
+    x, y, z = synth.plummer(n, 700 + n)
+    if n > 64:
+        for v in (x, y, z):
+            v[n - 3] = v[n // 2] = v[1]
+    rng = np.random.default_rng(n)
+    m = (10.0 ** rng.uniform(-3, 0, n)).astype(np.float32) / np.float32(n)
+    ctx.set_rsqrt_refine(refine)
+    names = [pgh.pgh_variant_name(0, v) for v in range(pgh.pgh_variant_count(0))]
+    fam = pgh.PGH_FAMILY_NEWTON_ALLPAIRS
+    ctx.set_variant(fam, names.index("mutual"))
+    eps = 0.0 if zero_eps else 1.0 / 64
+    idx = np.unique(np.linspace(0, n - 1, 40).astype(int).tolist() + [min(1, n - 1), max(0, n - 3)])
+    for _ in range(2):  # the scratch memory of the first call holds its sums
+        a, phi = _gpu_newton(ctx, x, y, z, x, y, z, m, eps=eps, with_phi=with_phi)
+        ref = oracle.newton(x[idx], y[idx], z[idx], np.full(idx.size, eps * eps, np.float32),
+                            x, y, z, m)
+        if n > 1:
+            _check(a[:, idx], phi[idx] if with_phi else None, ref, f"mutual {n}")
+        else:
+            assert np.all(a == 0)
+    assert np.isfinite(a).all()
+    xi = x.copy()
+    xi[n - 1] += np.float32(0.25)
+    out = []
+    for v in ("mutual", "rows"):
+        ctx.set_variant(fam, names.index(v))
+        out.append(_gpu_newton(ctx, xi, y, z, x, y, z, m, eps=eps, with_phi=with_phi))
+    assert np.array_equal(out[0][0], out[1][0])
+    if with_phi:
+        assert np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("unit", [1e-14, 1e13])
+def test_mutual_kernel_far_from_unit_scale(pgh, ctx, unit):
+    """Coordinates whose distances cubed leave the range of FP32 where the
+    masses bring the force back into it: as the rows kernel."""
+    n = 4000
+    x, y, z = (np.float32(unit) * v for v in synth.plummer(n, 12))
+    m = np.full(n, 1e-22 if unit < 1 else 1e20, np.float32)
+    names = [pgh.pgh_variant_name(0, v) for v in range(pgh.pgh_variant_count(0))]
+    out = []
+    for v in ("mutual", "rows"):
+        ctx.set_variant(pgh.PGH_FAMILY_NEWTON_ALLPAIRS, names.index(v))
+        out.append(_gpu_newton(ctx, x, y, z, x, y, z, m, eps=unit / 8))
+    assert np.isfinite(out[0][0]).all() and np.abs(out[1][0]).min() > 0
+    ea = rel_vec_err(out[0][0], out[1][0].astype(np.float64))
+    assert rms(ea) <= RMS_TOL and ea.max() <= MAX_TOL
