@@ -45,6 +45,7 @@ typedef const __attribute__((address_space(4))) f32x4 *ConstRecords;
 constexpr float kFarAway = 1.0e10f;
 constexpr int kLanes = 12;  // l-particles per lane
 constexpr int kWaves = 4;   // waves per workgroup
+constexpr int kBwdLanes = 8;  // l-particles per lane of the adjoint
 
 __global__ void __launch_bounds__(1024) k_same_set(int n, const unsigned *__restrict__ x,
                                                    const unsigned *__restrict__ y,
@@ -69,7 +70,8 @@ struct MutualArgs {
     const float4 *jmem;
     float eps2;
     int block0;  // the strip's first block
-    int chunk;   // k-particles per chunk, a divisor of the block
+    int chunk;   // k-particles per chunk, a divisor of the block, so that none
+                 // holds particles of two blocks, and a multiple of FRESH
     int chunks;  // chunks of the strip's first block
     float *lsum, *ksum;
     const int *same;
@@ -264,6 +266,164 @@ __global__ void __launch_bounds__(256) k_mutual_combine(MutualArgs a, int block,
     o[i] = sum;
 }
 
+// The adjoint of the force of a set on itself (adjoint.hip), each pair once: for
+// k, with d = r_l - r_k and e = m_l (w_k . d) - m_k (w_l . d),
+//   A += rho^3 w_l,  B += m_l rho^3,  C += rho^5 e d,  G += rho^3 (w_l . d),
+// and for l the same with k and l exchanged and -d, where e is the same.  34
+// operations and one root against 2 x 26 and two.  The mapping is
+// k_newton_mutual's, with eight l-particles per lane: 15 registers each.
+// Bound by FP32 issue at three waves a SIMD, 39 instructions per pair, two
+// thirds of them multiply-adds of three registers (3.5 cycles each here, 3.1
+// in the other kernel at eight waves): N = 65536 2402 -> 2052 us, 131072 9481
+// -> 8084, 50000 1485 -> 1222.
+template <bool REFINE>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3)))
+k_newton_mutual_bwd(MutualArgs a)
+{
+    constexpr int KL = kBwdLanes, W = kWaves, B = 64 * KL * W, G = 32, T = 2;
+    __shared__ float red[2][W][4 * G];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int block = a.block0 + blockIdx.y;
+    const int k0 = block * B + blockIdx.x * a.chunk;
+    if (k0 >= a.n) return;
+    const int k1 = min(k0 + a.chunk, a.n);
+    const int l0 = block * B + wave * 64 * KL + lane;
+    float lx[KL], ly[KL], lz[KL], lm[KL], lu[KL], lv[KL], lw[KL], s[KL][8];
+#pragma unroll
+    for (int r = 0; r < KL; ++r) {
+        const int l = l0 + 64 * r, at = min(l, a.n - 1);
+        float4 p = a.jmem[2 * (size_t)at], w = a.jmem[2 * (size_t)at + 1];
+        if (l >= a.n) {
+            p = make_float4(kFarAway, kFarAway, kFarAway, 0.f);
+            w = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        lx[r] = p.x, ly[r] = p.y, lz[r] = p.z, lm[r] = p.w;
+        lu[r] = w.x, lv[r] = w.y, lw[r] = w.z;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) s[r][c] = 0.f;
+    }
+    const ConstRecords rec = (ConstRecords)(unsigned long long)a.jmem;
+    struct Record {
+        f32x4 p, w;
+    };
+    // past the end the last record again, its mass and weight taken for zero
+    auto load = [&](int k) {
+        const size_t at = 2 * (size_t)min(k, a.n - 1);
+        return Record{rec[at], rec[at + 1]};
+    };
+    auto keep = [&](float v, int k) { return k < a.n ? v : 0.f; };
+    Record next[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) next[t] = load(k0 + t);
+
+    // the pair's terms of l (and the factors of those of k)
+    auto pair = [&](const Record &q, float km, float ku, float kv, float kw, int r, float dx,
+                    float dy, float dz, float r1, float &r3, float &wld, float &f) {
+        const float r2 = r1 * r1;
+        r3 = r2 * r1;
+        wld = lu[r] * dx;
+        wld = __builtin_fmaf(lv[r], dy, wld);
+        wld = __builtin_fmaf(lw[r], dz, wld);
+        float wkd = ku * dx;
+        wkd = __builtin_fmaf(kv, dy, wkd);
+        wkd = __builtin_fmaf(kw, dz, wkd);
+        f = r3 * r2 * __builtin_fmaf(lm[r], wkd, -km * wld);
+        s[r][0] = __builtin_fmaf(r3, ku, s[r][0]);
+        s[r][1] = __builtin_fmaf(r3, kv, s[r][1]);
+        s[r][2] = __builtin_fmaf(r3, kw, s[r][2]);
+        s[r][3] = __builtin_fmaf(km, r3, s[r][3]);
+        s[r][4] = __builtin_fmaf(-f, dx, s[r][4]);
+        s[r][5] = __builtin_fmaf(-f, dy, s[r][5]);
+        s[r][6] = __builtin_fmaf(-f, dz, s[r][6]);
+        s[r][7] = __builtin_fmaf(-r3, wkd, s[r][7]);
+    };
+    auto root = [&](float dx, float dy, float dz) {
+        float q = __builtin_fmaf(dx, dx, a.eps2);
+        q = __builtin_fmaf(dy, dy, q);
+        q = __builtin_fmaf(dz, dz, q);
+        const float y = __builtin_amdgcn_rsqf(q);
+        return REFINE ? y * __builtin_fmaf(-0.5f * q, y * y, 1.5f) : y;
+    };
+
+    if (k0 < (block + 1) * B) {
+        // of the block itself, for l only; l's own term is identically zero, but
+        // would enter A and B as +-m w / eps^3 and cancel only to rounding
+#pragma unroll 1
+        for (int k = k0; k < k1; k += T) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const Record q = next[t];
+                next[t] = load(k + T + t);
+                const float km = keep(q.p.w, k + t), ku = keep(q.w.x, k + t),
+                            kv = keep(q.w.y, k + t), kw = keep(q.w.z, k + t);
+#pragma unroll
+                for (int r = 0; r < KL; ++r) {
+                    const float dx = lx[r] - q.p.x, dy = ly[r] - q.p.y, dz = lz[r] - q.p.z;
+                    float r1 = root(dx, dy, dz), r3, wld, f;
+                    r1 = l0 + 64 * r == k + t ? 0.f : r1;
+                    pair(q, km, ku, kv, kw, r, dx, dy, dz, r1, r3, wld, f);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else {
+        const int row = lane >> 4, comp = ((row & 1) << 1) | (row >> 1);
+        int buf = 0;
+        for (int g = k0; g < k1; g += G, buf ^= 1) {
+#pragma unroll 1
+            for (int kk = 0; kk < G; kk += T) {
+                float mine = 0.f;
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const Record q = next[t];
+                    const int k = g + kk + t;
+                    next[t] = load(k + T);
+                    const float km = keep(q.p.w, k), ku = keep(q.w.x, k), kv = keep(q.w.y, k),
+                                kw = keep(q.w.z, k);
+                    float A[3] = {0.f, 0.f, 0.f}, Bk = 0.f, C[3] = {0.f, 0.f, 0.f}, Gk = 0.f;
+#pragma unroll
+                    for (int r = 0; r < KL; ++r) {
+                        const float dx = lx[r] - q.p.x, dy = ly[r] - q.p.y, dz = lz[r] - q.p.z;
+                        float r3, wld, f;
+                        pair(q, km, ku, kv, kw, r, dx, dy, dz, root(dx, dy, dz), r3, wld, f);
+                        A[0] = __builtin_fmaf(r3, lu[r], A[0]);
+                        A[1] = __builtin_fmaf(r3, lv[r], A[1]);
+                        A[2] = __builtin_fmaf(r3, lw[r], A[2]);
+                        Bk = __builtin_fmaf(lm[r], r3, Bk);
+                        C[0] = __builtin_fmaf(f, dx, C[0]);
+                        C[1] = __builtin_fmaf(f, dy, C[1]);
+                        C[2] = __builtin_fmaf(f, dz, C[2]);
+                        Gk = __builtin_fmaf(r3, wld, Gk);
+                    }
+                    const float gx = km * A[0] - ku * Bk + 3.f * C[0];
+                    const float gy = km * A[1] - kv * Bk + 3.f * C[1];
+                    const float gz = km * A[2] - kw * Bk + 3.f * C[2];
+                    // rows 0 .. 3 of the wave now hold the sums x, z, y, m
+                    const float v = row_sum(fold_rows(fold_halves(gx, gy), fold_halves(gz, -Gk)));
+                    mine = (lane & 1) == t ? v : mine;
+                }
+                red[buf][wave][G * comp + kk + (lane & 1)] = mine;
+            }
+            __syncthreads();  // two buffers in turn
+            if (tid < 4 * G) {
+                float v = 0.f;
+#pragma unroll
+                for (int w = 0; w < W; ++w) v += red[buf][w][tid];
+                const int c = tid / G, k = g + tid % G;
+                if (k < k1) a.ksum[((size_t)blockIdx.y * 4 + c) * a.n + k] = v;
+            }
+        }
+    }
+    float *out = a.lsum + ((size_t)blockIdx.y * a.chunks + blockIdx.x) * 4 * B + l0 - block * B;
+#pragma unroll
+    for (int r = 0; r < KL; ++r) {
+        out[64 * r] = lm[r] * s[r][0] - lu[r] * s[r][3] + 3.f * s[r][4];
+        out[B + 64 * r] = lm[r] * s[r][1] - lv[r] * s[r][3] + 3.f * s[r][5];
+        out[2 * B + 64 * r] = lm[r] * s[r][2] - lw[r] * s[r][3] + 3.f * s[r][6];
+        out[3 * B + 64 * r] = -s[r][7];
+    }
+}
+
 using MutualKernel = void (*)(MutualArgs);
 
 MutualKernel mutual_kernel(bool refine, bool guard, bool phi)
@@ -283,15 +443,18 @@ MutualKernel mutual_kernel(bool refine, bool guard, bool phi)
 
 }  // namespace
 
-MutualShape mutual_shape(int n, size_t part_cap)
+MutualShape mutual_shape(int n, size_t part_cap, bool adjoint)
 {
     MutualShape m{};
-    m.block = 64 * kLanes * kWaves;
+    m.block = 64 * kWaves * (adjoint ? kBwdLanes : kLanes);
     m.blocks = (n + m.block - 1) / m.block;
     // Short chunks balance the workgroups over the CUs, long ones write fewer
     // sums.  us with chunks of 192, 384 and 768: N = 50000 651, 734, 901; 65536
     // 1067, 1136, 1255; 131072 4127, 3975, 4084; 262144 16205, 15975, 15668.
     m.chunk = n < 100000 ? 192 : n < 230000 ? 384 : 768;
+    // the adjoint: 50000 1222 us with 128, 1308 with 256; 65536 2052, 2115;
+    // 131072 8070, 8084 and twice the memory
+    if (adjoint) m.chunk = n < 100000 ? 128 : 256;
     const size_t per_block = (size_t)4 * n + ((size_t)n + m.chunk) / m.chunk * 4 * m.block;
     m.strip = (int)std::min<size_t>(m.blocks, part_cap / per_block);
     m.floats = per_block * m.strip;
@@ -306,24 +469,43 @@ hipError_t launch_same_set(int n, const float *x, const float *y, const float *z
     return hipGetLastError();
 }
 
-hipError_t launch_newton_mutual(const MutualShape &m, int n, const float4 *jmem, float eps2,
-                                bool refine, bool guard, float *ax, float *ay, float *az,
-                                float *phi, float *part, const int *same, hipStream_t s)
+namespace {
+
+hipError_t launch_strips(MutualKernel kern, const MutualShape &m, MutualArgs a, float *ox,
+                         float *oy, float *oz, float *o4, hipStream_t s)
 {
-    MutualArgs a{n, jmem, eps2, 0, m.chunk, 0, nullptr, part, same};
-    const MutualKernel kern = mutual_kernel(refine, guard, phi != nullptr);
     for (a.block0 = 0; a.block0 < m.blocks; a.block0 += m.strip) {
         const int blocks = std::min(m.strip, m.blocks - a.block0);
         const int first = a.block0 * m.block;
-        a.chunks = (n - first + m.chunk - 1) / m.chunk;
-        a.lsum = a.ksum + (size_t)4 * n * blocks;
+        a.chunks = (a.n - first + m.chunk - 1) / m.chunk;
+        a.lsum = a.ksum + (size_t)4 * a.n * blocks;
         hipLaunchKernelGGL(kern, dim3(a.chunks, blocks), dim3(64 * kWaves), 0, s, a);
-        hipLaunchKernelGGL(k_mutual_combine, dim3((n - first + 255) / 256, phi ? 4 : 3), dim3(256),
-                           0, s, a, m.block, blocks, ax, ay, az, phi);
+        hipLaunchKernelGGL(k_mutual_combine, dim3((a.n - first + 255) / 256, o4 ? 4 : 3),
+                           dim3(256), 0, s, a, m.block, blocks, ox, oy, oz, o4);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t launch_newton_mutual(const MutualShape &m, int n, const float4 *jmem, float eps2,
+                                bool refine, bool guard, float *ax, float *ay, float *az,
+                                float *phi, float *part, const int *same, hipStream_t s)
+{
+    return launch_strips(mutual_kernel(refine, guard, phi != nullptr), m,
+                         MutualArgs{n, jmem, eps2, 0, m.chunk, 0, nullptr, part, same}, ax, ay, az,
+                         phi, s);
+}
+
+hipError_t launch_newton_mutual_bwd(const MutualShape &m, int n, const float4 *rec, float eps2,
+                                    bool refine, float *gx, float *gy, float *gz, float *gm,
+                                    float *part, hipStream_t s)
+{
+    return launch_strips(refine ? k_newton_mutual_bwd<true> : k_newton_mutual_bwd<false>, m,
+                         MutualArgs{n, rec, eps2, 0, m.chunk, 0, nullptr, part, nullptr}, gx, gy,
+                         gz, gm, s);
 }
 
 }  // namespace pgh

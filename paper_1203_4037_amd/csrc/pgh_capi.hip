@@ -257,6 +257,9 @@ constexpr size_t kMaxMutualFloats = (size_t)256 << 20;
 // mutual; 40000: 494, 456), and looking whether the sets are the same costs a
 // call in which they aren't 8 us of 494.
 constexpr int kMutualMin = 40000;
+// The adjoint of a set on itself: each pair twice 360 us at N = 24000, 334 mutual;
+// 176 at 16384, more mutual.
+constexpr int kMutualBwdMin = 24000;
 
 // Scratch of the allocation-free entry point (pgh_calc_newton_noalloc): the
 // partial sums of its j-split, in a device array of fixed size that each GPU
@@ -786,7 +789,7 @@ int pgh_calc_newton(pgh_ctx *c, int ni, const float *xi, const float *yi, const 
     const bool mutual = v == newton_allpairs_mutual() || (v < 0 && ni >= kMutualMin);
     if (v < 0) v = newton_allpairs_default(ni, c->nj, c->num_cu);
     if (mutual && ni == c->nj && !eps2_i) {
-        const MutualShape m = mutual_shape(ni, kMaxMutualFloats);
+        const MutualShape m = mutual_shape(ni, kMaxMutualFloats, false);
         if (m.strip > 0 && part_ready(c, m.floats)) {
             PGH_HIP(c, launch_same_set(ni, xi, yi, zi, c->jmem, c->same, c->stream));
             PGH_HIP(c, launch_newton_mutual(m, ni, c->jmem, c->eps2_all, c->refine != 0, guard, ax,
@@ -1312,6 +1315,14 @@ int pgh_newton_allpairs_bwd(pgh_ctx *c, int n, const float *x, const float *y, c
     int st = ensure_scratch(c, &c->scr_a, &c->scr_a_cap, 2 * (size_t)n);
     if (st) return st;
     PGH_HIP(c, launch_pack_xw(n, x, y, z, m, 0.f, wx, wy, wz, c->scr_a, c->stream));
+    if (n >= kMutualBwdMin) {
+        const MutualShape ms = mutual_shape(n, kMaxMutualFloats, true);
+        if (ms.strip > 0 && part_ready(c, ms.floats)) {
+            PGH_HIP(c, launch_newton_mutual_bwd(ms, n, c->scr_a, eps2, c->refine != 0, gx, gy, gz,
+                                                gm, c->part, c->stream));
+            return PGH_OK;
+        }
+    }
     const int S = adjoint_split(n, n, kMaxSplitFloats);
     if (S > 1 && (st = ensure_part(c, (size_t)S * 4 * n))) return st;
     PGH_HIP(c, launch_newton_allpairs_bwd(n, c->scr_a, eps2, c->refine != 0, gx, gy, gz, gm, S,

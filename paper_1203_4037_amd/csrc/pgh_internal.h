@@ -37,7 +37,7 @@ struct NewtonArgs {
     const int *same;
 };
 
-// The launch of the mutual kernel on a set of n (newton_mutual.hip).
+// The launch of a mutual kernel on a set of n (newton_mutual.hip).
 struct MutualShape {
     int block, blocks;  // l-particles of a block, blocks of the set
     int chunk;          // k-particles of a workgroup
@@ -45,7 +45,10 @@ struct MutualShape {
     size_t floats;      // scratch floats of a launch
 };
 // (strip = 0: not even one block's sums fit part_cap floats)
-MutualShape mutual_shape(int n, size_t part_cap);
+MutualShape mutual_shape(int n, size_t part_cap, bool adjoint);
+hipError_t launch_newton_mutual_bwd(const MutualShape &m, int n, const float4 *rec, float eps2,
+                                    bool refine, float *gx, float *gy, float *gz, float *gm,
+                                    float *part, hipStream_t s);
 hipError_t launch_same_set(int n, const float *x, const float *y, const float *z,
                            const float4 *jmem, int *same, hipStream_t s);
 hipError_t launch_newton_mutual(const MutualShape &m, int n, const float4 *jmem, float eps2,

@@ -568,3 +568,40 @@ def test_table_moments_path(pgh, ctx):
     for rep in range(2):
         check(items, x, y, z, x, y, z, m, synth.weights(n, 47 + rep), f"disjoint j {rep}",
               rest=False)
+
+
+@pytest.mark.parametrize("n", [24000, 24576, 24577, 26500])
+@pytest.mark.parametrize("refine", [0, 1])
+def test_mutual_adjoint_of_large_sets(pgh, ctx, n, refine):
+    """The adjoint that evaluates each pair once, at and beside a whole number
+    of its blocks, some masses zero, against the gather in FP64 for spread
+    particles.  A pair's terms are at most T = 4 rho^3 (m_k |w_l| + m_l |w_k|)
+    per component and take some 12 roundings, a sum some 200 more; these walk
+    at random: 4 sqrt(212) 2^-24 of the terms' sum, 3.5e-6."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    p = torch.randn(3, n, generator=g, device="cuda")
+    w = torch.randn(3, n, generator=g, device="cuda")
+    m = torch.rand(n, generator=g, device="cuda") / n
+    m[::7] = 0.0
+    eps2 = 1e-4
+    ctx.set_rsqrt_refine(refine)
+    ctx._sync_stream()
+    out = torch.full((4, n), float("nan"), device="cuda")
+    pgh.pgh_newton_allpairs_bwd(ctx.h, n, *p, m, eps2, *w, *out)
+    idx = torch.linspace(0, n - 1, 200, device="cuda").long()
+    P, W, M = p.double(), w.double(), m.double()
+    d = P[:, None, :] - P[:, idx, None]
+    rho2 = 1.0 / ((d * d).sum(0) + float(np.float32(eps2)))
+    rho3 = rho2 ** 1.5
+    rho3[torch.arange(200, device="cuda"), idx] = 0.0
+    wl, wk = (W[:, None, :] * d).sum(0), (W[:, idx, None] * d).sum(0)
+    e = M[None] * wk - M[idx, None] * wl
+    ref = ((M[idx, None] * rho3)[None] * W[:, None, :] - W[:, idx, None] * (M[None] * rho3)[None]
+           + 3 * (rho3 * rho2 * e)[None] * d).sum(2)
+    size = 4 * (rho3 * (M[idx, None] * W.norm(dim=0)[None] + M[None] * W[:, idx].norm(dim=0)[:, None])).sum(1)
+    assert bool(((out[:3, idx].double() - ref).abs() <= 3.5e-6 * size[None]).all())
+    gm = -(rho3 * wl).sum(1)
+    size_m = (rho3 * W.norm(dim=0)[None] * d.norm(dim=0)).sum(1)
+    assert bool(((out[3, idx].double() - gm).abs() <= 3.5e-6 * size_m).all())
+    assert bool(torch.isfinite(out).all())
