@@ -28,7 +28,7 @@
 //           distance from its com to the group's bounding box, and adds its
 //           pseudo-particles; an opened leaf adds its particles.
 //
-// The build launches every level with its size in a device table and waits
+// The build keeps the sizes of the levels in a device table and waits
 // for the stream once, at its end (the walk waits after its counting pass);
 // neither is meant for graph capture.
 #include <hipcub/hipcub.hpp>
