@@ -155,10 +155,17 @@ lib = _load()
 # argument marshalling
 # --------------------------------------------------------------------------
 
+_Tensor, _F32 = torch.Tensor, torch.float32
+
+
 def _ptr(t, n=None, what="array", device=None):
     """Device pointer of a float32 contiguous GPU tensor with at least n elements."""
     if t is None:
         return None
+    # every check at once (0.31 us an array, one by one 0.36), then which failed
+    if (device is None and isinstance(t, _Tensor) and t.dtype is _F32 and t.is_cuda
+            and t.is_contiguous() and (n is None or t.numel() >= n)):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{what} must be a torch tensor")
     if t.dtype != torch.float32:
@@ -181,6 +188,11 @@ def _check(ctx, st):
 
 def _stream(device):
     return torch.cuda.current_stream(device).cuda_stream
+
+
+# the same handle without a Stream object around it (0.1 against 1.2 us, and
+# every call asks), once pgh_open's _stream has initialised the device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _stream)
 
 
 # --------------------------------------------------------------------------
@@ -646,7 +658,8 @@ class Context:
     """One library context on one GPU; calls run on torch's current stream."""
 
     def __init__(self, device: int = 0):
-        self.device = torch.device("cuda", device).index
+        self._device = torch.device("cuda", device)
+        self.device = self._device.index
         self.h = pgh_open(self.device)
         self.nj = 0
         self.table = None
@@ -666,10 +679,10 @@ class Context:
             pass
 
     def _sync_stream(self):
-        pgh_set_stream(self.h, _stream(self.device))
+        pgh_set_stream(self.h, _raw_stream(self.device))
 
     def _empty(self, n):
-        return torch.empty(n, dtype=torch.float32, device=torch.device("cuda", self.device))
+        return torch.empty(n, dtype=_F32, device=self._device)
 
     def set_eps_to_all(self, eps):
         pgh_set_eps_to_all(self.h, eps)
