@@ -896,7 +896,14 @@ def main():
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
                      "traffic": measured_traffic(r["variant_name"], r["refine"]),
                      "traffic_unit": "bytes/launch",
-                     "kernel": "k_newton_allpairs",
+                     "kernel": {"mutual": "k_newton_mutual",
+                                "rows": "k_newton_rows"}.get(r["variant_name"],
+                                                             "k_newton_allpairs"),
+                     # the mutual kernel forms a pair's difference, distance and root
+                     # once for its two interactions, each of which counts its 38
+                     # flop: its achieved rate is not bounded by the peak
+                     "pairs_evaluated_per_interaction":
+                         0.5 if r["variant_name"] == "mutual" else 1.0,
                      # HIP events around pgh_calc_newton on its stream: the kernel and,
                      # when the j-range is split, k_combine_split (a few microseconds)
                      "kernel_ms": r["kern_ms"],
