@@ -269,12 +269,13 @@ struct NewtonBatchVariant {
     BatchKernel (*pick)(bool refine, bool guard, bool phi);
 };
 const NewtonBatchVariant kNewtonBatchVariants[] = {
-    {"ki=1 jt=64 u=8", newton_kernel_t<false, 8>},  // the default
+    {"ki=1 jt=64 u=8", newton_kernel_t<false, 8>},
     {"ki=1 jt=64 u=8 rcp", newton_kernel_t<true, 8>},
     {"ki=1 jt=64 u=4", newton_kernel_t<false, 4>},
     {"ki=1 jt=64 u=2", newton_kernel_t<false, 2>},
     {"ki=1 jt=64 u=16", newton_kernel_t<false, 16>},
 };
+constexpr int kDeepVariant = 4;
 constexpr int kNumNewtonBatchVariants =
     sizeof(kNewtonBatchVariants) / sizeof(kNewtonBatchVariants[0]);
 
@@ -345,6 +346,12 @@ hipError_t launch_newton_batch(const BatchArgs &a, int variant, bool refine, boo
 {
     // packed outputs always carry the potential
     const bool phi = a.phi != nullptr || a.out4 != nullptr;
+    // the built-in choice: the deeper unroll for plans that give a wave two
+    // tasks at most, where the latency of a tile's reads shows (us with U = 8 and
+    // 16: 4000 lists of 64 x 512 59.4, 57.1; 500 of 256 x 4096 211.8, 203.1; 1000
+    // tree lists 208, 201), the smaller loop for longer queues (5000 tree lists
+    // 834, 841; 20000 of 40 x 33 25.9, 26.2)
+    if (variant < 0) variant = a.n_tasks <= 16384 ? kDeepVariant : 0;
     return launch(newton_kernel(refine, guard, phi, variant), a, num_cu, s, phi);
 }
 

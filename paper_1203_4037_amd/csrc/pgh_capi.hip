@@ -1219,7 +1219,7 @@ int pgh_batch_newton(pgh_ctx *c, const pgh_plan *p, const float *xi, const float
     a.xj = xj, a.yj = yj, a.zj = zj, a.mj = mj;
     a.ax = ax, a.ay = ay, a.az = az, a.phi = phi;
     const bool guard = (eps2_i == nullptr) && !(c->eps2_all > 0.f);
-    const int v = std::max(0, c->variant[PGH_FAMILY_NEWTON_BATCH]);
+    const int v = c->variant[PGH_FAMILY_NEWTON_BATCH];
     PGH_HIP(c, launch_newton_batch(a, v, c->refine != 0, guard, c->num_cu, c->stream));
     return PGH_OK;
 }
@@ -1744,7 +1744,7 @@ int pgh_tree_newton(pgh_ctx *c, pgh_tree *t, float *ax, float *ay, float *az, fl
     a.jxm = s.xmj;
     a.out4 = s.res;
     const bool guard = !(c->eps2_all > 0.f);
-    const int v = std::max(0, c->variant[PGH_FAMILY_NEWTON_BATCH]);
+    const int v = c->variant[PGH_FAMILY_NEWTON_BATCH];
     PGH_HIP(c, launch_newton_batch(a, v, c->refine != 0, guard, c->num_cu, c->stream));
     PGH_HIP(c, launch_tree_outputs(s, ax, ay, az, phi, c->stream));
     return PGH_OK;
