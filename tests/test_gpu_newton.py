@@ -303,3 +303,36 @@ def test_mutual_kernel_far_from_unit_scale(pgh, ctx, unit):
     assert np.isfinite(out[0][0]).all() and np.abs(out[1][0]).min() > 0
     ea = rel_vec_err(out[0][0], out[1][0].astype(np.float64))
     assert rms(ea) <= RMS_TOL and ea.max() <= MAX_TOL
+
+
+def test_mutual_choice_inside_a_graph(pgh, ctx):
+    """The choice by the sets is made on the device: a captured call follows the
+    i-particles as they become another set and the j-set again; replays with
+    eager calls of the same context between them."""
+    import torch
+    n = 41000
+    p = to_dev(*synth.plummer(n, 31))
+    m = torch.full((n,), 1.0 / n, device="cuda")
+    i = [v.clone() for v in p]
+    ctx.set_eps_to_all(1.0 / 64)
+    ctx.set_j(*p, m)
+    names = [pgh.pgh_variant_name(0, v) for v in range(pgh.pgh_variant_count(0))]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ctx.newton(*i)  # grows the scratch memory
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = ctx.newton(*i)
+    for k in range(6):
+        i[1][7 * k] = p[1][7 * k] + (0.5 if k % 2 else 0.0)
+        g.replay()
+        torch.cuda.synchronize()
+        got = torch.stack(out).clone()
+        ctx.set_variant(pgh.PGH_FAMILY_NEWTON_ALLPAIRS, names.index("rows" if k % 2 else "mutual"))
+        want = torch.stack(ctx.newton(*i))
+        ctx.set_variant(pgh.PGH_FAMILY_NEWTON_ALLPAIRS, -1)
+        assert torch.equal(got, want), k
+        i[1][7 * k] = p[1][7 * k]

@@ -207,3 +207,38 @@ def test_all_pairs_counts_of_the_near_kernel(pgh, ctx, ni, nj, variant, rcut):
     items = [(int(i), 1, 0, nj) for i in rows]
     assert np.array_equal(out[0][3][rows], _counts(items, pi, pj, rcut)[rows])
     assert np.array_equal(*out) and np.isfinite(out[0]).all()
+
+
+def test_near_choice_inside_a_graph(pgh, ctx):
+    """The kernel for many pairs inside is chosen on the device: a captured call
+    counts right as the particles, in place, move together and apart."""
+    import torch
+    n, rcut = 20001, 0.05
+    rng = np.random.default_rng(8)
+    base = rng.random((3, n)).astype(np.float32)
+    _count_table(pgh, ctx, rcut)
+    d = to_dev(*base)
+    one = torch.ones(n, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ctx.set_j(*d, one)
+        ctx.table_force(*d, with_phi=True)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ctx.set_j(*d, one)
+        out = ctx.table_force(*d, with_phi=True)
+    rows = np.unique(np.linspace(0, n - 1, 60).astype(int))
+    items = [(int(i), 1, 0, n) for i in rows]
+    for k in range(5):
+        p = base * np.float32(0.03 if k % 2 else 1.0)
+        for v, w in zip(d, to_dev(*p)):
+            v.copy_(w)
+        g.replay()
+        torch.cuda.synchronize()
+        phi = out[3].cpu().numpy().copy()
+        eager = ctx.table_force(*d, with_phi=True)[3].cpu().numpy()
+        assert np.array_equal(phi[rows], _counts(items, p, p, rcut)[rows]), k
+        assert np.array_equal(phi, eager), k
