@@ -321,8 +321,10 @@ __global__ void __launch_bounds__(NT) k_newton_rows(NewtonArgs a)
         ++t;
     }
     if (t * NT < nj) {
-        // a zero-mass record far away adds exactly zero, also unsoftened
-        if (t * NT + tid >= nj) p0 = make_float4(1.0e10f, 1.0e10f, 1.0e10f, 0.f);
+        // the other lanes hold the last record, which without its mass adds
+        // exactly zero where its own pairs are finite (a record put far away
+        // would not: its |d|^2 may overflow where no pair's does)
+        if (t * NT + tid >= nj) p0.w = 0.f;
         pairs(p0);
     }
 

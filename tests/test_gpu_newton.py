@@ -336,3 +336,28 @@ def test_mutual_choice_inside_a_graph(pgh, ctx):
         ctx.set_variant(pgh.PGH_FAMILY_NEWTON_ALLPAIRS, -1)
         assert torch.equal(got, want), k
         i[1][7 * k] = p[1][7 * k]
+
+
+@pytest.mark.parametrize("refine", [0, 1])
+@pytest.mark.parametrize("variant,ni,nj", [("rows", 257, 300), ("rows", 9, 4100), ("rows", 4501, 513),
+                                           ("mutual", 3073, 3073), (None, 1000, 1000)])
+def test_compact_cluster_far_from_the_origin(pgh, ctx, variant, ni, nj, refine):
+    """Lists that end between two steps, of particles farther from the origin
+    than the square root of the largest FP32 number: every pair is finite, and
+    a filled-up lane may only add what one of them, massless, adds."""
+    off = np.float32(3.0e20)
+    xj, yj, zj = (off + np.float32(1.0e17) * v for v in synth.plummer(nj, 41))
+    if variant == "mutual" or variant is None:
+        xi, yi, zi = xj, yj, zj
+    else:
+        xi, yi, zi = (off + np.float32(1.0e17) * v for v in synth.plummer(ni, 42))
+    m = np.full(nj, 1.0e30, np.float32)
+    ctx.set_rsqrt_refine(refine)
+    names = [pgh.pgh_variant_name(0, v) for v in range(pgh.pgh_variant_count(0))]
+    ctx.set_variant(pgh.PGH_FAMILY_NEWTON_ALLPAIRS, -1 if variant is None else names.index(variant))
+    a, phi = _gpu_newton(ctx, xi, yi, zi, xj, yj, zj, m, eps=1.0e16)
+    idx = np.unique(np.linspace(0, ni - 1, 60).astype(int))
+    e2 = np.full(idx.size, np.float32(1.0e16) ** 2, np.float32)
+    ref = oracle.newton(xi[idx], yi[idx], zi[idx], e2, xj, yj, zj, m)
+    assert np.isfinite(a).all() and np.isfinite(phi).all()
+    _check(a[:, idx], phi[idx], ref, f"{variant} {ni} x {nj}")
