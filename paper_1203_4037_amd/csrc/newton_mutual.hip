@@ -347,7 +347,9 @@ k_newton_mutual_bwd(MutualArgs a)
 
     if (k0 < (block + 1) * B) {
         // of the block itself, for l only; l's own term is identically zero, but
-        // would enter A and B as +-m w / eps^3 and cancel only to rounding
+        // would enter A and B as +-m w / eps^3 and cancel only to rounding, and
+        // the last particle's copies past the end, zero mass and weight or not,
+        // as 0 / eps^5, which leaves the range of FP32 for small softenings
 #pragma unroll 1
         for (int k = k0; k < k1; k += T) {
 #pragma unroll
@@ -360,7 +362,7 @@ k_newton_mutual_bwd(MutualArgs a)
                 for (int r = 0; r < KL; ++r) {
                     const float dx = lx[r] - q.p.x, dy = ly[r] - q.p.y, dz = lz[r] - q.p.z;
                     float r1 = root(dx, dy, dz), r3, wld, f;
-                    r1 = l0 + 64 * r == k + t ? 0.f : r1;
+                    r1 = l0 + 64 * r == min(k + t, a.n - 1) ? 0.f : r1;
                     pair(q, km, ku, kv, kw, r, dx, dy, dz, r1, r3, wld, f);
                 }
                 __builtin_amdgcn_sched_barrier(0);

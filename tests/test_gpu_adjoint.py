@@ -605,3 +605,52 @@ def test_mutual_adjoint_of_large_sets(pgh, ctx, n, refine):
     size_m = (rho3 * W.norm(dim=0)[None] * d.norm(dim=0)).sum(1)
     assert bool(((out[3, idx].double() - gm).abs() <= 3.5e-6 * size_m).all())
     assert bool(torch.isfinite(out).all())
+
+
+def _gather64(p, w, m, eps2, idx):
+    """The adjoint of the rows idx in FP64, and for each row the sums of the
+    largest terms a pair can add to a position's and to a mass's gradient."""
+    import torch
+    P, W, M = p.double(), w.double(), m.double()
+    d = P[:, None, :] - P[:, idx, None]
+    rho2 = 1.0 / ((d * d).sum(0) + float(np.float32(eps2)))
+    rho2[torch.arange(idx.numel(), device="cuda"), idx] = 0.0
+    rho3 = rho2 ** 1.5
+    wl, wk = (W[:, None, :] * d).sum(0), (W[:, idx, None] * d).sum(0)
+    e = M[None] * wk - M[idx, None] * wl
+    ref = ((M[idx, None] * rho3)[None] * W[:, None, :] - W[:, idx, None] * (M[None] * rho3)[None]
+           + 3 * (rho3 * rho2 * e)[None] * d).sum(2)
+    size = 4 * (rho3 * (M[idx, None] * W.norm(dim=0)[None] + M[None] * W[:, idx].norm(dim=0)[:, None])).sum(1)
+    gm = -(rho3 * wl).sum(1)
+    size_m = (rho3 * W.norm(dim=0)[None] * d.norm(dim=0)).sum(1)
+    return ref, size, gm, size_m
+
+
+# an odd n and a softening whose fifth power is no FP32 number; several strips
+# of blocks with the chunks of smaller and of larger sets; no mass gradient
+@pytest.mark.parametrize("n,eps2,with_gm", [(24001, 1e-17, True), (24576, 1e-17, True),
+                                            (26501, 1e-30, False), (99001, 1e-4, True),
+                                            (100001, 1e-4, True), (131072, 1e-4, False)])
+@pytest.mark.parametrize("refine", [0, 1])
+def test_mutual_adjoint_strips_and_tiny_softening(pgh, ctx, n, eps2, with_gm, refine):
+    """As test_mutual_adjoint_of_large_sets, whose bound holds here: the roundings
+    of a pair are the same, and a row's partial sums (n / chunk of chunk terms)
+    add at most another sqrt(n / 128) = 32 steps of the walk, 3.7e-6."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    p = torch.randn(3, n, generator=g, device="cuda")
+    w = torch.randn(3, n, generator=g, device="cuda")
+    m = torch.rand(n, generator=g, device="cuda") / n
+    m[::7] = 0.0
+    ctx.set_rsqrt_refine(refine)
+    ctx._sync_stream()
+    out = torch.full((4, n), float("nan"), device="cuda")
+    pgh.pgh_newton_allpairs_bwd(ctx.h, n, *p, m, eps2, *w, *out[:3], out[3] if with_gm else None)
+    rows = out if with_gm else out[:3]
+    assert bool(torch.isfinite(rows).all()) and (with_gm or bool(torch.isnan(out[3]).all()))
+    idx = torch.cat([torch.linspace(0, n - 1, 100, device="cuda").long(),
+                     torch.arange(n - 20, n - 1, device="cuda")])
+    ref, size, gm, size_m = _gather64(p, w, m, eps2, idx)
+    assert bool(((out[:3, idx].double() - ref).abs() <= 3.7e-6 * size[None]).all())
+    if with_gm:
+        assert bool(((out[3, idx].double() - gm).abs() <= 3.7e-6 * size_m).all())
