@@ -379,10 +379,9 @@ k_batch_table_near(BatchArgs a)
                          (unsigned)(K - 1) << (PHI ? 4 : 3), ~((1u << kshift) - 1u)};
     const char *tab = (const char *)stab;
     __syncthreads();  // the only workgroup barrier: waves are independent after it
-    // whether pairs beyond the cutoff add exactly zero (and the cutoff is
-    // far above the smallest numbers, which the products may flush)
+    // whether pairs beyond the cutoff add exactly zero and can be found
     const Entry last = stab[K - 1];
-    bool last_zero = last.x == 0.f && last.y == 0.f && a.r2max > 1.0e-30f;
+    bool last_zero = last.x == 0.f && last.y == 0.f && filter_cut(a.r2max);
     if constexpr (PHI) last_zero = last_zero && last.z == 0.f && last.w == 0.f;
 
     while (t < n_t) {
@@ -436,7 +435,7 @@ k_batch_table_near(BatchArgs a)
                     const float r2 =
                         __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));
                     const bool keep = base + 64 * s + lane < n_j &&
-                                      (r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
+                                      (whole || r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
                     const unsigned long long who = __ballot(keep);
                     if (keep) {
                         const int k = kept + lanes_below(who);

@@ -424,7 +424,8 @@ k_table_near(TableArgs a)
     if (a.dense && *a.dense != 0) return;  // k_table_allpairs computes this call
     const int K = 1 << (a.E + a.F);
     // after the table, NI float4 per wave: its tile of 64 records, then its sums
-    float4 *const sums = dyn4 + (PHI ? K : K / 2);
+    // (a table of one (G0, G1) takes a float4 all the same)
+    float4 *const sums = dyn4 + (PHI ? K : (K + 1) / 2);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float4 *const tile = sums + wave * NI;
 
@@ -444,7 +445,7 @@ k_table_near(TableArgs a)
     const TableConsts kc{a.c, __float_as_uint(a.smax), kshift - (PHI ? 4 : 3),
                          (unsigned)(K - 1) << (PHI ? 4 : 3), ~((1u << kshift) - 1u)};
     __syncthreads();
-    bool last_zero = a.r2max > 1.0e-30f;
+    bool last_zero = filter_cut(a.r2max);
     if (PHI) {
         const float4 e = dyn4[K - 1];
         last_zero = last_zero && e.x == 0.f && e.y == 0.f && e.z == 0.f && e.w == 0.f;
@@ -508,7 +509,7 @@ k_table_near(TableArgs a)
             const float r2 = __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));
             const bool valid = base + lane < nj;
             // (each step is monotone: no pair with the chunk has a smaller |d|^2)
-            const bool keep = valid && (r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
+            const bool keep = valid && (whole || r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
             if (!__any(keep)) continue;
             wave_sync_tile();  // the previous step's reads are done
             tile[filter_slot(lane)] = keep ? v : make_float4(1.0e10f, 1.0e10f, 1.0e10f, 0.f);
@@ -737,7 +738,7 @@ hipError_t launch_table_near(const TableArgs &a, int num_cu, hipStream_t s)
 {
     const bool phi = is_phi(a);
     // four columns share a record's terms; two give small sets more waves
-    const size_t table = table_lds_bytes(a);
+    const size_t table = std::max(sizeof(float4), table_lds_bytes(a));
     const int nc = a.ni >= 32768 ? 4 : 2;
     // eight waves and two workgroups to a CU, or sixteen where a large table
     // (or few chunks) leaves room for one

@@ -25,7 +25,7 @@
 // besides is found out by the FP32 evaluation.
 //
 // Particles that are not ordinary() (infinite, NaN, huge) and, when the last
-// node is not zero, all i-particles get a norm that makes every pair of theirs
+// node is not zero or the cutoff not filter_cut(), all i-particles get a norm that makes every pair of theirs
 // a candidate; rows past a list's end and unused columns one that makes none.
 #pragma once
 
@@ -44,6 +44,15 @@ typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
 constexpr float kFilterNorm = 1.0f - 0x1p-14f;
 constexpr float kFilterCut = 1.0f + 0x1p-13f;
 constexpr float kAlways = -1.0e36f, kNever = 1.0e37f;  // beside norms of at most 1.2e31
+
+// Whether the products can tell distances from the cutoff: far above the
+// smallest numbers, which they may flush, and no larger than the norms.  False
+// for the r2max of tables without an ordinary cutoff, which need not be a number
+// (a table of one node) nor above zero (|d|^2 in units of a tiny cutoff overflows).
+__device__ __forceinline__ bool filter_cut(float r2max)
+{
+    return r2max > 1.0e-30f && r2max < 1.0e30f;
+}
 
 // The two operands of 64 particles, one per lane: t[0] of particles 0 .. 31,
 // t[1] of 32 .. 63 (lanes < 32 hold the first eight terms of particle lane mod

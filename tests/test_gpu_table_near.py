@@ -242,3 +242,43 @@ def test_near_choice_inside_a_graph(pgh, ctx):
         eager = ctx.table_force(*d, with_phi=True)[3].cpu().numpy()
         assert np.array_equal(phi[rows], _counts(items, p, p, rcut)[rows]), k
         assert np.array_equal(phi, eager), k
+
+
+# shapes of tables whose least |d|^2 at the last node is not an ordinary number:
+# one node only (s_max = 2), a cutoff whose square is no FP32 number, and ones
+# whose squared inverse or whose distance to |d|^2 = 0 leaves the range
+@pytest.mark.parametrize("e,f,rcut", [(0, 0, 0.5), (0, 0, 1e19), (E, F, 1e-20), (E, F, 3e-23),
+                                      (E, F, 1e19), (E, F, 3e18), (1, 0, 0.5), (6, 0, 1e-12),
+                                      (6, 4, 1e19)])
+@pytest.mark.parametrize("path", ["batched", "moments", "near", "rows", "default"])
+def test_tables_without_an_ordinary_cutoff(pgh, ctx, e, f, rcut, path):
+    """A table that is nowhere zero, given by its entries: every kernel adds
+    every pair, as the general ones (variant 0) do.  Differences to the
+    rounding of sums of up to 1000 terms of at most m max|G| |d| each."""
+    rng = np.random.default_rng(5)
+    items = np.array([(0, 70, 0, 300), (70, 30, 300, 1000), (100, 64, 1300, 65)], np.int32)
+    pi = rng.random((3, 164)).astype(np.float32)
+    pj = rng.random((3, 1365)).astype(np.float32)
+    m = np.full(1365, 1.0, np.float32)
+    k = 1 << (e + f)
+    t = np.zeros(2 * k, np.float32)
+    t[0::2] = rng.uniform(0.5, 1.0, k)
+    ctx.set_table(e, f, rcut, to_dev(t)[0])
+    di, dj = to_dev(*pi), to_dev(*pj, m)
+    plan = ctx.plan(items, 164, 1365)
+    batched = path in ("batched", "moments")
+    fam = pgh.PGH_FAMILY_TABLE_BATCH if batched else pgh.PGH_FAMILY_TABLE_ALLPAIRS
+    names = [pgh.pgh_variant_name(fam, v) for v in range(pgh.pgh_variant_count(fam))]
+    ctx.set_j(*dj)
+    got = []
+    for v in (0, names.index(path) if path in names and not batched else -1):
+        ctx.set_variant(fam, v)
+        if path == "moments" and v == -1:
+            got.append(np.stack(to_host(*plan.table_moments(*di, *dj)[0])))
+        elif batched:
+            got.append(np.stack(to_host(*plan.table(*di, *dj))))
+        else:
+            got.append(np.stack(to_host(*ctx.table_force(*di))))
+    a, b = got
+    assert np.abs(a).max() > 1.0 and np.isfinite(a).all()
+    assert np.abs(a - b).max() <= 1365 * 1000 * 2.0 ** -24 * np.sqrt(3)
