@@ -330,8 +330,10 @@ __global__ void __launch_bounds__(NT) k_table_rows(TableArgs a)
             ++t;
         }
         if (t * NT < nj) {
-            // a zero-mass record far away adds exactly zero
-            if (t * NT + tid >= nj) p0 = make_float4(1.0e10f, 1.0e10f, 1.0e10f, 0.f);
+            // the other lanes hold the last record, which without its mass adds
+            // zero (a record far away would take the last node, not a number
+            // perhaps, where no pair does)
+            if (t * NT + tid >= nj) p0.w = 0.f;
             pairs(p0);
         }
         if (g + (int)gridDim.x < groups) p0 = load(0), p1 = load(1);
@@ -512,7 +514,9 @@ k_table_near(TableArgs a)
             const bool keep = valid && (whole || r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
             if (!__any(keep)) continue;
             wave_sync_tile();  // the previous step's reads are done
-            tile[filter_slot(lane)] = keep ? v : make_float4(1.0e10f, 1.0e10f, 1.0e10f, 0.f);
+            // (dropped, or past the end and so the last record again: without
+            // its mass, so that the whole path adds zero for it)
+            tile[filter_slot(lane)] = make_float4(v.x, v.y, v.z, keep ? v.w : 0.f);
             wave_sync_tile();
             const float4 *mine = tile + (lane & 32);
             bool direct = blind > 0;

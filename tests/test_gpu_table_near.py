@@ -282,3 +282,31 @@ def test_tables_without_an_ordinary_cutoff(pgh, ctx, e, f, rcut, path):
     a, b = got
     assert np.abs(a).max() > 1.0 and np.isfinite(a).all()
     assert np.abs(a - b).max() <= 1365 * 1000 * 2.0 ** -24 * np.sqrt(3)
+
+
+@pytest.mark.parametrize("variant", ["near", "rows"])
+@pytest.mark.parametrize("with_phi", [False, True])
+@pytest.mark.parametrize("ni,nj", [(164, 1365), (33, 65), (5, 3)])
+def test_last_node_not_finite_where_no_pair_reaches_it(pgh, ctx, variant, with_phi, ni, nj):
+    """Lists that end between two steps, all pairs inside the cutoff: nothing
+    of the last node's infinity and NaN reaches a result."""
+    rng = np.random.default_rng(6)
+    pi, pj = rng.random((3, ni)).astype(np.float32), rng.random((3, nj)).astype(np.float32)
+    rcut = 4.0
+    table = ctx.build_table(E, F, rcut, eps=rcut / 15)
+    table[-2:] = np.inf, np.nan
+    ctx.set_table(E, F, rcut, to_dev(table)[0])
+    if with_phi:
+        t = np.zeros(2 * K, np.float32)
+        t[0::2] = 1.0
+        t[-2] = np.nan
+        ctx._sync_stream()
+        pgh.pgh_set_pot_table(ctx.h, to_dev(t)[0])
+    fam = pgh.PGH_FAMILY_TABLE_ALLPAIRS
+    names = [pgh.pgh_variant_name(fam, v) for v in range(pgh.pgh_variant_count(fam))]
+    ctx.set_variant(fam, names.index(variant))
+    ctx.set_j(*to_dev(*pj, np.ones(nj, np.float32)))
+    out = np.stack(to_host(*ctx.table_force(*to_dev(*pi), with_phi=with_phi)))
+    assert np.isfinite(out).all()
+    if with_phi:
+        assert np.array_equal(out[3], np.full(ni, float(nj)))
