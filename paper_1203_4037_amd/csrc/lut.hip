@@ -166,6 +166,7 @@ __global__ void __launch_bounds__(NT) k_table_allpairs(TableArgs a)
 // A step whose tests all found pairs of most of their i-particles inside is
 // followed by this many evaluated whole without a test.
 constexpr int kWholeSteps = 7;
+constexpr int kFreshSteps = 16;  // of k_table_near, in a sum before it is added to its total
 
 // One j-record of the lane against Q uniform i-particles; s[k]: their sums.
 template <int Q, bool PHI>
@@ -425,11 +426,11 @@ k_table_near(TableArgs a)
     extern __shared__ float4 dyn4[];
     if (a.dense && *a.dense != 0) return;  // k_table_allpairs computes this call
     const int K = 1 << (a.E + a.F);
-    // after the table, NI float4 per wave: its tile of 64 records, then its sums
-    // (a table of one (G0, G1) takes a float4 all the same)
-    float4 *const sums = dyn4 + (PHI ? K : (K + 1) / 2);
+    // after the table (one (G0, G1) takes a float4 all the same) each wave's
+    // tile of 64 records, then each wave's sums of the chunk
+    float4 *const tiles = dyn4 + (PHI ? K : (K + 1) / 2), *const sums = tiles + 64 * W;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float4 *const tile = sums + wave * NI;
+    float4 *const tile = tiles + 64 * wave, *const total = sums + wave * NI;
 
     // the wave's share of the j-particles, a multiple of 64 records
     const int per = ((a.nj + 64 * W - 1) / (64 * W)) * 64;
@@ -499,7 +500,30 @@ k_table_near(TableArgs a)
         }
 #pragma unroll
         for (int q = 0; q < NC; ++q) tx[q] = ty[q] = tz[q] = tp[q] = 0.f;
+        // A column's sums of both halves' rows go to its words in LDS once per
+        // kFreshSteps steps, so that FP32 rounding grows with 32 kFreshSteps terms
+        // and the number of these sums, not with the wave's share of the list
+        // (10^6 neighbours of one mass: 1.6e-4 in one running sum).
+#pragma unroll
+        for (int q = 0; q < NC / 2; ++q) total[64 * q + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+        auto to_total = [&] {
+#pragma unroll
+            for (int q = 0; q < NC; q += 2) {
+                // lane l: column q for l < 32, q + 1 for the others
+                auto both = [&](float *v) {
+                    const float a = v[q] + __shfl_xor(v[q], 32);
+                    const float b = v[q + 1] + __shfl_xor(v[q + 1], 32);
+                    v[q] = v[q + 1] = 0.f;
+                    return lane < 32 ? a : b;
+                };
+                float4 t = total[32 * q + lane];
+                t.x += both(tx), t.y += both(ty), t.z += both(tz);
+                if (PHI) t.w += both(tp);
+                total[32 * q + lane] = t;
+            }
+        };
 
+        int fresh = 0;  // steps in the sums
         int blind = 0;  // steps still to be evaluated whole without a test
         for (int base = 0; base < nj; base += 64) {
             const float4 v = p0;
@@ -513,6 +537,10 @@ k_table_near(TableArgs a)
             // (each step is monotone: no pair with the chunk has a smaller |d|^2)
             const bool keep = valid && (whole || r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
             if (!__any(keep)) continue;
+            if (fresh++ == kFreshSteps) {
+                to_total();
+                fresh = 1;
+            }
             wave_sync_tile();  // the previous step's reads are done
             // (dropped, or past the end and so the last record again: without
             // its mass, so that the whole path adds zero for it)
@@ -557,16 +585,8 @@ k_table_near(TableArgs a)
             }
         }
 
-        // both halves' rows, then the waves' shares in order
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            const float sx = tx[q] + __shfl_xor(tx[q], 32), sy = ty[q] + __shfl_xor(ty[q], 32);
-            const float sz = tz[q] + __shfl_xor(tz[q], 32);
-            const float sp = PHI ? tp[q] + __shfl_xor(tp[q], 32) : 0.f;
-            if (lane < 32) tile[32 * q + lane] = make_float4(sx, sy, sz, sp);
-        }
-        __syncthreads();
+        to_total();
+        __syncthreads();  // then the waves' shares in order
         for (int k = tid; k < C * n_i; k += 64 * W) {
             const int c = k / n_i, i = k - c * n_i;
             float r = 0.f;
@@ -741,14 +761,15 @@ TableKernel near_kernel(int nc, bool phi)
 hipError_t launch_table_near(const TableArgs &a, int num_cu, hipStream_t s)
 {
     const bool phi = is_phi(a);
-    // four columns share a record's terms; two give small sets more waves
+    // four columns share a record's terms; two give small sets more waves, and
+    // are what LDS has room for beside the largest tables
     const size_t table = std::max(sizeof(float4), table_lds_bytes(a));
-    const int nc = a.ni >= 32768 ? 4 : 2;
+    const int nc = a.ni >= 32768 && table <= 65536 ? 4 : 2;
     // eight waves and two workgroups to a CU, or sixteen where a large table
     // (or few chunks) leaves room for one
     const int groups = (a.ni + 32 * nc - 1) / (32 * nc);
     const int w = table > 32768 || groups <= num_cu ? 16 : 8;
-    const size_t lds = table + (size_t)w * 32 * nc * sizeof(float4);
+    const size_t lds = table + (size_t)w * (64 + 32 * nc) * sizeof(float4);
     const TableKernel kern = w == 16 ? near_kernel<16>(nc, phi) : near_kernel<8>(nc, phi);
     hipError_t e = allow_dynamic_lds((const void *)kern, lds);
     if (e != hipSuccess) return e;

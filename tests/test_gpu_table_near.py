@@ -310,3 +310,37 @@ def test_last_node_not_finite_where_no_pair_reaches_it(pgh, ctx, variant, with_p
     assert np.isfinite(out).all()
     if with_phi:
         assert np.array_equal(out[3], np.full(ni, float(nj)))
+
+
+def _sum_bound(terms):
+    """Relative error of `terms` FP32 additions of one sign, each off by at
+    most half an ulp of a partial sum no larger than the result."""
+    return terms * 2.0 ** -24
+
+
+@pytest.mark.parametrize("order", ["together", "in turn"])
+@pytest.mark.parametrize("spread", [0.4, 0.75])
+def test_near_sums_do_not_grow_with_the_list(pgh, ctx, order, spread):
+    """10^6 + 3 neighbours of mass 0.7 (spread 0.4: blocks evaluated whole; 0.75:
+    some beyond the cutoff, in candidates' rounds where they are the most), in a
+    row or among as many far ones.  The potential counts them, so each of the terms is the
+    same number and a running sum errs in one direction.  Fresh sums of at most
+    512 terms: 512 + a wave's 62500 / 256 + 16 waves' additions."""
+    n = 1000003
+    rng = np.random.default_rng(4)
+    rcut = 0.5
+    _count_table(pgh, ctx, rcut)
+    pj = (spread * (rng.random((3, n)) - 0.5)).astype(np.float32)
+    if order == "in turn":
+        pj[:, ::2] += np.float32(20.0)
+    pi = (0.02 * (rng.random((3, 64)) - 0.5)).astype(np.float32)
+    fam = pgh.PGH_FAMILY_TABLE_ALLPAIRS
+    names = [pgh.pgh_variant_name(fam, v) for v in range(pgh.pgh_variant_count(fam))]
+    ctx.set_variant(fam, names.index("near"))
+    mass = np.float32(0.7)
+    ctx.set_j(*to_dev(*pj, np.full(n, mass)))
+    phi = to_host(*ctx.table_force(*to_dev(*pi), with_phi=True))[3]
+    want = _counts([(0, 64, 0, n)], pi, pj, rcut) * float(mass)
+    assert want.min() > 5e4
+    e = np.abs(phi - want) / want
+    assert e.max() <= _sum_bound(512 + 62500 / 256 + 16), e.max()
