@@ -43,6 +43,9 @@ constexpr int kStaticRounds = 4;
 // k_batch_table_near evaluates a block of 64 records whole when some lane has
 // more candidates than this among its 2 x 32 pairs
 constexpr int kDirectHits = 24;
+// Records in a lane's sums before these are added to its totals, at least; half
+// of them, as the lane's partner has the others, and up to 64 SB more.
+constexpr int kFreshRows = 512;
 
 // The lanes of one task: lane (phase, row) holds slots q + k stride
 // (k < KI) of its chunk (i-particles i0 + slot, the chunk's partial-sum
@@ -314,8 +317,10 @@ k_batch_table_near(BatchArgs a)
 {
     static_assert(!MOM || !PHI, "moments come without a potential");
     using Entry = std::conditional_t<PHI, float4, float2>;
+    constexpr int TW = MOM ? 3 : 1;  // words of four sums per i-particle
     __shared__ Entry stab[1 << TB];
     __shared__ float4 jt[WPB][64 * SB];
+    __shared__ float4 totals[WPB][TW][64];
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -410,6 +415,7 @@ k_batch_table_near(BatchArgs a)
             const float cx = uniform(whole ? 0.f : 0.5f * (xl + xh)),
                         cy = uniform(whole ? 0.f : 0.5f * (yl + yh)),
                         cz = uniform(whole ? 0.f : 0.5f * (zl + zh));
+            const float cut = uniform(whole ? INFINITY : a.r2max);
             const FilterOps cols =
                 filter_cols_of(ix, iy, iz, lane < n_i, last_zero, cx, cy, cz, a.r2max);
             float px[2], py[2], pz[2];  // of both columns
@@ -418,8 +424,42 @@ k_batch_table_near(BatchArgs a)
             float tm[MOM ? 7 : 1][2];
 #pragma unroll
             for (int c = 0; c < (MOM ? 7 : 1); ++c) tm[c][0] = tm[c][1] = 0.f;
+            // Slot `lane`'s sums over the two halves' rows, which then start
+            // afresh.  Those of a long list go to the lane's words in LDS once
+            // per kFreshRows records evaluated, so that FP32 rounding grows with
+            // these and the number of such sums, not with the list (400000
+            // neighbours of one mass: 2.0e-3 in one running sum).
+            bool long_list = false;
+            int rows = 0;  // in the sums
+            auto take = [&](float4 *v) {
+                auto slot = [&](float *u) {
+                    const float s0 = u[0] + __shfl_xor(u[0], 32), s1 = u[1] + __shfl_xor(u[1], 32);
+                    u[0] = u[1] = 0.f;
+                    return lane < 32 ? s0 : s1;
+                };
+                v[0] = make_float4(slot(tx), slot(ty), slot(tz), PHI ? slot(tp) : 0.f);
+                if constexpr (MOM) {
+                    v[1] = make_float4(slot(tm[0]), slot(tm[1]), slot(tm[2]), slot(tm[3]));
+                    v[2] = make_float4(slot(tm[4]), slot(tm[5]), slot(tm[6]), 0.f);
+                }
+                if (long_list) {
+#pragma unroll
+                    for (int w = 0; w < TW; ++w) {
+                        const float4 o = totals[wave][w][lane];
+                        v[w].x += o.x, v[w].y += o.y, v[w].z += o.z, v[w].w += o.w;
+                    }
+                }
+            };
 
             for (int base = 0; base < n_j; base += 64 * SB) {
+                if (rows >= kFreshRows) {
+                    float4 v[TW];
+                    take(v);
+#pragma unroll
+                    for (int w = 0; w < TW; ++w) totals[wave][w][lane] = v[w];
+                    long_list = true;
+                    rows = 0;
+                }
                 wave_sync();  // the previous tile's reads are done
                 int kept = 0;
 #pragma unroll
@@ -435,7 +475,7 @@ k_batch_table_near(BatchArgs a)
                     const float r2 =
                         __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));
                     const bool keep = base + 64 * s + lane < n_j &&
-                                      (whole || r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
+                                      (r2 < cut || !ordinary(v.x, v.y, v.z, v.w));
                     const unsigned long long who = __ballot(keep);
                     if (keep) {
                         const int k = kept + lanes_below(who);
@@ -445,6 +485,7 @@ k_batch_table_near(BatchArgs a)
                 }
                 wave_sync();
                 if (base + 64 * SB < n_j) load(j_off, n_j, base + 64 * SB);
+                rows += kept;
 
                 for (int k0 = 0; k0 < kept; k0 += 64) {
                     const float4 *rows64 = tile + k0;
@@ -495,23 +536,16 @@ k_batch_table_near(BatchArgs a)
                 }
             }
 
-            // the two halves' rows; lane l then keeps slot l
-            auto slots = [&](const float *v) {
-                const float s0 = v[0] + __shfl_xor(v[0], 32), s1 = v[1] + __shfl_xor(v[1], 32);
-                return lane < 32 ? s0 : s1;
-            };
-            const float ox = slots(tx), oy = slots(ty), oz = slots(tz);
-            const float op = PHI ? slots(tp) : 0.f;
-            float om[MOM ? 7 : 1];
-#pragma unroll
-            for (int c = 0; c < (MOM ? 7 : 1); ++c) om[c] = MOM ? slots(tm[c]) : 0.f;
+            float4 o[TW];
+            take(o);
             if (lane < n_i) {
                 if (tk.n_parts <= 1) {
-                    put(a.ax + i_off, lane, ox);
-                    put(a.ay + i_off, lane, oy);
-                    put(a.az + i_off, lane, oz);
-                    if (PHI) put(a.phi + i_off, lane, op);
+                    put(a.ax + i_off, lane, o[0].x);
+                    put(a.ay + i_off, lane, o[0].y);
+                    put(a.az + i_off, lane, o[0].z);
+                    if (PHI) put(a.phi + i_off, lane, o[0].w);
                     if constexpr (MOM) {
+                        const float om[7] = {o[1].x, o[1].y, o[1].z, o[1].w, o[2].x, o[2].y, o[2].z};
 #pragma unroll
                         for (int c = 0; c < 7; ++c)
                             put(a.mom + (size_t)c * a.ni_total + i_off, lane, om[c]);
@@ -519,10 +553,10 @@ k_batch_table_near(BatchArgs a)
                 } else {
                     // partial sums of one part of a split j-list (k_combine)
                     const size_t q = (size_t)(tk.slot + tk.part) * 64 + (sub ? tk.n_i : 0) + lane;
-                    a.partial[q] = make_float4(ox, oy, oz, op);
+                    a.partial[q] = o[0];
                     if constexpr (MOM) {
-                        a.mpartial[2 * q] = make_float4(om[0], om[1], om[2], om[3]);
-                        a.mpartial[2 * q + 1] = make_float4(om[4], om[5], om[6], 0.f);
+                        a.mpartial[2 * q] = o[1];
+                        a.mpartial[2 * q + 1] = o[2];
                     }
                 }
             }
@@ -576,8 +610,8 @@ TableKernelPick pick_near(int tb, bool phi)
     if (tb <= 12)
         return {phi ? k_batch_table_near<12, true, kMidWaves, 2, false>
                     : k_batch_table_near<12, false, kMidWaves, 2, false>, kMidWaves};
-    return {phi ? k_batch_table_near<13, true, kMidWaves, 2, false>
-                : k_batch_table_near<14, false, kMidWaves, 2, false>, kMidWaves};
+    return {phi ? k_batch_table_near<13, true, kMidWaves, 1, false>
+                : k_batch_table_near<14, false, kMidWaves, 1, false>, kMidWaves};
 }
 
 struct TableBatchVariant {

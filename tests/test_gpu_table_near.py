@@ -344,3 +344,35 @@ def test_near_sums_do_not_grow_with_the_list(pgh, ctx, order, spread):
     assert want.min() > 5e4
     e = np.abs(phi - want) / want
     assert e.max() <= _sum_bound(512 + 62500 / 256 + 16), e.max()
+
+
+@pytest.mark.parametrize("spread", [0.4, 0.75])
+@pytest.mark.parametrize("ni", [1, 40])
+@pytest.mark.parametrize("moments", [False, True])
+def test_batched_sums_do_not_grow_with_the_list(pgh, ctx, spread, ni, moments):
+    """2048 lists over one range of 400000 neighbours of mass 0.7, which a plan
+    does not cut: as above, or S (the moments' first row, sum of m g) where the
+    table itself counts.  Fresh sums of at most 512 terms, added 400000 / 256
+    times, then over two halves."""
+    n, lists = 400000, 2048
+    rng = np.random.default_rng(4)
+    rcut = 0.5
+    _count_table(pgh, ctx, rcut)
+    if moments:
+        t = np.zeros(2 * K, np.float32)
+        t[0:-2:2] = 1.0
+        ctx.set_table(E, F, rcut, to_dev(t)[0])
+    pj = (spread * (rng.random((3, n)) - 0.5)).astype(np.float32)
+    pi = (0.02 * (rng.random((3, ni * lists)) - 0.5)).astype(np.float32)
+    items = np.array([(ni * k, ni, 0, n) for k in range(lists)], np.int32)
+    plan = ctx.plan(items, ni * lists, n)
+    mass = np.float32(0.7)
+    d = to_dev(*pi), to_dev(*pj, np.full(n, mass))
+    if moments:
+        got = to_host(plan.table_moments(*d[0], *d[1])[1])[0][:ni * lists]
+    else:
+        got = to_host(*plan.table(*d[0], *d[1], with_phi=True))[3]
+    rows = np.unique(np.linspace(0, ni * lists - 1, 24).astype(int))
+    want = _counts([(int(r), 1, 0, n) for r in rows], pi, pj, rcut)[rows] * float(mass)
+    e = np.abs(got[rows] - want) / want
+    assert e.max() <= _sum_bound(512 + n / 256 + 2), e.max()
