@@ -62,7 +62,7 @@ struct TaskLanes {
 // KI i-particles per lane, TW j-records per lane per tile (unpaired tasks),
 // 2^TB table entries at most, HT the (H, G1) form, PHI the potential table,
 // WPB waves per workgroup (one table copy per workgroup).
-template <int KI, int TW, int TB, bool HT, bool PHI, int WPB, bool PF>
+template <int KI, int TW, int TB, bool HT, bool PHI, int WPB>
 // eight waves per SIMD whatever the workgroup size (64 VGPRs at most)
 __global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_batch_table(BatchArgs a)
@@ -70,9 +70,7 @@ k_batch_table(BatchArgs a)
     using Entry = std::conditional_t<PHI, float4, float2>;
     constexpr int kEntryLog = PHI ? 4 : 3;
     __shared__ Entry stab[1 << TB];
-    // a wave's j-tile: 128 records and 8 of padding, read (and unused) by
-    // the prefetch after a tile's last step
-    __shared__ float4 jt[WPB][136];
+    __shared__ float4 jt[WPB][128];  // a wave's j-tile
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -210,26 +208,8 @@ k_batch_table(BatchArgs a)
                 auto full = [&](auto stride_c, auto trips_c) {
                     constexpr int S = decltype(stride_c)::value;
                     constexpr int N = decltype(trips_c)::value;
-                    if constexpr (PF) {
-                        // the next record is read before this step's
-                        // table gathers are waited for, so one LDS round
-                        // trip per step remains on the wave's path
-                        float4 p = src[0];
 #pragma unroll 2
-                        for (int it = 0; it < N; ++it) {
-                            TableGather<KI, PHI> q;
-                            table_head<KI, HT, PHI>(p, L.px, L.py, L.pz, tab, kc, q);
-                            const float4 pn = src[(it + 1) * S];
-                            // nothing of the sums moves above the next
-                            // record's read
-                            __builtin_amdgcn_sched_barrier(0);
-                            table_tail<KI, PHI>(p.w, q, tx, ty, tz, tp);
-                            p = pn;
-                        }
-                    } else {
-#pragma unroll 2
-                        for (int it = 0; it < N; ++it) step(src[it * S]);
-                    }
+                    for (int it = 0; it < N; ++it) step(src[it * S]);
                 };
                 using std::integral_constant;
                 if (L.paired) {
@@ -574,44 +554,45 @@ using TableKernel = void (*)(BatchArgs);
 // A kernel of a variant for a table of 2^tb nodes, and its waves per
 // workgroup.  The table's LDS bounds the workgroups per CU, so larger tables
 // take wider workgroups whatever the variant's own width: up to 2^10 nodes
-// the variant's; up to 2^12 (32 KiB, 64 KiB with the potential) 16 waves,
-// two workgroups per CU (one with the potential); beyond (128 KiB at 2^14,
-// or at 2^13 with the potential) 12 waves, the most whose j-tiles (2176
-// bytes each) fit beside the table in the 160 KiB of a CU.  With its own two
-// waves per workgroup a variant would leave SIMDs idle there.
-constexpr int kMidWaves = 16;
-constexpr int kWideWaves = 12;
+// the variant's; beyond 16 waves, two workgroups per CU up to 2^12 (32 KiB; one
+// with the potential, 64 KiB), one beside the largest tables (128 KiB at 2^14,
+// or at 2^13 with the potential), where 16 j-tiles of 2 KiB fill the 160 KiB of a
+// CU.  With its own two waves per workgroup a variant would leave SIMDs idle
+// there.
+constexpr int kWideWaves = 16;
 
 struct TableKernelPick {
     TableKernel k;
     int wpb;
 };
 
-template <int KI, int TW, bool HT, int WPB, bool PF = false>
+template <int KI, int TW, bool HT, int WPB>
 TableKernelPick pick(int tb, bool phi)
 {
     if (tb <= 10)
-        return {phi ? k_batch_table<KI, TW, 10, HT, true, WPB, PF>
-                    : k_batch_table<KI, TW, 10, HT, false, WPB, PF>, WPB};
+        return {phi ? k_batch_table<KI, TW, 10, HT, true, WPB>
+                    : k_batch_table<KI, TW, 10, HT, false, WPB>, WPB};
     if (tb <= 12)
-        return {phi ? k_batch_table<KI, TW, 12, HT, true, kMidWaves, PF>
-                    : k_batch_table<KI, TW, 12, HT, false, kMidWaves, PF>, kMidWaves};
-    return {phi ? k_batch_table<KI, TW, 13, HT, true, kWideWaves, PF>
-                : k_batch_table<KI, TW, 14, HT, false, kWideWaves, PF>, kWideWaves};
+        return {phi ? k_batch_table<KI, TW, 12, HT, true, kWideWaves>
+                    : k_batch_table<KI, TW, 12, HT, false, kWideWaves>, kWideWaves};
+    return {phi ? k_batch_table<KI, TW, 13, HT, true, kWideWaves>
+                : k_batch_table<KI, TW, 14, HT, false, kWideWaves>, kWideWaves};
 }
 
 // The variant that finds the pairs inside the cutoff first: two columns of
-// i-particles per lane, two rows of records per tile, four waves.
+// i-particles per lane, as many records per lane and tile (SB) as registers and,
+// beside the largest tables, LDS leave room for, four waves (16 beside tables of
+// more than 2^10 nodes).
 TableKernelPick pick_near(int tb, bool phi)
 {
     if (tb <= 10)
         return {phi ? k_batch_table_near<10, true, 4, 2, false>
                     : k_batch_table_near<10, false, 4, 4, false>, 4};
     if (tb <= 12)
-        return {phi ? k_batch_table_near<12, true, kMidWaves, 2, false>
-                    : k_batch_table_near<12, false, kMidWaves, 2, false>, kMidWaves};
-    return {phi ? k_batch_table_near<13, true, kMidWaves, 1, false>
-                : k_batch_table_near<14, false, kMidWaves, 1, false>, kMidWaves};
+        return {phi ? k_batch_table_near<12, true, kWideWaves, 2, false>
+                    : k_batch_table_near<12, false, kWideWaves, 2, false>, kWideWaves};
+    return {phi ? k_batch_table_near<13, true, kWideWaves, 1, false>
+                : k_batch_table_near<14, false, kWideWaves, 1, false>, kWideWaves};
 }
 
 struct TableBatchVariant {
@@ -621,8 +602,8 @@ struct TableBatchVariant {
 };
 
 // The tile shapes the autotuner chooses among: i-particles per lane (KI),
-// j-records per lane per tile (TW), waves per workgroup, the one-record
-// prefetch (pf) and the table form.  The "htab" variants keep the (H, G1)
+// j-records per lane per tile (TW), waves per workgroup, the table form, and "near", which evaluates the pairs inside
+// the cutoff only.  The "htab" variants keep the (H, G1)
 // form in LDS (two instructions fewer per pair): the same interpolant with
 // one more FP32 rounding per node, of H_k = G0_k - G1_k s_k, which is
 // relative to G1_k s_k rather than to g; near rcut, where g goes to zero,
@@ -632,14 +613,15 @@ struct TableBatchVariant {
 const TableBatchVariant kTableBatchVariants[] = {
     {"ki=1 tw=1 wg=4", 4, pick<1, 1, false, 4>},
     {"ki=2 tw=1 wg=4", 4, pick<2, 1, false, 4>},
-    {"ki=2 tw=2 wg=4", 4, pick_near},
+    {"ki=2 tw=2 wg=4", 4, pick<2, 2, false, 4>},
     {"ki=1 tw=1 wg=16", 16, pick<1, 1, false, 16>},
     {"ki=2 tw=2 wg=16", 16, pick<2, 2, false, 16>},
-    {"ki=1 tw=1 wg=4 pf", 4, pick<1, 1, false, 4, true>},
+    {"near", 4, pick_near},
     {"ki=2 tw=1 wg=4 htab", 4, pick<2, 1, true, 4>},
     {"ki=2 tw=2 wg=4 htab", 4, pick<2, 2, true, 4>},
     {"ki=2 tw=2 wg=2 htab", 2, pick<2, 2, true, 2>},
 };
+constexpr int kNearVariant = 5;
 constexpr int kNumTableBatchVariants = sizeof(kTableBatchVariants) / sizeof(kTableBatchVariants[0]);
 
 int resident_blocks(TableKernel k, int wpb)
@@ -665,9 +647,9 @@ const char *table_batch_variant_name(int v)
     return (v >= 0 && v < kNumTableBatchVariants) ? kTableBatchVariants[v].name : nullptr;
 }
 
-int table_batch_default() { return 2; }
+int table_batch_default() { return kNearVariant; }
 
-bool table_batch_near(int v) { return v == 2; }
+bool table_batch_near(int v) { return v == kNearVariant; }
 
 // The pair-slot figures of set_wave_prio: a quarter of the plan's
 // interactions per wave of the launch, and its mean task.
@@ -682,10 +664,10 @@ hipError_t launch_table_batch_moments(const BatchArgs &a0, int num_cu, hipStream
 {
     if (a0.n_tasks <= 0) return hipSuccess;
     const int tb = a0.E + a0.F;
-    const int wpb = tb <= 10 ? 4 : kMidWaves;
+    const int wpb = tb <= 10 ? 4 : kWideWaves;
     const TableKernel k = tb <= 10   ? k_batch_table_near<10, false, 4, 4, true>
-                          : tb <= 12 ? k_batch_table_near<12, false, kMidWaves, 2, true>
-                                     : k_batch_table_near<13, false, kMidWaves, 2, true>;
+                          : tb <= 12 ? k_batch_table_near<12, false, kWideWaves, 2, true>
+                                     : k_batch_table_near<13, false, kWideWaves, 2, true>;
     BatchArgs a = a0;
     a.phi = nullptr;
     a.ptable = nullptr;

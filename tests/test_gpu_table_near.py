@@ -376,3 +376,24 @@ def test_batched_sums_do_not_grow_with_the_list(pgh, ctx, spread, ni, moments):
     want = _counts([(int(r), 1, 0, n) for r in rows], pi, pj, rcut)[rows] * float(mass)
     e = np.abs(got[rows] - want) / want
     assert e.max() <= _sum_bound(512 + n / 256 + 2), e.max()
+
+
+def test_every_variant_is_the_kernel_its_name_says(pgh, ctx):
+    """Tuning files hold variants by name: the paper's form with two i-particles
+    per lane and two records per tile sums in one order, bit for bit, whatever
+    the workgroup's width, and "near" is another kernel, the built-in choice here."""
+    items, pi, pj = _lists(np.random.default_rng(9), np.zeros(3), 0.3, True)
+    ctx.build_table(E, F, 0.05, eps=0.05 / 15)
+    m = np.random.default_rng(2).uniform(0.5, 1.5, pj.shape[1]).astype(np.float32)
+    fam = pgh.PGH_FAMILY_TABLE_BATCH
+    names = [pgh.pgh_variant_name(fam, v) for v in range(pgh.pgh_variant_count(fam))]
+    d = to_dev(*pi), to_dev(*pj, m)
+    plan = ctx.plan(items, pi.shape[1], pj.shape[1])
+    out = {}
+    for v in ("ki=2 tw=2 wg=4", "ki=2 tw=2 wg=16", "near", None):
+        ctx.set_variant(fam, -1 if v is None else names.index(v))
+        zero = to_dev(*np.zeros((3, pi.shape[1])))
+        out[v] = np.stack(to_host(*plan.table(*d[0], *d[1], out=zero)))
+    assert np.array_equal(out["ki=2 tw=2 wg=4"], out["ki=2 tw=2 wg=16"])
+    assert np.array_equal(out["near"], out[None])
+    assert not np.array_equal(out["near"], out["ki=2 tw=2 wg=4"])
