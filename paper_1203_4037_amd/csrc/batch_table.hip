@@ -41,8 +41,10 @@ namespace {
 // plans of at most this many tasks per wave run in the static order
 constexpr int kStaticRounds = 4;
 // k_batch_table_near evaluates a block of 64 records whole when some lane has
-// more candidates than this among its 2 x 32 pairs
-constexpr int kDirectHits = 24;
+// more candidates than this among its 2 x 32 pairs, or its 32 of a single column
+// (which break even at a quarter of the pairs inside: 4096 lists of 32 x 1500
+// 97 us with 12 of 32, 76 with 18).
+constexpr int kDirectHits = 24, kDirectHits1 = 18;
 // Records in a lane's sums before these are added to its totals, at least; half
 // of them, as the lane's partner has the others, and up to 64 SB more.
 constexpr int kFreshRows = 512;
@@ -61,12 +63,15 @@ struct TaskLanes {
 
 // KI i-particles per lane, TW j-records per lane per tile (unpaired tasks),
 // 2^TB table entries at most, HT the (H, G1) form, PHI the potential table,
-// WPB waves per workgroup (one table copy per workgroup).
-template <int KI, int TW, int TB, bool HT, bool PHI, int WPB>
+// WPB waves per workgroup (one table copy per workgroup), MOM also the i-side
+// moments of the adjoint (table_tail_mom; the paper's form, no potential).
+template <int KI, int TW, int TB, bool HT, bool PHI, int WPB, bool MOM = false>
 // eight waves per SIMD whatever the workgroup size (64 VGPRs at most)
 __global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_batch_table(BatchArgs a)
 {
+    static_assert(!MOM || (!HT && !PHI), "moments take the paper's form, no potential");
+    constexpr int M = MOM ? 7 : 1;
     using Entry = std::conditional_t<PHI, float4, float2>;
     constexpr int kEntryLog = PHI ? 4 : 3;
     __shared__ Entry stab[1 << TB];
@@ -184,6 +189,9 @@ k_batch_table(BatchArgs a)
         float tx[KI], ty[KI], tz[KI], tp[KI];
 #pragma unroll
         for (int k = 0; k < KI; ++k) tx[k] = ty[k] = tz[k] = tp[k] = 0.f;
+        float tm[M][KI];
+#pragma unroll
+        for (int c = 0; c < M * KI; ++c) tm[c / KI][c % KI] = 0.f;
         const float4 *src = tile + (L.second ? 64 : 0) + L.phase;
         // the wave's static tasks after this one (round is this task's + 1)
         const unsigned more = stat ? rounds_g - round : 0u;
@@ -200,7 +208,10 @@ k_batch_table(BatchArgs a)
             if (tl + 1 < L.ntiles) load(tk, L, tl + 1);
             const int cnt = min(L.T, L.nj - tl * L.T);
             auto step = [&](const float4 p) {
-                table_pairs_v<KI, HT, PHI>(p, L.px, L.py, L.pz, tab, kc, tx, ty, tz, tp);
+                if constexpr (MOM)
+                    table_pairs_mom<KI>(p, L.px, L.py, L.pz, tab, kc, tx, ty, tz, tm);
+                else
+                    table_pairs_v<KI, HT, PHI>(p, L.px, L.py, L.pz, tab, kc, tx, ty, tz, tp);
             };
             if (cnt == L.T) {
                 // a full tile: T / P records per lane with a compile-time
@@ -236,6 +247,9 @@ k_batch_table(BatchArgs a)
                 ty[k] += __shfl_xor(ty[k], d);
                 tz[k] += __shfl_xor(tz[k], d);
                 if (PHI) tp[k] += __shfl_xor(tp[k], d);
+                if constexpr (MOM)
+#pragma unroll
+                    for (int c = 0; c < 7; ++c) tm[c][k] += __shfl_xor(tm[c][k], d);
             }
         }
         if (L.phase == 0) {
@@ -249,11 +263,18 @@ k_batch_table(BatchArgs a)
                     a.ay[i] = ty[k];
                     a.az[i] = tz[k];
                     if (PHI) a.phi[i] = tp[k];
+                    if constexpr (MOM)
+#pragma unroll
+                        for (int c = 0; c < 7; ++c) a.mom[(size_t)c * a.ni_total + i] = tm[c][k];
                 } else {
                     // partial sums of one part of a split j-list; k_combine
                     // adds the parts of the chunk in order after this launch
                     const size_t at = (size_t)(tk.slot + tk.part) * 64 + L.lane0 + slot;
                     a.partial[at] = make_float4(tx[k], ty[k], tz[k], tp[k]);
+                    if constexpr (MOM) {
+                        a.mpartial[2 * at] = make_float4(tm[0][k], tm[1][k], tm[2][k], tm[3][k]);
+                        a.mpartial[2 * at + 1] = make_float4(tm[4][k], tm[5][k], tm[6][k], 0.f);
+                    }
                 }
             }
         }
@@ -410,7 +431,7 @@ k_batch_table_near(BatchArgs a)
             // these and the number of such sums, not with the list (400000
             // neighbours of one mass: 2.0e-3 in one running sum).
             bool long_list = false;
-            int rows = 0;  // in the sums
+            int summed = 0;  // records in the sums
             auto take = [&](float4 *v) {
                 auto slot = [&](float *u) {
                     const float s0 = u[0] + __shfl_xor(u[0], 32), s1 = u[1] + __shfl_xor(u[1], 32);
@@ -432,13 +453,13 @@ k_batch_table_near(BatchArgs a)
             };
 
             for (int base = 0; base < n_j; base += 64 * SB) {
-                if (rows >= kFreshRows) {
+                if (summed >= kFreshRows) {
                     float4 v[TW];
                     take(v);
 #pragma unroll
                     for (int w = 0; w < TW; ++w) totals[wave][w][lane] = v[w];
                     long_list = true;
-                    rows = 0;
+                    summed = 0;
                 }
                 wave_sync();  // the previous tile's reads are done
                 int kept = 0;
@@ -465,29 +486,44 @@ k_batch_table_near(BatchArgs a)
                 }
                 wave_sync();
                 if (base + 64 * SB < n_j) load(j_off, n_j, base + 64 * SB);
-                rows += kept;
+                summed += kept;
 
                 for (int k0 = 0; k0 < kept; k0 += 64) {
                     const float4 *rows64 = tile + k0;
                     const bool valid = k0 + lane < kept;
-                    const FilterOps rows = filter_rows_of(rows64[filter_slot(lane)], valid, cx, cy, cz);
+                    const FilterOps rows =
+                        filter_rows_of(rows64[filter_slot(lane)], valid, cx, cy, cz);
                     const unsigned m0 = filter_mask(rows, cols.t[0]);
                     unsigned m1 = 0;
                     if (n_i > 32) m1 = filter_mask(rows, cols.t[1]);
                     const float4 *mine = rows64 + (lane & 32);  // this half's rows
-                    if (__any(__popc(m0) + __popc(m1) > kDirectHits)) {
+                    if (__any(__popc(m0) + __popc(m1) > (n_i > 32 ? kDirectHits : kDirectHits1))) {
                         // rows past the last kept one are made far away, massless
                         if (!valid)
                             tile[k0 + filter_slot(lane)] = make_float4(kFar, kFar, kFar, 0.f);
                         wave_sync();
                         const TableConsts kd = table_consts(a.c, a.smax, a.E, a.F, PHI ? 4 : 3);
-#pragma unroll 1
-                        for (int p = 0; p < 32; ++p) {
-                            if constexpr (MOM)
-                                table_pairs_mom<2>(mine[p], px, py, pz, tab, kd, tx, ty, tz, tm);
-                            else
-                                table_pairs_v<2, false, PHI>(mine[p], px, py, pz, tab, kd, tx, ty,
-                                                             tz, tp);
+                        auto pairs = [&](const float4 r, auto n) {
+                            constexpr int N = decltype(n)::value;
+                            if constexpr (MOM) {
+                                float sm[7][N];
+#pragma unroll
+                                for (int c = 0; c < 7 * N; ++c) sm[c / N][c % N] = tm[c / N][c % N];
+                                table_pairs_mom<N>(r, px, py, pz, tab, kd, tx, ty, tz, sm);
+#pragma unroll
+                                for (int c = 0; c < 7 * N; ++c) tm[c / N][c % N] = sm[c / N][c % N];
+                            } else {
+                                table_pairs_v<N, false, PHI>(r, px, py, pz, tab, kd, tx, ty, tz, tp);
+                            }
+                        };
+                        if (n_i > 32) {
+#pragma unroll MOM ? 1 : 2
+                            for (int p = 0; p < 32; ++p)
+                                pairs(mine[p], std::integral_constant<int, 2>{});
+                        } else {
+#pragma unroll MOM ? 2 : 4
+                            for (int p = 0; p < 32; ++p)
+                                pairs(mine[p], std::integral_constant<int, 1>{});
                         }
                         continue;
                     }
@@ -621,7 +657,7 @@ const TableBatchVariant kTableBatchVariants[] = {
     {"ki=2 tw=2 wg=4 htab", 4, pick<2, 2, true, 4>},
     {"ki=2 tw=2 wg=2 htab", 2, pick<2, 2, true, 2>},
 };
-constexpr int kNearVariant = 5;
+constexpr int kPaperVariant = 2, kNearVariant = 5;
 constexpr int kNumTableBatchVariants = sizeof(kTableBatchVariants) / sizeof(kTableBatchVariants[0]);
 
 int resident_blocks(TableKernel k, int wpb)
@@ -632,8 +668,14 @@ int resident_blocks(TableKernel k, int wpb)
     auto it = cache.find((const void *)k);
     if (it != cache.end()) return it->second;
     int n = 0;
+    hipFuncAttributes f{};
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, 64 * wpb, 0) != hipSuccess || n < 1)
         n = 1;
+    // LDS is given out in steps of 1280 bytes, which that count may not know: a
+    // workgroup too many per CU runs after all others (moments of 20000 lists of 8 x
+    // 300, 12288 bytes of LDS: 13 workgroups 84 us, 12 60 us)
+    if (hipFuncGetAttributes(&f, (const void *)k) == hipSuccess && f.sharedSizeBytes > 0)
+        n = std::max(1, std::min(n, 163840 / (((int)f.sharedSizeBytes + 1279) / 1280 * 1280)));
     cache[(const void *)k] = n;
     return n;
 }
@@ -647,7 +689,21 @@ const char *table_batch_variant_name(int v)
     return (v >= 0 && v < kNumTableBatchVariants) ? kTableBatchVariants[v].name : nullptr;
 }
 
-int table_batch_default() { return kNearVariant; }
+// The near kernel pays per list entry and column of 32 i-particles, whatever the
+// chunk holds and wherever most pairs are; k_batch_table gives a chunk of at most
+// 16 four times the lanes.  us a call of 4096 lists of n_i x 1500 with 1, 10, 25 and
+// 100% of the pairs inside, k_batch_table (alike for all) and near: n_i = 8 42: 32,
+// 53, 72, 105; 16 45: 35, 56, 73, 104; 24 75: 38, 58, 75, 105; 32 75: 38, 58, 76, 105;
+// 64 140: 49, 87, 148, 174; 200 400: 155, 264, 410, 575.  So lists of few i-particles,
+// as of single cells, take the former: up to 1.3 times the time with hardly
+// any pair inside, never 2.5 times with many.  Which pairs are inside isn't
+// known before the call: for lists of more i-particles the near kernel costs
+// 1.25 to 1.4 times the other's time where half of the pairs or more are (or a table
+// whose last node is not zero makes every pair count), against 2 times less with
+// one in a hundred; the tuner (pgh_autotune_plan) tells.
+bool table_batch_few(long long n_rows, long long n_chunks) { return n_rows <= 16 * n_chunks; }
+
+int table_batch_default(bool few) { return few ? kPaperVariant : kNearVariant; }
 
 bool table_batch_near(int v) { return v == kNearVariant; }
 
@@ -660,14 +716,20 @@ static void set_prio_args(BatchArgs &a)
     a.prio_task = inter / (unsigned long long)std::max(1, a.n_tasks);
 }
 
-hipError_t launch_table_batch_moments(const BatchArgs &a0, int num_cu, hipStream_t s)
+hipError_t launch_table_batch_moments(const BatchArgs &a0, bool few, int num_cu, hipStream_t s)
 {
     if (a0.n_tasks <= 0) return hipSuccess;
     const int tb = a0.E + a0.F;
-    const int wpb = tb <= 10 ? 4 : kWideWaves;
-    const TableKernel k = tb <= 10   ? k_batch_table_near<10, false, 4, 4, true>
-                          : tb <= 12 ? k_batch_table_near<12, false, kWideWaves, 2, true>
-                                     : k_batch_table_near<13, false, kWideWaves, 2, true>;
+    // (k_batch_table here with one i-particle per lane, as the seven moments
+    // take registers, and for small tables two waves per workgroup, six per SIMD)
+    const int wpb = tb <= 10 ? few ? 2 : 4 : kWideWaves;
+    const TableKernel k =
+        few ? tb <= 10   ? k_batch_table<1, 2, 10, false, false, 2, true>
+              : tb <= 12 ? k_batch_table<1, 2, 12, false, false, kWideWaves, true>
+                         : k_batch_table<1, 2, 13, false, false, kWideWaves, true>
+        : tb <= 10 ? k_batch_table_near<10, false, 4, 4, true>
+        : tb <= 12 ? k_batch_table_near<12, false, kWideWaves, 2, true>
+                   : k_batch_table_near<13, false, kWideWaves, 2, true>;
     BatchArgs a = a0;
     a.phi = nullptr;
     a.ptable = nullptr;
@@ -685,7 +747,7 @@ hipError_t launch_table_batch_moments(const BatchArgs &a0, int num_cu, hipStream
 hipError_t launch_table_batch(const BatchArgs &a0, int variant, int num_cu, hipStream_t s)
 {
     if (a0.n_tasks <= 0) return hipSuccess;
-    if (variant < 0 || variant >= kNumTableBatchVariants) variant = table_batch_default();
+    if (variant < 0 || variant >= kNumTableBatchVariants) variant = kNearVariant;
     const bool phi = a0.phi && a0.ptable;
     const TableKernelPick pk = kTableBatchVariants[variant].pick(a0.E + a0.F, phi);
     const TableKernel k = pk.k;

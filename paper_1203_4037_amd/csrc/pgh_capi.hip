@@ -67,6 +67,7 @@ struct pgh_plan {
     bool i_cover, j_cover;
     // every i-row is in exactly one i-major task of the table adjoint
     bool i_once;
+    bool few;  // few i-particles per chunk (table_batch_few)
     NearList near;
     // partial moments of split chunks (pgh_batch_table_moments), grown on
     // its first call on the plan: two float4 per partial sum
@@ -410,6 +411,9 @@ void set_plan_counts(pgh_plan *p, int n_items, int ni_total, int nj_total, int n
     p->n_chunks = n_split;
     p->n_slots = n_slots;
     p->ordered = ordered;
+    long long rows = 0, chunks = 0;
+    for (const pgh_item &it : ordered) rows += it.n_i, chunks += (it.n_i + 63) / 64;
+    p->few = table_batch_few(rows, chunks);
 }
 
 // The wave count the planner cuts work for: the context's setting, else the
@@ -505,8 +509,8 @@ int plan_fill(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items, int n
     set_plan_counts(p, n_items, ni_total, nj_total, (int)n_t, hp.nq, hp.q_begin, hp.interactions,
                     (int)n_c, hp.n_slots, hp.ordered);
     // chunks of less than 64 suit the other kernels only (a tree's lists are
-    // for the Newton force)
-    if (c->hp.chunk < 64 && !p->tree_owned) return near_fill(c, p, n_items, items, ni_total, nj_total);
+    // for the Newton force, lists of few i-particles for k_batch_table)
+    if (c->hp.chunk < 64 && !p->tree_owned && !p->few) return near_fill(c, p, n_items, items, ni_total, nj_total);
     return PGH_OK;
 }
 
@@ -1253,7 +1257,7 @@ int pgh_batch_table(pgh_ctx *c, const pgh_plan *p, const float *xi, const float 
     a.smax = (float)smax;
     a.r2max = table_r2max(a.c, smax);
     int v = c->variant[PGH_FAMILY_TABLE_BATCH];
-    if (v < 0) v = table_batch_default();
+    if (v < 0) v = table_batch_default(p->few);
     if (table_batch_near(v)) use_near_list(a, p);
     PGH_HIP(c, launch_table_batch(a, v, c->num_cu, c->stream));
     return PGH_OK;
@@ -1293,11 +1297,11 @@ int pgh_batch_table_moments(pgh_ctx *c, pgh_plan *p, const float *xi, const floa
     a.c = table_scale(smax, c->tab_rcut);
     a.smax = (float)smax;
     a.r2max = table_r2max(a.c, smax);
-    use_near_list(a, p);
+    if (!p->few) use_near_list(a, p);
     a.mom = mom;
     a.mpartial = p->mpartial;
     a.ni_total = p->ni_total;
-    PGH_HIP(c, launch_table_batch_moments(a, c->num_cu, c->stream));
+    PGH_HIP(c, launch_table_batch_moments(a, p->few, c->num_cu, c->stream));
     return PGH_OK;
 }
 

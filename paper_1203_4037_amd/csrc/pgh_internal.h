@@ -199,7 +199,10 @@ int newton_batch_variants();
 const char *newton_batch_variant_name(int v);
 int table_batch_variants();
 const char *table_batch_variant_name(int v);
-int table_batch_default();  // the variant used when none is chosen
+// whether a plan of n_rows i-particles in n_chunks chunks of 64 has few in a chunk, and
+// the variant used when none is chosen
+bool table_batch_few(long long n_rows, long long n_chunks);
+int table_batch_default(bool few);
 bool table_batch_near(int v);  // whether variant v leaves out the pairs beyond the cutoff
 // k_combine over the split chunks of a batched launch (after it, same stream)
 hipError_t launch_combine(const BatchArgs &a, bool phi, hipStream_t s);
@@ -228,7 +231,7 @@ hipError_t launch_newton_batch(const BatchArgs &a, int variant, bool refine, boo
 hipError_t launch_table_batch(const BatchArgs &a, int variant, int num_cu, hipStream_t s);
 // The table force with the i-side moments of its adjoint (a.mom, a.mpartial
 // set; one i-particle per lane, the paper's (G0, G1) form).
-hipError_t launch_table_batch_moments(const BatchArgs &a, int num_cu, hipStream_t s);
+hipError_t launch_table_batch_moments(const BatchArgs &a, bool few, int num_cu, hipStream_t s);
 
 // Records of two float4: (x, y, z, s or s_all) and (wx, wy, wz, 0).
 hipError_t launch_pack_xw(int n, const float *x, const float *y, const float *z, const float *s,

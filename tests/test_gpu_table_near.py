@@ -397,3 +397,32 @@ def test_every_variant_is_the_kernel_its_name_says(pgh, ctx):
     assert np.array_equal(out["ki=2 tw=2 wg=4"], out["ki=2 tw=2 wg=16"])
     assert np.array_equal(out["near"], out[None])
     assert not np.array_equal(out["near"], out["ki=2 tw=2 wg=4"])
+
+
+# both sides of the built-in choice (16 i-particles per chunk on average), one and two
+# columns, and the numbers of pairs inside at which blocks are evaluated whole
+@pytest.mark.parametrize("n_i", [1, 8, 15, 16, 17, 32, 33, 64, 80])
+@pytest.mark.parametrize("rcut", [0.06, 0.35, 0.5, 4.0])
+@pytest.mark.parametrize("waves", [0, 16])
+def test_lists_of_one_size_count(pgh, ctx, n_i, rcut, waves):
+    """The neighbour counts, exact integers, of lists of one group size, from the
+    potential and from the moments of a table that counts."""
+    rng = np.random.default_rng(n_i)
+    sizes_j = [0, 1, 63, 64, 65, 130, 257, 900] * 4
+    items, j0 = [], 0
+    for k, b in enumerate(sizes_j):
+        items.append((n_i * k, n_i, j0, b))
+        j0 += b
+    items = np.array(items, np.int32)
+    ni = n_i * len(sizes_j)
+    pi, pj = rng.random((3, ni)).astype(np.float32), rng.random((3, j0)).astype(np.float32)
+    _count_table(pgh, ctx, rcut)
+    ctx.set_plan_waves(waves)
+    plan = ctx.plan(items, ni, j0)
+    d = to_dev(*pi), to_dev(*pj, np.ones(j0, np.float32))
+    want = _counts(items, pi, pj, rcut)
+    assert np.array_equal(to_host(*plan.table(*d[0], *d[1], with_phi=True))[3], want)
+    t = np.zeros(2 * K, np.float32)
+    t[0:-2:2] = 1.0
+    ctx.set_table(E, F, rcut, to_dev(t)[0])
+    assert np.array_equal(to_host(plan.table_moments(*d[0], *d[1])[1])[0][:ni], want)
