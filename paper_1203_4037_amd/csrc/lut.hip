@@ -563,7 +563,7 @@ k_table_near(TableArgs a)
             if (direct) {
                 --blind;
                 const TableConsts kd = table_consts(a.c, a.smax, a.E, a.F, PHI ? 4 : 3);
-#pragma unroll 2
+#pragma unroll (NC == 2 ? 4 : 2)
                 for (int p = 0; p < 32; ++p)
                     table_pairs_v<NC, false, PHI>(mine[p], px, py, pz, tab, kd, tx, ty, tz, tp);
                 continue;
@@ -658,11 +658,13 @@ size_t table_lds_bytes(const TableArgs &a)
 //     i-particles leaves CUs idle (N = 5500: 42 -> 15 us, 42 -> 18; 8192: 29.6 ->
 //     24.9, 30.0 -> 29.0; 5000 x 20000 54 -> 34, 55 -> 44), and for few
 //     i-particles;
-//   * k_table_near above, for at least 8192 x 4096 (N = 16384 81 -> 28, 83 -> 89);
-//     from 4 x 10^8 pairs on, where every pair inside would cost it more than
-//     the 9 us of k_table_density and a launch that returns at once,
-//     k_table_density picks k_table_near or k_table_allpairs on the device
-//     (N = 32768 277 -> 86, 302 -> 308; 65536 1097 -> 292, 1196 -> 1203);
+//   * k_table_near above, for at least 8192 x 4096 (N = 10240 50 -> 21, 50 -> 63;
+//     16384 88 -> 28, 94 -> 98); from as many i-particles on as give each CU more
+//     than one chunk, or 4 x 10^8 pairs, every pair inside would cost it far more
+//     than the 8 us of k_table_density and the launches that return at once
+//     (N = 20000 144 -> 59, 155 -> 237), and k_table_density picks k_table_near
+//     or k_table_allpairs on the device (20000 144 -> 68, 155 -> 152; 32768 300
+//     -> 88, 325 -> 331; 65536 1097 -> 292, 1196 -> 1203);
 //   * k_table_allpairs otherwise (3000 x 60000: 67 us, both others 63 and 78).
 constexpr int kAutoVariant = kNumTableVariants;
 
@@ -675,7 +677,10 @@ AutoKernel auto_kernel(int ni, int nj)
     return ni >= 8192 && nj >= 4096 ? AutoKernel::near : AutoKernel::allpairs;
 }
 
-bool auto_decides(int ni, int nj) { return (double)ni * nj >= 4.0e8; }
+bool auto_decides(int ni, int nj, int num_cu)
+{
+    return ni > 64 * num_cu || (double)ni * nj >= 4.0e8;
+}
 
 // k_table_allpairs' variant: two i-particles per lane once these fill the CUs
 int allpairs_variant(int ni, int num_cu)
@@ -705,7 +710,7 @@ int table_allpairs_split(const TableArgs &a, int variant, int num_cu, size_t par
     if (variant == kAutoVariant) {
         const AutoKernel k = auto_kernel(a.ni, a.nj);
         if (k == AutoKernel::rows) return rows_split(a, part_cap);
-        if (k == AutoKernel::near && !auto_decides(a.ni, a.nj)) return 1;
+        if (k == AutoKernel::near && !auto_decides(a.ni, a.nj, num_cu)) return 1;
         variant = allpairs_variant(a.ni, num_cu);
     }
     if (variant == kNearVariant) return 1;
@@ -795,7 +800,7 @@ hipError_t launch_table_allpairs(const TableArgs &a0, int variant, int S, int nu
         variant = k == AutoKernel::rows   ? kRowsVariant
                   : k == AutoKernel::near ? kNearVariant
                                           : allpairs_variant(a.ni, num_cu);
-        if (k == AutoKernel::near && auto_decides(a.ni, a.nj)) {
+        if (k == AutoKernel::near && auto_decides(a.ni, a.nj, num_cu)) {
             a.dense = dense;
             hipLaunchKernelGGL(phi ? k_table_density<true> : k_table_density<false>, dim3(1),
                                dim3(1024), 0, s, a, dense);

@@ -426,3 +426,10 @@ def test_lists_of_one_size_count(pgh, ctx, n_i, rcut, waves):
     t[0:-2:2] = 1.0
     ctx.set_table(E, F, rcut, to_dev(t)[0])
     assert np.array_equal(to_host(plan.table_moments(*d[0], *d[1])[1])[0][:ni], want)
+
+
+# about as many chunks as CUs, where the choice begins to be made on the device
+@pytest.mark.parametrize("ni,nj", [(16384, 7000), (16385, 7000), (16385, 24500)])
+@pytest.mark.parametrize("rcut", [0.03, 0.4])
+def test_all_pairs_counts_where_the_device_begins_to_choose(pgh, ctx, ni, nj, rcut):
+    test_all_pairs_counts_of_the_near_kernel(pgh, ctx, ni, nj, None, rcut)
