@@ -424,7 +424,8 @@ int planner_waves(const pgh_ctx *c)
 }
 
 // The task list of k_batch_table_near for a plan made on the host: the same
-// items cut by kNearRule.  Synchronous.
+// items cut by kNearRule.  Synchronous.  The plan can do without: where there is no
+// memory for it the kernel takes the plan's own list.
 int near_fill(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items, int ni_total,
               int nj_total)
 {
@@ -441,12 +442,12 @@ int near_fill(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items, int n
     const size_t part_bytes = (size_t)hp.n_slots * 64 * sizeof(float4);
     const size_t up_bytes = queue_bytes + n_t * sizeof(Task) + n_c * sizeof(SplitChunk);
     NearList &l = p->near;
-    if (hipMalloc((void **)&l.block, part_bytes + up_bytes) != hipSuccess) {
-        l.block = nullptr;
-        return fail(c, PGH_ENOMEM, "hipMalloc(table task list) failed");
+    if (hipMalloc((void **)&l.block, part_bytes + up_bytes) != hipSuccess ||
+        ensure_pinned(c, up_bytes) != PGH_OK) {
+        (void)hipGetLastError();  // not the launches' error
+        free_near(p);
+        return PGH_OK;
     }
-    st = ensure_pinned(c, up_bytes);
-    if (st) return st;
     char *pin = (char *)c->pin, *up = l.block + part_bytes;
     std::memset(pin, 0, queue_bytes);
     write_tasks(hp, (Task *)(pin + queue_bytes));
@@ -510,7 +511,11 @@ int plan_fill(pgh_ctx *c, pgh_plan *p, int n_items, const pgh_item *items, int n
                     (int)n_c, hp.n_slots, hp.ordered);
     // chunks of less than 64 suit the other kernels only (a tree's lists are
     // for the Newton force, lists of few i-particles for k_batch_table)
-    if (c->hp.chunk < 64 && !p->tree_owned && !p->few) return near_fill(c, p, n_items, items, ni_total, nj_total);
+    if (hp.chunk < 64 && !p->tree_owned && !p->few) {
+        st = near_fill(c, p, n_items, items, ni_total, nj_total);
+        if (st) reset_plan(p);
+        return st;
+    }
     return PGH_OK;
 }
 
