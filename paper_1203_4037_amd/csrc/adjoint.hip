@@ -32,6 +32,7 @@
 
 #include "table_pairs.h"
 #include "pgh_internal.h"
+#include "rows.h"
 
 namespace pgh {
 
@@ -360,15 +361,6 @@ __global__ void __launch_bounds__(256) k_newton_bwd_j(int nj, const float4 *__re
 // ---------------------------------------------------------------------------
 // table-force adjoint over a plan
 // ---------------------------------------------------------------------------
-
-__device__ __forceinline__ void wave_sync()
-{
-    // LDS operations of one wave complete in order; the fences keep the
-    // compiler from moving tile reads across the writes of other lanes.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The table-force adjoint over the lists of a plan.  Task kinds (one index
 // space):

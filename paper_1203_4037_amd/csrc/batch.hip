@@ -351,7 +351,7 @@ hipError_t launch_newton_batch(const BatchArgs &a, int variant, bool refine, boo
     // 16: 4000 lists of 64 x 512 59.4, 57.1; 500 of 256 x 4096 211.8, 203.1; 1000
     // tree lists 208, 201), the smaller loop for longer queues (5000 tree lists
     // 834, 841; 20000 of 40 x 33 25.9, 26.2)
-    if (variant < 0) variant = a.n_tasks <= 16384 ? kDeepVariant : 0;
+    if (variant < 0) variant = a.n_tasks <= 2 * batch_resident_waves(num_cu) ? kDeepVariant : 0;
     return launch(newton_kernel(refine, guard, phi, variant), a, num_cu, s, phi);
 }
 

@@ -20,6 +20,7 @@
 #define PGH_HD __host__ __device__
 #endif
 #include "plan_expand.h"
+#include "rows.h"
 
 namespace pgh {
 
@@ -137,15 +138,6 @@ __device__ __forceinline__ void set_wave_prio(unsigned long long rem, unsigned l
         __builtin_amdgcn_s_setprio(1);
     else
         __builtin_amdgcn_s_setprio(0);
-}
-
-// LDS operations of one wave complete in order; this keeps the compiler
-// from moving reads of a wave's tile above the writes of its other lanes.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Coordinate of padding j-records: far enough that every pair term with them

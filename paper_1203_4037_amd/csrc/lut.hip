@@ -541,11 +541,11 @@ k_table_near(TableArgs a)
                 to_total();
                 fresh = 1;
             }
-            wave_sync_tile();  // the previous step's reads are done
+            wave_sync();  // the previous step's reads are done
             // (dropped, or past the end and so the last record again: without
             // its mass, so that the whole path adds zero for it)
             tile[filter_slot(lane)] = make_float4(v.x, v.y, v.z, keep ? v.w : 0.f);
-            wave_sync_tile();
+            wave_sync();
             const float4 *mine = tile + (lane & 32);
             bool direct = blind > 0;
             unsigned m[NC];

@@ -31,7 +31,9 @@
 //
 // Accuracy.  Sums over a tile are formed in fresh registers and added to
 // the running totals once per tile, so FP32 rounding grows with
-// JT + nj/JT rather than nj.
+// JT + nj/JT rather than nj.  In the rows kernel a lane's sum has the
+// nj / (NT S) terms of its own records (S shares), and the NT lanes' sums meet in
+// a tree: 4096 + 10 steps for 10^6 j-particles.
 #include <algorithm>
 
 #include "newton_pair.h"

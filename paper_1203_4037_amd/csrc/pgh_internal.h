@@ -181,8 +181,8 @@ hipError_t allow_dynamic_lds(const void *kernel, size_t bytes);
 int newton_allpairs_variants();
 const char *newton_allpairs_variant_name(int v);
 int newton_allpairs_default(int ni, int nj, int num_cu);
-int newton_allpairs_rows();
-int newton_allpairs_mutual();  // the variant that needs no j-split for large i-sets
+int newton_allpairs_rows();    // the variant that needs no j-split for large i-sets
+int newton_allpairs_mutual();  // and the one that evaluates each pair of a set once
 int newton_allpairs_split(int ni, int nj, int variant, size_t part_cap);
 hipError_t launch_newton_allpairs(const NewtonArgs &a, int variant, bool refine, bool guard,
                                   int S, hipStream_t s);

@@ -1,6 +1,7 @@
 // The "rows" mapping of the all-pairs launches (newton.hip, lut.hip): a
 // workgroup holds a few i-particles as wave-uniform values, its lanes take the
-// j-particles, and the lanes' sums meet at the end.
+// j-particles, and the lanes' sums meet at the end.  And what other kernels too do
+// across the lanes of a wave.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -34,6 +35,15 @@ __device__ __forceinline__ float dpp_f32(float v)
 {
     return __uint_as_float(
         (unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+
+// LDS operations of one wave complete in order; this keeps the compiler
+// from moving reads of a wave's tile above the writes of its other lanes.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // The sum over each row of 16 lanes, in all of them (row_ror 8, 4, 2, 1).

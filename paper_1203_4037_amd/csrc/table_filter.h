@@ -31,6 +31,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "rows.h"
 #include "table_pairs.h"
 
 namespace pgh {
@@ -39,7 +40,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
 
 constexpr float kFilterNorm = 1.0f - 0x1p-14f;
 constexpr float kFilterCut = 1.0f + 0x1p-13f;
@@ -82,7 +82,7 @@ __device__ __forceinline__ FilterOps filter_ops(const unsigned *k0, const unsign
     FilterOps o;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const u32x2v r = __builtin_amdgcn_permlane32_swap(k0[w], k1[w], false, false);
+        const u32x2 r = __builtin_amdgcn_permlane32_swap(k0[w], k1[w], false, false);
         o.t[0][w] = r.x;
         o.t[1][w] = r.y;
     }
@@ -120,17 +120,10 @@ __device__ __forceinline__ FilterOps filter_cols(float x, float y, float z, floa
 // A lane's value of particle l mod 32 and of particle 32 + l mod 32.
 __device__ __forceinline__ void both_halves(float v, float *o)
 {
-    const u32x2v r =
+    const u32x2 r =
         __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     o[0] = __uint_as_float(r.x);
     o[1] = __uint_as_float(r.y);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float row_ror(float v)
-{
-    return __uint_as_float(
-        (unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
 }
 
 // The least and the greatest of a wave's 64 values (all lanes active, none a
@@ -139,10 +132,10 @@ __device__ __forceinline__ float row_ror(float v)
 template <class Op>
 __device__ __forceinline__ float wave_fold(float v, Op op)
 {
-    v = op(v, row_ror<0x128>(v));
-    v = op(v, row_ror<0x124>(v));
-    v = op(v, row_ror<0x122>(v));
-    v = op(v, row_ror<0x121>(v));
+    v = op(v, dpp_f32<0x128>(v));
+    v = op(v, dpp_f32<0x124>(v));
+    v = op(v, dpp_f32<0x122>(v));
+    v = op(v, dpp_f32<0x121>(v));
     const int u = (int)__float_as_uint(v);
     auto row = [&](int l) { return __uint_as_float((unsigned)__builtin_amdgcn_readlane(u, l)); };
     return op(op(row(0), row(16)), op(row(32), row(48)));
@@ -163,15 +156,6 @@ __device__ __forceinline__ int lanes_below(unsigned long long who)
 {
     return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(who >> 32),
                                           __builtin_amdgcn_mbcnt_lo((unsigned)who, 0u));
-}
-
-// LDS operations of one wave complete in order; this keeps the compiler
-// from moving reads of a wave's tile above the writes of its other lanes.
-__device__ __forceinline__ void wave_sync_tile()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // The candidates of 64 rows for the column lane mod 32 of one operand: bit
