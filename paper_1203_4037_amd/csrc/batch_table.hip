@@ -516,12 +516,14 @@ k_batch_table_near(BatchArgs a)
                                 table_pairs_v<N, false, PHI>(r, px, py, pz, tab, kd, tx, ty, tz, tp);
                             }
                         };
+                        // (one and two records at a time: with two and four some registers
+                        // of the rounds below spill, 4^3-cell lists 18.8 -> 19.3 us)
                         if (n_i > 32) {
-#pragma unroll MOM ? 1 : 2
+#pragma unroll 1
                             for (int p = 0; p < 32; ++p)
                                 pairs(mine[p], std::integral_constant<int, 2>{});
                         } else {
-#pragma unroll MOM ? 2 : 4
+#pragma unroll MOM ? 1 : 2
                             for (int p = 0; p < 32; ++p)
                                 pairs(mine[p], std::integral_constant<int, 1>{});
                         }
@@ -692,15 +694,14 @@ const char *table_batch_variant_name(int v)
 // The near kernel pays per list entry and column of 32 i-particles, whatever the
 // chunk holds and wherever most pairs are; k_batch_table gives a chunk of at most
 // 16 four times the lanes.  us a call of 4096 lists of n_i x 1500 with 1, 10, 25 and
-// 100% of the pairs inside, k_batch_table (alike for all) and near: n_i = 8 42: 32,
-// 53, 72, 105; 16 45: 35, 56, 73, 104; 24 75: 38, 58, 75, 105; 32 75: 38, 58, 76, 105;
-// 64 140: 49, 87, 148, 174; 200 400: 155, 264, 410, 575.  So lists of few i-particles,
-// as of single cells, take the former: up to 1.3 times the time with hardly
-// any pair inside, never 2.5 times with many.  Which pairs are inside isn't
-// known before the call: for lists of more i-particles the near kernel costs
-// 1.25 to 1.4 times the other's time where half of the pairs or more are (or a table
-// whose last node is not zero makes every pair count), against 2 times less with
-// one in a hundred; the tuner (pgh_autotune_plan) tells.
+// 100% of the pairs inside, k_batch_table (much alike for all) and near: n_i = 16 41:
+// 35, 56, 74, 108; 32 75: 37, 58, 78, 108; 64 140: 49, 87, 157, 183; 200 400: 148, 266,
+// 404, 563.  So lists of few i-particles, as of single cells, take the former: up to
+// 1.2 times the time with hardly any pair inside, never 2.5 times with many.
+// Which pairs are inside isn't known before the call: lists of more i-particles pay
+// 1.3 to 1.45 times the former's time where half of the pairs or more are (or a
+// table whose last node is not zero makes every pair count), against a half to a third of
+// it with one in a hundred; the tuner (pgh_autotune_plan) times both.
 bool table_batch_few(long long n_rows, long long n_chunks) { return n_rows <= 16 * n_chunks; }
 
 int table_batch_default(bool few) { return few ? kPaperVariant : kNearVariant; }
