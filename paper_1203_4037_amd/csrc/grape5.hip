@@ -171,11 +171,13 @@ void g5_calculate_force_on_x(double (*xi)[3], double (*ai)[3], double *pi, int n
         st = pgh_calc_table(g5.ctx, ni, d, d + cap, d + 2 * cap, d + 3 * cap, d + 4 * cap,
                             d + 5 * cap, nullptr);
     else {
-        // Forces handed out in double show every change of the FP32 summation
-        // order, and a host program pays for conversions and transfers far
-        // more than for the kernel (N = 16384: 95 of 290 us), so these calls
-        // keep one order: the LDS-tile kernels with one, or from 2^17
-        // i-particles up four, per lane (64-record tiles for few i-particles)
+        // The Newton force keeps the kernels, and so the order of summation and every
+        // bit of the doubles handed out, that these calls have always had: LDS tiles
+        // with one, or from 2^17 i-particles up four, i-particles per lane (64-record tiles
+        // for few).  Up to N = 16384 the built-in choice gains nothing beside conversion
+        // and transfers (us a step, these and the choice: 1024 197, 194; 4096 267, 261;
+        // 16384 300, 300); 65536 1840, 1550; 131072 6500, 4830.  The table force takes the
+        // built-in choice, worth more (16384 280 -> 217, 65536 1530 -> 645).
         const int v = ni <= 4 * g5.num_cu ? 1 : ni >= (1 << 17) ? 3 : 0;
         if (!check(pgh_set_variant(g5.ctx, PGH_FAMILY_NEWTON_ALLPAIRS, v), "g5_calculate_force_on_x"))
             return;
