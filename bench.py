@@ -36,30 +36,30 @@ TABLE_FLOPS = 20  # per interaction, this project's count of the FP32 ops of the
 
 # Counters of the headline kernel per variant, from rocprofv3 --pmc runs of
 # `bench.py --no-extras --no-cpu --variant NAME --copy-calibration 256`:
-# FETCH_SIZE and WRITE_SIZE (KiB per dispatch of k_newton_allpairs), each
-# scaled by what the counter reads for a 256 MiB device-to-device copy, and
-# SQ_INSTS_VALU_FLOPS_FP32 (x 64 per dispatch / interactions).  Valid only for
+# FETCH_SIZE and WRITE_SIZE (KiB per call of the pair kernel, its strips added),
+# each scaled by what the counter reads for a 256 MiB device-to-device copy, and
+# SQ_INSTS_VALU_FLOPS_FP32 (x 64 per call / interactions).  Valid only for
 # the kernel sources they were taken on (their SHA-256); otherwise the bench
 # reports them as null.
 MEASURED = {
-    "sources_sha256": "325486dddd3df0a060c6bcc4e60caff126f310cb2756c711cf358a22d6b7ad8d",
+    "sources_sha256": "afadb49c45e83ff6ca6ce70decbfecd6c31df47b7ea4e8be2f8844ad7fbb9c23",
     # the 256 MiB copy: FETCH_SIZE 131091 KiB (x2.0), WRITE_SIZE 262144 KiB (x1.0)
     "fetch_factor": 2.0, "write_factor": 1.0,
     "by_variant": {
+        # two strips of blocks: 862 MiB of sums written, read back by k_mutual_combine
+        "mutual": {"fetch_kib": 163076, "write_kib": 882740, "valu_flops_per_interaction": 15.9},
+        # no partial sums; the 4 MiB j-set fetched many times by each XCD's L2
+        "rows": {"fetch_kib": 76806, "write_kib": 4096, "valu_flops_per_interaction": 21.0},
         # j split in 8 shares: 32 MiB of partial sums written, read back by k_combine_split
-        "ki=4 jt=256 u=2": {"fetch_kib": 18319.9, "write_kib": 32768,
+        "ki=4 jt=256 u=2": {"fetch_kib": 18311, "write_kib": 32768,
                             "valu_flops_per_interaction": 21.0},
         # j split in 2 shares
-        "ki=1 jt=256 u=8": {"fetch_kib": 17944.1, "write_kib": 8192,
-                            "valu_flops_per_interaction": 21.0},
-        "ki=1 jt=64 u=8": {"fetch_kib": 17943.1, "write_kib": 8192,
-                           "valu_flops_per_interaction": 21.1},
-        # j split in 4 shares
-        "ki=2 jt=256 u=4": {"fetch_kib": 17946.3, "write_kib": 16384,
+        "ki=1 jt=256 u=8": {"fetch_kib": 17941, "write_kib": 8192,
                             "valu_flops_per_interaction": 21.0},
     },
 }
 KERNEL_SOURCES = ("paper_1203_4037_amd/csrc/newton.hip", "paper_1203_4037_amd/csrc/newton_pair.h",
+                  "paper_1203_4037_amd/csrc/newton_mutual.hip", "paper_1203_4037_amd/csrc/rows.h",
                   "paper_1203_4037_amd/csrc/split.h")
 
 
@@ -84,7 +84,7 @@ def counters_for(variant_name, refine):
 
 
 def measured_traffic(variant_name, refine):
-    """HBM bytes per dispatch of the headline kernel, or None."""
+    """HBM bytes per call of the headline kernel, or None."""
     c = counters_for(variant_name, refine)
     if c is None:
         return None
@@ -910,7 +910,8 @@ def main():
                      "kernel_ms_median": r["kern_ms_median"], "kernel_ms_min": r["kern_ms_min"],
                      "flops_per_interaction": NEWTON_FLOPS,
                      # the FP32 flops the VALU counters count for this kernel (FMA = 2;
-                     # 21 per interaction, not the paper's 38) against the same peak;
+                     # 21 per interaction, 15.9 of the mutual kernel, not the paper's 38)
+                     # against the same peak;
                      # null when the counters were taken on other sources
                      "valu_flops_per_interaction": hw_flops,
                      "valu_tflops": hw_tflops,

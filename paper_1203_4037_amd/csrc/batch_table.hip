@@ -305,11 +305,11 @@ k_batch_table(BatchArgs a)
 // Per 64 x 64 pairs about 45 vector instructions for the operands, 64 for the
 // signs (one to two issue slots each) and four products, and 26 a round of
 // candidates, against 64 x 17 before; what is left is the launch, the first
-// loads' latency and the rounds.  Measured, per call in graphs of ten, with
-// k_batch_table (KI = 2, TW = 2, the default until then) and now: 4096 lists of
-// 4^3 cells 30.8 -> 18.1 us, 512 lists of 8^3 cells 95.6 -> 21.7, with the
-// potential 94.9 -> 22.7, with four times the cutoff (a tenth of the pairs
-// inside) 97.5 -> 62.
+// loads' latency and the rounds (a VALU instruction per SIMD every 10 cycles of
+// 4096 lists of 4^3 cells, every 8 of 512 of 8^3, counted).  Measured, per call in
+// graphs of twenty, with k_batch_table (KI = 2, TW = 2) and now: 4096 lists of 4^3
+// cells 31.3 -> 18.8 us, 512 lists of 8^3 cells 95.5 -> 21.9, with the potential 95 ->
+// 24.0; other shapes and densities at table_batch_few.
 //
 // MOM: also the i-side moments of the adjoint (table_tail_mom).
 template <int TB, bool PHI, int WPB, int SB, bool MOM>

@@ -16,10 +16,12 @@
 // ksum[block][4][n], and k_mutual_combine adds a particle's sums in order.  A
 // strip of blocks at a time where all would not fit the scratch memory.
 //
-// Bound by FP32 issue: 22 instructions and a root per pair with the potential, 3
-// of them the meetings of the lanes, which is what twelve particles per lane
-// are for (with eight 16.6 ms at N = 262144, with four 19.1, with sixteen, too
-// few waves, 17.2).  No branch inside the k-loop: past one the compiler moves
+// Bound by FP32 issue: 21.4 VALU instructions per pair with the potential (counted
+// at N = 262144, where k_newton_allpairs issues 28.4 for the pair's two terms), one
+// every 3.3 cycles of a SIMD with the three waves that 53 KB of LDS leave room for
+// (3.1 there, with eight); 3 of them are the meetings of the lanes, which is what
+// twelve particles per lane are for (with eight 16.6 ms at N = 262144, with four
+// 19.1, with sixteen, too few waves, 17.2).  No branch inside the k-loop: past one the compiler moves
 // the l-sums of four k, and spills their factors (113 ms).  Whole call, each
 // pair twice (rows, ki = 4) and here: N = 262144 19.0 -> 15.7 ms, 131072 5.0 ->
 // 4.0, 65536 1.27 -> 1.07, 40000 0.49 -> 0.46.
@@ -191,7 +193,6 @@ k_newton_mutual(MutualArgs a)
                             s[r][3] -= kr;
                             fp -= lr;
                         }
-                        
                     }
                     f[t][0] = fx, f[t][1] = fy, f[t][2] = fz, f[t][3] = fp;
                 }
@@ -272,10 +273,10 @@ __global__ void __launch_bounds__(256) k_mutual_combine(MutualArgs a, int block,
 // and for l the same with k and l exchanged and -d, where e is the same.  34
 // operations and one root against 2 x 26 and two.  The mapping is
 // k_newton_mutual's, with eight l-particles per lane: 15 registers each.
-// Bound by FP32 issue at three waves a SIMD, 39 instructions per pair, two
-// thirds of them multiply-adds of three registers (3.5 cycles each here, 3.1
-// in the other kernel at eight waves): N = 65536 2402 -> 2052 us, 131072 9481
-// -> 8084, 50000 1485 -> 1222.
+// Bound by FP32 issue: 39.6 VALU instructions per pair counted at N = 65536, two
+// thirds of them multiply-adds of three registers, one every 3.7 cycles of a
+// SIMD at three waves: N = 65536 2402 -> 2052 us, 131072 9481 -> 8084, 50000 1485
+// -> 1222.
 template <bool REFINE>
 __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3)))
 k_newton_mutual_bwd(MutualArgs a)
