@@ -125,7 +125,15 @@ PGH_API int pgh_set_rsqrt_refine(pgh_ctx *c, int on);
  * or NULL to skip the potential.  The sum runs over every j, so when an
  * i-particle is also a j-particle phi_i includes its self term -m_i/eps_i
  * (the paper's convention, Sec. 4.1); its force term is zero.  Outputs must
- * not alias inputs. */
+ * not alias inputs.
+ * The context keeps a scratch buffer for partial sums, grown on demand (which
+ * synchronises): at most 256 MiB for a split j-range, and up to 1 GiB for a call
+ * without eps2_i whose ni = nj >= 40000 (or with the variant "mutual").  There
+ * the device compares the i-positions with the j-memory and where they are the
+ * same evaluates each pair once; without memory for that, or in a capture
+ * with a smaller buffer, the call does without it.  A captured graph holds the
+ * buffer's address: later calls that grow it leave the graph invalid, as
+ * calls on other streams would overwrite it. */
 PGH_API int pgh_calc_newton(pgh_ctx *c, int ni, const float *xi, const float *yi, const float *zi,
                     const float *eps2_i, float *ax, float *ay, float *az, float *phi);
 
@@ -243,14 +251,18 @@ PGH_API int pgh_plan_free(pgh_ctx *c, pgh_plan *p);
  * list's chunks and the device writes the tasks from one compact entry per
  * list or pair; 0 = the host writes every task.  Both give the same tasks;
  * plans whose chunks of 64 would fill less than the device's resident waves
- * are always made on the host. */
+ * are made on the host all the same (but for tree walks, whose plans keep
+ * chunks of 64 at all sizes). */
 PGH_API int pgh_set_plan_expansion(pgh_ctx *c, int on_device);
 
 /* The number of waves the planner cuts the work of later plans (and tree
  * walks) for: groups are cut into chunks of 64, or of 32 or 16 i-particles
  * while fewer tasks than this would result, and long j-lists into parts of
  * an eighth of this count's average share of the work (the schedule of
- * Sec. 5.1's lists; it changes no result beyond FP32 summation order).  0
+ * Sec. 5.1's lists; it changes no result beyond FP32 summation order).  Plans cut
+ * below 64, of lists of more than 16 i-particles per chunk on average, also hold
+ * a second, coarser cut for the table kernel that leaves out the pairs beyond the
+ * cutoff (chunks of 32 or more, parts of a quarter of these waves' share).  0
  * (default) = the resident waves of the batched kernels on the context's
  * device; PGH_EINVAL if negative.  A tuning dimension for callers that
  * time plans (the binding's Context.plan_tuned). */
@@ -306,7 +318,8 @@ PGH_API int pgh_batch_table(pgh_ctx *c, const pgh_plan *p, const float *xi, cons
  *   gm_k = -sum_{l != k} rho^3 (w_l . d),  d = r_l - r_k,
  *   rho = (|d|^2 + eps2)^{-1/2}.
  * The self pair, whose term is identically zero, is skipped.  The particle
- * records are packed into context scratch (grown on demand, which
+ * records are packed into context scratch, and from n = 24000 on partial sums
+ * take up to 1 GiB of it (pgh_calc_newton's buffer; grown on demand, which
  * synchronises).  gx, gy, gz, gm: n outputs (gm may be NULL). */
 PGH_API int pgh_newton_allpairs_bwd(pgh_ctx *c, int n, const float *x, const float *y, const float *z,
                             const float *m, float eps2, const float *wx, const float *wy,
@@ -503,7 +516,9 @@ PGH_API int pgh_tree_build(pgh_ctx *c, pgh_tree *t, int n, const float *x, const
  * them.  record_src != 0 also keeps each entry's source (PGH_TREE_LIST_SRC).
  * The plan is made in compact form on the host (one entry per group or pair
  * of partly filled chunks) and expanded into its tasks on the device; it
- * holds the same tasks as pgh_plan_create would make from the lists.
+ * holds the same tasks as pgh_plan_create would make from the lists where these
+ * fill the device's resident waves in chunks of 64; smaller plans keep such
+ * chunks here, and cut lists into parts of 256 entries or more.
  * Synchronous.  PGH_ESTATE before a build; PGH_ERANGE when theta is too
  * small for the walk's frontier (more than 4096 nodes to test on one level
  * for one group) or the lists exceed 2^31 - 1 entries. */
