@@ -166,7 +166,10 @@ __global__ void __launch_bounds__(NT) k_table_allpairs(TableArgs a)
 // A step whose tests all found pairs of most of their i-particles inside is
 // followed by this many evaluated whole without a test.
 constexpr int kWholeSteps = 7;
-constexpr int kFreshSteps = 16;  // of k_table_near, in a sum before it is added to its total
+// k_table_near: a lane's sums are added to its totals before a step that finds this many
+// terms in them; a step with at most kLightHits candidates in every lane counts for as
+// many, any other for all its 32 rows.
+constexpr int kFreshTerms = 512, kLightHits = 4;
 
 // One j-record of the lane against Q uniform i-particles; s[k]: their sums.
 template <int Q, bool PHI>
@@ -500,10 +503,10 @@ k_table_near(TableArgs a)
         }
 #pragma unroll
         for (int q = 0; q < NC; ++q) tx[q] = ty[q] = tz[q] = tp[q] = 0.f;
-        // A column's sums of both halves' rows go to its words in LDS once per
-        // kFreshSteps steps, so that FP32 rounding grows with 32 kFreshSteps terms
-        // and the number of these sums, not with the wave's share of the list
-        // (10^6 neighbours of one mass: 1.6e-4 in one running sum).
+        // A column's sums of both halves' rows go to its words in LDS before they
+        // have many terms, so that FP32 rounding grows with kFreshTerms and the
+        // number of these sums, not with the wave's share of the list (10^6
+        // neighbours of one mass: 1.6e-4 in one running sum).
 #pragma unroll
         for (int q = 0; q < NC / 2; ++q) total[64 * q + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
         auto to_total = [&] {
@@ -523,7 +526,7 @@ k_table_near(TableArgs a)
             }
         };
 
-        int fresh = 0;  // steps in the sums
+        int fresh = 0;  // terms in a sum at most
         int blind = 0;  // steps still to be evaluated whole without a test
         for (int base = 0; base < nj; base += 64) {
             const float4 v = p0;
@@ -537,9 +540,9 @@ k_table_near(TableArgs a)
             // (each step is monotone: no pair with the chunk has a smaller |d|^2)
             const bool keep = valid && (whole || r2 < a.r2max || !ordinary(v.x, v.y, v.z, v.w));
             if (!__any(keep)) continue;
-            if (fresh++ == kFreshSteps) {
+            if (fresh >= kFreshTerms) {
                 to_total();
-                fresh = 1;
+                fresh = 0;
             }
             wave_sync();  // the previous step's reads are done
             // (dropped, or past the end and so the last record again: without
@@ -559,9 +562,11 @@ k_table_near(TableArgs a)
                 }
                 direct = __any(hits > 12 * NC);
                 if (direct) blind = kWholeSteps + 1;
+                else fresh += __any(hits > kLightHits) ? 32 : kLightHits;
             }
             if (direct) {
                 --blind;
+                fresh += 32;
                 const TableConsts kd = table_consts(a.c, a.smax, a.E, a.F, PHI ? 4 : 3);
 #pragma unroll (NC == 2 ? 4 : 2)
                 for (int p = 0; p < 32; ++p)
