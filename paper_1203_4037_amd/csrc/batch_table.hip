@@ -45,9 +45,8 @@ constexpr int kStaticRounds = 4;
 // (which break even at a quarter of the pairs inside: 4096 lists of 32 x 1500
 // 97 us with 12 of 32, 76 with 18).
 constexpr int kDirectHits = 24, kDirectHits1 = 18;
-// Records in a lane's sums before these are added to its totals, at least; half
-// of them, as the lane's partner has the others, and up to 64 SB more.
-constexpr int kFreshRows = 512;
+// and adds the sums of so many list entries, half of them in a lane, to the outputs.
+constexpr int kSegment = 2048;
 
 // The lanes of one task: lane (phase, row) holds slots q + k stride
 // (k < KI) of its chunk (i-particles i0 + slot, the chunk's partial-sum
@@ -308,8 +307,8 @@ k_batch_table(BatchArgs a)
 // loads' latency and the rounds (a VALU instruction per SIMD every 10 cycles of
 // 4096 lists of 4^3 cells, every 8 of 512 of 8^3, counted).  Measured, per call in
 // graphs of twenty, with k_batch_table (KI = 2, TW = 2) and now: 4096 lists of 4^3
-// cells 31.3 -> 18.8 us, 512 lists of 8^3 cells 95.5 -> 21.9, with the potential 95 ->
-// 24.0; other shapes and densities at table_batch_few.
+// cells 31.3 -> 17.4 us, 512 lists of 8^3 cells 95.5 -> 21.2, with the potential 95 ->
+// 23.7; other shapes and densities at table_batch_few.
 //
 // MOM: also the i-side moments of the adjoint (table_tail_mom).
 template <int TB, bool PHI, int WPB, int SB, bool MOM>
@@ -318,10 +317,8 @@ k_batch_table_near(BatchArgs a)
 {
     static_assert(!MOM || !PHI, "moments come without a potential");
     using Entry = std::conditional_t<PHI, float4, float2>;
-    constexpr int TW = MOM ? 3 : 1;  // words of four sums per i-particle
     __shared__ Entry stab[1 << TB];
     __shared__ float4 jt[WPB][64 * SB];
-    __shared__ float4 totals[WPB][TW][64];
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -399,10 +396,16 @@ k_batch_table_near(BatchArgs a)
         if (t_next < n_t && lane < 12) fld = ((const int *)(tbase + t_next))[lane];
 
         const int parts = tk.n_i2 > 0 ? 2 : 1;
-        for (int sub = 0; sub < parts; ++sub) {
+        // A list is taken kSegment entries at a time, each of which adds its sums to
+        // the outputs, so that FP32 rounding grows with kSegment / 2 and the number
+        // of segments, not with the list (400000 neighbours of one mass: 2.0e-3 in
+        // one running sum).
+        bool again = false;  // of a list begun before
+        for (int sub = 0; sub < parts;) {
             const int i_off = sub ? tk.i_off2 : tk.i_off, n_i = sub ? tk.n_i2 : tk.n_i;
-            const int j_off = sub ? tk.j_off2 : tk.j_off, n_j = sub ? tk.n_j2 : tk.n_j;
-            if (sub) begin(i_off, n_i, j_off, n_j);
+            const int j_off = sub ? tk.j_off2 : tk.j_off, n_all = sub ? tk.n_j2 : tk.n_j;
+            const int n_j = min(n_all, kSegment);
+            if (sub || again) begin(i_off, n_i, j_off, n_j);
 
             // the box around the chunk (lanes past its end hold its first
             // i-particle), or all space when nothing may be left out
@@ -425,42 +428,7 @@ k_batch_table_near(BatchArgs a)
             float tm[MOM ? 7 : 1][2];
 #pragma unroll
             for (int c = 0; c < (MOM ? 7 : 1); ++c) tm[c][0] = tm[c][1] = 0.f;
-            // Slot `lane`'s sums over the two halves' rows, which then start
-            // afresh.  Those of a long list go to the lane's words in LDS once
-            // per kFreshRows records evaluated, so that FP32 rounding grows with
-            // these and the number of such sums, not with the list (400000
-            // neighbours of one mass: 2.0e-3 in one running sum).
-            bool long_list = false;
-            int summed = 0;  // records in the sums
-            auto take = [&](float4 *v) {
-                auto slot = [&](float *u) {
-                    const float s0 = u[0] + __shfl_xor(u[0], 32), s1 = u[1] + __shfl_xor(u[1], 32);
-                    u[0] = u[1] = 0.f;
-                    return lane < 32 ? s0 : s1;
-                };
-                v[0] = make_float4(slot(tx), slot(ty), slot(tz), PHI ? slot(tp) : 0.f);
-                if constexpr (MOM) {
-                    v[1] = make_float4(slot(tm[0]), slot(tm[1]), slot(tm[2]), slot(tm[3]));
-                    v[2] = make_float4(slot(tm[4]), slot(tm[5]), slot(tm[6]), 0.f);
-                }
-                if (long_list) {
-#pragma unroll
-                    for (int w = 0; w < TW; ++w) {
-                        const float4 o = totals[wave][w][lane];
-                        v[w].x += o.x, v[w].y += o.y, v[w].z += o.z, v[w].w += o.w;
-                    }
-                }
-            };
-
             for (int base = 0; base < n_j; base += 64 * SB) {
-                if (summed >= kFreshRows) {
-                    float4 v[TW];
-                    take(v);
-#pragma unroll
-                    for (int w = 0; w < TW; ++w) totals[wave][w][lane] = v[w];
-                    long_list = true;
-                    summed = 0;
-                }
                 wave_sync();  // the previous tile's reads are done
                 int kept = 0;
 #pragma unroll
@@ -486,7 +454,6 @@ k_batch_table_near(BatchArgs a)
                 }
                 wave_sync();
                 if (base + 64 * SB < n_j) load(j_off, n_j, base + 64 * SB);
-                summed += kept;
 
                 for (int k0 = 0; k0 < kept; k0 += 64) {
                     const float4 *rows64 = tile + k0;
@@ -517,7 +484,7 @@ k_batch_table_near(BatchArgs a)
                             }
                         };
                         // (one and two records at a time: with two and four some registers
-                        // of the rounds below spill, 4^3-cell lists 18.8 -> 19.3 us)
+                        // of the rounds below spill, 4^3-cell lists 17.4 -> 18.2 us)
                         if (n_i > 32) {
 #pragma unroll 1
                             for (int p = 0; p < 32; ++p)
@@ -554,30 +521,51 @@ k_batch_table_near(BatchArgs a)
                 }
             }
 
-            float4 o[TW];
-            take(o);
-            if (lane < n_i) {
-                if (tk.n_parts <= 1) {
-                    put(a.ax + i_off, lane, o[0].x);
-                    put(a.ay + i_off, lane, o[0].y);
-                    put(a.az + i_off, lane, o[0].z);
-                    if (PHI) put(a.phi + i_off, lane, o[0].w);
-                    if constexpr (MOM) {
-                        const float om[7] = {o[1].x, o[1].y, o[1].z, o[1].w, o[2].x, o[2].y, o[2].z};
+            // the two halves' rows; lane l then keeps slot l
+            auto slots = [&](const float *v) {
+                const float s0 = v[0] + __shfl_xor(v[0], 32), s1 = v[1] + __shfl_xor(v[1], 32);
+                return lane < 32 ? s0 : s1;
+            };
+            const float ox = slots(tx), oy = slots(ty), oz = slots(tz);
+            const float op = PHI ? slots(tp) : 0.f;
+            float om[MOM ? 7 : 1];
 #pragma unroll
-                        for (int c = 0; c < 7; ++c)
-                            put(a.mom + (size_t)c * a.ni_total + i_off, lane, om[c]);
+            for (int c = 0; c < (MOM ? 7 : 1); ++c) om[c] = MOM ? slots(tm[c]) : 0.f;
+            if (lane < n_i) {
+                auto out = [&](float *p, float v) {
+                    p += i_off;
+                    put(p, lane, again ? at(p, lane) + v : v);
+                };
+                if (tk.n_parts <= 1) {
+                    out(a.ax, ox);
+                    out(a.ay, oy);
+                    out(a.az, oz);
+                    if (PHI) out(a.phi, op);
+                    if constexpr (MOM) {
+#pragma unroll
+                        for (int c = 0; c < 7; ++c) out(a.mom + (size_t)c * a.ni_total, om[c]);
                     }
                 } else {
                     // partial sums of one part of a split j-list (k_combine)
                     const size_t q = (size_t)(tk.slot + tk.part) * 64 + (sub ? tk.n_i : 0) + lane;
-                    a.partial[q] = o[0];
+                    auto add = [&](float4 *p, float4 v) {
+                        if (again) v.x += p->x, v.y += p->y, v.z += p->z, v.w += p->w;
+                        *p = v;
+                    };
+                    add(a.partial + q, make_float4(ox, oy, oz, op));
                     if constexpr (MOM) {
-                        a.mpartial[2 * q] = o[1];
-                        a.mpartial[2 * q + 1] = o[2];
+                        add(a.mpartial + 2 * q, make_float4(om[0], om[1], om[2], om[3]));
+                        add(a.mpartial + 2 * q + 1, make_float4(om[4], om[5], om[6], 0.f));
                     }
                 }
             }
+            again = n_all > kSegment;
+            if (!again)
+                ++sub;
+            else if (sub)
+                tk.j_off2 += kSegment, tk.n_j2 -= kSegment;
+            else
+                tk.j_off += kSegment, tk.n_j -= kSegment;
         }
         t = t_next;
         if (t < n_t) {
@@ -629,8 +617,8 @@ TableKernelPick pick_near(int tb, bool phi)
     if (tb <= 12)
         return {phi ? k_batch_table_near<12, true, kWideWaves, 2, false>
                     : k_batch_table_near<12, false, kWideWaves, 2, false>, kWideWaves};
-    return {phi ? k_batch_table_near<13, true, kWideWaves, 1, false>
-                : k_batch_table_near<14, false, kWideWaves, 1, false>, kWideWaves};
+    return {phi ? k_batch_table_near<13, true, kWideWaves, 2, false>
+                : k_batch_table_near<14, false, kWideWaves, 2, false>, kWideWaves};
 }
 
 struct TableBatchVariant {
@@ -695,8 +683,8 @@ const char *table_batch_variant_name(int v)
 // chunk holds and wherever most pairs are; k_batch_table gives a chunk of at most
 // 16 four times the lanes.  us a call of 4096 lists of n_i x 1500 with 1, 10, 25 and
 // 100% of the pairs inside, k_batch_table (much alike for all) and near: n_i = 16 41:
-// 35, 56, 74, 108; 32 75: 37, 58, 78, 108; 64 140: 49, 87, 157, 183; 200 400: 148, 266,
-// 404, 563.  So lists of few i-particles, as of single cells, take the former: up to
+// 35, 56, 74, 108; 32 75: 36, 57, 76, 109; 64 140: 47, 85, 149, 182; 200 400: 152, 269,
+// 440, 560.  So lists of few i-particles, as of single cells, take the former: up to
 // 1.2 times the time with hardly any pair inside, never 2.5 times with many.
 // Which pairs are inside isn't known before the call: lists of more i-particles pay
 // 1.3 to 1.45 times the former's time where half of the pairs or more are (or a

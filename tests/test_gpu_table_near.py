@@ -325,7 +325,8 @@ def test_near_sums_do_not_grow_with_the_list(pgh, ctx, order, spread):
     some beyond the cutoff, in candidates' rounds where they are the most), in a
     row or among as many far ones.  The potential counts them, so each of the terms is the
     same number and a running sum errs in one direction.  Fresh sums of at most
-    512 terms: 512 + a wave's 62500 / 256 + 16 waves' additions."""
+    543 terms, so at most 62500 / 512 of them, and 16 waves: less than the 512 +
+    62500 / 256 + 16 additions allowed."""
     n = 1000003
     rng = np.random.default_rng(4)
     rcut = 0.5
@@ -352,8 +353,9 @@ def test_near_sums_do_not_grow_with_the_list(pgh, ctx, order, spread):
 def test_batched_sums_do_not_grow_with_the_list(pgh, ctx, spread, ni, moments):
     """2048 lists over one range of 400000 neighbours of mass 0.7, which a plan
     does not cut: as above, or S (the moments' first row, sum of m g) where the
-    table itself counts.  Fresh sums of at most 512 terms, added 400000 / 256
-    times, then over two halves."""
+    table itself counts.  A lane's sum of at most 1024 terms (of a segment of 2048
+    entries), n / 2048 of them, then over two halves: less than the 512 + n / 256 + 2
+    additions allowed."""
     n, lists = 400000, 2048
     rng = np.random.default_rng(4)
     rcut = 0.5
