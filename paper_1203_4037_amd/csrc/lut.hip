@@ -414,9 +414,9 @@ __global__ void __launch_bounds__(1024) k_table_density(TableArgs a, int *dense)
 // most of whose pairs are inside is evaluated whole, and the next kWholeSteps
 // after it without a test.  The waves' sums meet in LDS at the end.
 //
-// Per 64 records and column 79 VALU instructions (counted; 32 of them signs, 17 its
+// Per 64 records and column 78 VALU instructions (counted; 32 of them signs, 17 its
 // share of the records' terms) and two products, against 64 x 17 / 2 before: bound by
-// the issue of these, one every 4.3 cycles of a SIMD, the matrix cores busy a fifth
+// the issue of these, one every 4.4 cycles of a SIMD, the matrix cores busy a fifth
 // of the time.  N = 65536 (T16, phi off) in a box of 21 cutoffs 1121 -> 280 us, of 5
 // cutoffs 1138 -> 478, with most pairs inside 1216 -> 1390 (auto_kernel leaves that to
 // k_table_allpairs); N = 16384 81 -> 28 us.
