@@ -41,10 +41,14 @@ namespace {
 // plans of at most this many tasks per wave run in the static order
 constexpr int kStaticRounds = 4;
 // k_batch_table_near evaluates a block of 64 records whole when some lane has
-// more candidates than this among its 2 x 32 pairs, or its 32 of a single column
-// (which break even at a quarter of the pairs inside: 4096 lists of 32 x 1500
-// 97 us with 12 of 32, 76 with 18).
+// more candidates than kDirectHits among its 2 x 32 pairs, or kDirectHits1 among
+// its 32 of a single column (which break even at a quarter of the pairs inside: 4096
+// lists of 32 x 1500 97 us with 12 of 32, 76 with 18), and after one with more than
+// kMostHits the next kWholeBlocks without looking (64 x 1500 with every pair inside 182
+// -> 158 us, with hardly any 17.3 -> 17.5; with moments or a potential, where it gained
+// less than it cost the others, every block is looked at),
 constexpr int kDirectHits = 24, kDirectHits1 = 18;
+constexpr int kMostHits = 36, kMostHits1 = 22, kWholeBlocks = 7;
 // and adds the sums of so many list entries, half of them in a lane, to the outputs.
 constexpr int kSegment = 2048;
 
@@ -297,8 +301,8 @@ k_batch_table(BatchArgs a)
 //     rows in lanes < 32, half in the others;
 //   * each lane evaluates its own candidates one after another, in FP32 as
 //     k_batch_table does, reading each record by its own index.  Where the
-//     pairs inside the cutoff are not few (some lane has more than
-//     kDirectHits of 64) the 64 records are evaluated whole.
+//     pairs inside the cutoff are not few (kDirectHits) the 64 records are
+//     evaluated whole, and where they are the most the next ones too.
 // A paired task is its two chunks in turn.
 //
 // Per 64 x 64 pairs about 45 vector instructions for the operands, 64 for the
@@ -307,8 +311,8 @@ k_batch_table(BatchArgs a)
 // loads' latency and the rounds (a VALU instruction per SIMD every 10 cycles of
 // 4096 lists of 4^3 cells, every 8 of 512 of 8^3, counted).  Measured, per call in
 // graphs of twenty, with k_batch_table (KI = 2, TW = 2) and now: 4096 lists of 4^3
-// cells 31.3 -> 17.4 us, 512 lists of 8^3 cells 95.5 -> 21.2, with the potential 95 ->
-// 23.7; other shapes and densities at table_batch_few.
+// cells 31.3 -> 17.5 us, 512 lists of 8^3 cells 95.5 -> 21.6, with the potential 95 ->
+// 24.0; other shapes and densities at table_batch_few.
 //
 // MOM: also the i-side moments of the adjoint (table_tail_mom).
 template <int TB, bool PHI, int WPB, int SB, bool MOM>
@@ -316,6 +320,7 @@ __global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(M
 k_batch_table_near(BatchArgs a)
 {
     static_assert(!MOM || !PHI, "moments come without a potential");
+    constexpr bool kLook = MOM || PHI;  // before every block (kMostHits)
     using Entry = std::conditional_t<PHI, float4, float2>;
     __shared__ Entry stab[1 << TB];
     __shared__ float4 jt[WPB][64 * SB];
@@ -428,6 +433,7 @@ k_batch_table_near(BatchArgs a)
             float tm[MOM ? 7 : 1][2];
 #pragma unroll
             for (int c = 0; c < (MOM ? 7 : 1); ++c) tm[c][0] = tm[c][1] = 0.f;
+            int blind = 0;  // blocks still to be evaluated whole without a test
             for (int base = 0; base < n_j; base += 64 * SB) {
                 wave_sync();  // the previous tile's reads are done
                 int kept = 0;
@@ -458,13 +464,20 @@ k_batch_table_near(BatchArgs a)
                 for (int k0 = 0; k0 < kept; k0 += 64) {
                     const float4 *rows64 = tile + k0;
                     const bool valid = k0 + lane < kept;
-                    const FilterOps rows =
-                        filter_rows_of(rows64[filter_slot(lane)], valid, cx, cy, cz);
-                    const unsigned m0 = filter_mask(rows, cols.t[0]);
-                    unsigned m1 = 0;
-                    if (n_i > 32) m1 = filter_mask(rows, cols.t[1]);
                     const float4 *mine = rows64 + (lane & 32);  // this half's rows
-                    if (__any(__popc(m0) + __popc(m1) > (n_i > 32 ? kDirectHits : kDirectHits1))) {
+                    unsigned m0 = 0, m1 = 0;
+                    if (kLook || blind == 0) {
+                        const FilterOps rows =
+                            filter_rows_of(rows64[filter_slot(lane)], valid, cx, cy, cz);
+                        m0 = filter_mask(rows, cols.t[0]);
+                        if (n_i > 32) m1 = filter_mask(rows, cols.t[1]);
+                        const int hits = __popc(m0) + __popc(m1);
+                        const bool most = !kLook && __any(hits > (n_i > 32 ? kMostHits : kMostHits1));
+                        if (__any(hits > (n_i > 32 ? kDirectHits : kDirectHits1)))
+                            blind = most ? kWholeBlocks + 1 : 1;
+                    }
+                    if (blind > 0) {
+                        --blind;
                         // rows past the last kept one are made far away, massless
                         if (!valid)
                             tile[k0 + filter_slot(lane)] = make_float4(kFar, kFar, kFar, 0.f);
@@ -483,14 +496,12 @@ k_batch_table_near(BatchArgs a)
                                 table_pairs_v<N, false, PHI>(r, px, py, pz, tab, kd, tx, ty, tz, tp);
                             }
                         };
-                        // (one and two records at a time: with two and four some registers
-                        // of the rounds below spill, 4^3-cell lists 17.4 -> 18.2 us)
                         if (n_i > 32) {
-#pragma unroll 1
+#pragma unroll MOM ? 1 : 2
                             for (int p = 0; p < 32; ++p)
                                 pairs(mine[p], std::integral_constant<int, 2>{});
                         } else {
-#pragma unroll MOM ? 1 : 2
+#pragma unroll 2
                             for (int p = 0; p < 32; ++p)
                                 pairs(mine[p], std::integral_constant<int, 1>{});
                         }
@@ -683,13 +694,14 @@ const char *table_batch_variant_name(int v)
 // chunk holds and wherever most pairs are; k_batch_table gives a chunk of at most
 // 16 four times the lanes.  us a call of 4096 lists of n_i x 1500 with 1, 10, 25 and
 // 100% of the pairs inside, k_batch_table (much alike for all) and near: n_i = 16 41:
-// 35, 56, 74, 108; 32 75: 36, 57, 76, 109; 64 140: 47, 85, 149, 182; 200 400: 152, 269,
-// 440, 560.  So lists of few i-particles, as of single cells, take the former: up to
-// 1.2 times the time with hardly any pair inside, never 2.5 times with many.
+// 35, 56, 74, 95; 32 75: 38, 58, 77, 94; 64 140: 49, 86, 146, 158; 200 400: 149, 269,
+// 401, 510.  So lists of few i-particles, as of single cells, take the former: up to
+// 1.2 times the time with hardly any pair inside, never 2.3 times with many.
 // Which pairs are inside isn't known before the call: lists of more i-particles pay
-// 1.3 to 1.45 times the former's time where half of the pairs or more are (or a
-// table whose last node is not zero makes every pair count), against a half to a third of
-// it with one in a hundred; the tuner (pgh_autotune_plan) times both.
+// 1.1 to 1.3 times the former's time where half of the pairs or more are (or a table
+// whose last node is not zero makes every pair count; with fewer tasks than SIMDs more:
+// 300 lists of 64 x 400 24 us, 13 the former), against a half to a third of it with one
+// in a hundred (there 10); the tuner (pgh_autotune_plan) times both.
 bool table_batch_few(long long n_rows, long long n_chunks) { return n_rows <= 16 * n_chunks; }
 
 int table_batch_default(bool few) { return few ? kPaperVariant : kNearVariant; }
